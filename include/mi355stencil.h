@@ -118,14 +118,16 @@ int stencil_plan_varcoef(st_plan** out, int64_t rows, int64_t cols, double bound
 int stencil_destroy(st_plan* plan);
 
 /* stencil_set_blocking -- choose the temporal-blocking depth tb (steps per HBM
- * round trip, 1..16; up to 64 steps per halo swap for ST_VARIANT_RESIDENT) and the output tile (tile_x, tile_y) of the tiled
- * kernel; 0 keeps the current value.  The result is bitwise independent of
+ * round trip, 1..16; up to 64 steps per halo swap for ST_VARIANT_RESIDENT) and the tile (tile_x, tile_y) of the tiled
+ * kernels; 0 keeps the current value.  The result is bitwise independent of
  * these choices.  Errors: ST_EINVAL (value out of range), ST_EUNSUPPORTED
  * (tile not instantiated; the supported set is listed by stencil_tiles()). */
 int stencil_set_blocking(st_plan* plan, int tb, int tile_x, int tile_y);
 
 /* kernel variants of the constant-weight sweep */
-#define ST_VARIANT_TILED   0  /* one launch per pass, one tile per workgroup                    */
+#define ST_VARIANT_TILED   0  /* one launch per pass, one tile per workgroup, kept in registers
+                                 (tile_x and tile_y choose among its tile sizes); passes over
+                                 grids large enough for it run on the marching kernels           */
 #define ST_VARIANT_STREAM  1  /* persistent workgroups; the next tile is copied into LDS by DMA
                                  while the current one computes (FP32, cols % 4 == 0)          */
 #define ST_VARIANT_MARCH   2  /* each wavefront walks a column band down the grid, rows in a
@@ -299,8 +301,8 @@ int stencil_norms(const st_plan* plan, const void* u_prev, const void* u, double
 
 /* stencil_autotune -- time every supported (variant, tb, tile) candidate on the caller's buffers
  * for `sample_steps` steps (one warm-up run, then the better of two timed runs) and keep the
- * fastest in the plan (variant, blocking and segment length).  Candidates: LDS tiles with tb in
- * {1, 2, 3, 4, 6, 8} within their LDS budget; marching with one, four and, when cols % 8 == 0,
+ * fastest in the plan (variant, blocking and segment length).  Candidates: register tiles with tb in
+ * {1, 2, 3, 4, 6, 8, 12, 16} and LDS tiles with tb in {1, 2, 3, 4, 6, 8} within their budgets; marching with one, four and, when cols % 8 == 0,
  * eight columns per lane at every depth each offers, each depth above 1 also with segments of
  * at least 1/2 (when that is 2 rows or more), 1, 2, 4 and 8 x r (tb - 1) rows
  * (stencil_set_march_segment); the resident variant at swap depths {1, 2, 4, 8, 12, 16, 24, 32, 48}
@@ -330,8 +332,8 @@ int stencil_solve_ws_bytes(const st_plan* plan, int64_t check_every, size_t* byt
  * device and read back; the loop stops once it is <= tol or after max_steps steps.  `out`
  * receives the last iterate, *steps_done the number of steps taken (a multiple of check_every
  * unless max_steps cut the last interval), *rel_residual the last residual.  The result is
- * bitwise the same as stencil_run(plan, in, out, *steps_done).  With a marching variant the
- * test itself runs on the device and raises a flag that turns the passes enqueued after
+ * bitwise the same as stencil_run(plan, in, out, *steps_done).  With a marching or the tiled
+ * variant the test itself runs on the device and raises a flag that turns the passes enqueued after
  * convergence into no-ops, so the host enqueues checks in chunks of 1, 2, 4, ... 64 and
  * synchronises once per chunk; other variants synchronise at every check.  The call returns
  * with the stream idle.  The workspace (stencil_solve_ws_bytes) holds the previous iterate,

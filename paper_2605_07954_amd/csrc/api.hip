@@ -544,7 +544,7 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
     float best_ms = 1e30f;
     int tiles[32];
     const int nt = supported_tiles(tiles, 16);
-    static const int kTb[] = {1, 2, 3, 4, 6, 8};
+    static const int kTb[] = {1, 2, 3, 4, 6, 8, 12, 16};
     hipEvent_t e0, e1;
     ST_HIP_CHECK(hipEventCreate(&e0));
     ST_HIP_CHECK(hipEventCreate(&e1));
@@ -571,13 +571,17 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
         } else if (is_march(var)) {
             for (int tb = 1; tb <= max_tb(plan, tx, ty) && nc < 16; ++tb) cands[nc++] = tb;
         } else {
-            for (int tb : kTb) cands[nc++] = tb;
+            // register tiles also pay at 12 and 16 levels (small grids, where launches cost most)
+            for (int tb : kTb)
+                if (tb <= 8 || (var == VARIANT_TILED && plan->kind == KIND_CONST)) cands[nc++] = tb;
         }
         for (int k = 0; k < nc && rc == ST_OK; ++k) {
             const int tb = cands[k];
             if (plan->kind == KIND_CONST && tb > max_tb(plan, tx, ty)) continue;
             if (plan->kind == KIND_VARCOEF && varcoef_lds_bytes(tb, tx, ty) > lds_limit()) continue;
             if (tb > sample_steps) continue;
+            // a pass that marches anyway has no tile: one candidate of the four
+            if (var == VARIANT_TILED && ti > 0 && tiled_march_columns(plan, tb)) continue;
             plan->tb = tb;
             plan->tile_x = tx;
             plan->tile_y = ty;
@@ -739,13 +743,14 @@ int stencil_solve(st_plan* plan, const void* in, void* out, int64_t max_steps, i
         }
     } guard{plan, plan->flags};
     plan->flags &= ~ST_FLAG_GRAPH;
-    // Marching plans: the convergence test runs on the device, where it raises a flag that turns
+    // Marching and tiled plans: the convergence test runs on the device, where it raises a flag that turns
     // the remaining passes and reductions into no-ops, so the host enqueues checks in growing
     // chunks (1, 2, 4, ... 64) and synchronises once per chunk, not once per check.  Other
     // variants read the residual back at every check.
-    const bool on_device = plan->kind == KIND_CONST && !(plan->flags & ST_FLAG_NAIVE) && is_march(plan->variant) &&
-                           march_usable(plan) &&
-                           plan->tb <= march_max_tb(plan->shape, plan->radius, march_vmax(plan->variant));
+    const bool on_device = plan->kind == KIND_CONST && !(plan->flags & ST_FLAG_NAIVE) &&
+                           (plan->variant == VARIANT_TILED ||
+                            (is_march(plan->variant) && march_usable(plan) &&
+                             plan->tb <= march_max_tb(plan->shape, plan->radius, march_vmax(plan->variant))));
     if (on_device) {
         clear_stale_error();
         hipLaunchKernelGGL(solve_reset, dim3(1), dim3(1), 0, s, rec);

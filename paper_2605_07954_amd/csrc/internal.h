@@ -103,6 +103,8 @@ size_t elem_size(int storage);
 // launchers (sweep.hip / varcoef.hip); return ST_OK or an error code
 int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa, int levels, hipStream_t s);
 int launch_naive(const st_plan* p, const void* src, void* dst, const float* kappa, hipStream_t s);
+// columns per lane when the marching kernels run a pass of the tiled variant, else 0 (sweep.hip)
+int tiled_march_columns(const st_plan* p, int levels);
 bool tile_supported(int shape, int radius, int tx, int ty);
 int supported_tiles(int* xy, int cap);
 int max_tb(const st_plan* p, int tx, int ty);

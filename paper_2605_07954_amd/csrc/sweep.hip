@@ -1,17 +1,14 @@
 // Jacobi sweep kernels for constant-weight star and box stencils (paper Sec. II-C update,
 // Sec. IV-A fixed halo, Sec. IV-E centre-first accumulation).
 //
-// Two kernels:
-//   sweep_naive  one step per launch, one thread per cell, neighbours read straight from
-//                global memory with a bounds test.  The plain GPU reference path.
-//   sweep_tiled  tb steps per launch (temporal blocking).  A 256-thread workgroup owns a
-//                TX x TY output tile; it loads the tile plus an r*tb halo into LDS with
-//                16-byte loads (cells outside the grid get the halo value b), then runs tb
-//                levels in LDS (ping-pong), each level shrinking the valid region by r,
-//                and stores only the tile.  Each thread computes a 4-column x RS-row block
-//                from a register ring of input rows (three 16-byte LDS reads per row), so
-//                every tap is a register operand of one FMA.
-// Both use the same per-cell FP32 order (centre product, then one FMA per footprint tap in
+// Kernels:
+//   sweep_naive   one step per launch, one thread per cell, neighbours read straight from
+//                 global memory with a bounds test.  The plain GPU reference path.
+//   sweep_block   tb steps per launch (temporal blocking) on register tiles, see block_body.h and
+//                 sweep_block.h.
+//   sweep_stream  tb steps per launch on LDS tiles, persistent workgroups, the next tile copied into
+//                 LDS by DMA while the current one computes.
+// All use the same per-cell FP32 order (centre product, then one FMA per footprint tap in
 // row-major order), so their results are bitwise identical for every tb and tile.
 #include <algorithm>
 #include <map>
@@ -19,6 +16,7 @@
 
 #include "internal.h"
 #include "storage.h"
+#include "sweep_block.h"
 #include "sweep_body.h"
 
 namespace st {
@@ -52,17 +50,6 @@ __global__ __launch_bounds__(256) void sweep_naive(SweepArgs a) {
             }
         static_cast<T*>(a.dst)[idx] = F::st(acc);
     }
-}
-
-// ---------------------------------------------------------------------------
-// tiled temporal-blocking kernel (body in sweep_body.h, shared with the batched kernel)
-// ---------------------------------------------------------------------------
-template <int S, int R, int SHAPE, int TX, int TY, int RS>
-__global__ __launch_bounds__(NT) void sweep_tiled(SweepArgs a) {
-    extern __shared__ float4 lds4[];
-    const int64_t t = xcd_tile(blockIdx.x, a.tiles_x * a.tiles_y);
-    tile_body<S, R, SHAPE, TX, TY, RS>(a.src, a.dst, a.rows, a.cols, a.b, a.tb, (t / a.tiles_x) * TY,
-                                       (t % a.tiles_x) * TX, a.w, reinterpret_cast<float*>(lds4));
 }
 
 // ---------------------------------------------------------------------------
@@ -248,40 +235,67 @@ struct TileDef {
 };
 constexpr TileDef kTiles[] = {{64, 64}, {128, 32}, {128, 64}, {256, 32}};
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-constexpr int kRS = 8;
 
 using KernelFn = void (*)(SweepArgs);
 
 template <int S, int R, int SH>
-KernelFn tiled_fn(int tile) {
-    switch (tile) {
-        case 0: return sweep_tiled<S, R, SH, 64, 64, kRS>;
-        case 1: return sweep_tiled<S, R, SH, 128, 32, kRS>;
-        case 2: return sweep_tiled<S, R, SH, 128, 64, kRS>;
-        case 3: return sweep_tiled<S, R, SH, 256, 32, kRS>;
+BlockFn block_fn(int def) {
+    switch (def) {
+        case 0: return sweep_block<S, R, SH, 1, 8, 8>;
+        case 1: return sweep_block<S, R, SH, 2, 4, 8>;
+        case 2: return sweep_block<S, R, SH, 2, 8, 8>;
+        case 3: return sweep_block<S, R, SH, 4, 4, 8>;
+        case 4: return sweep_block<S, R, SH, 2, 8, 16>;
     }
     return nullptr;
 }
 
 template <int S, int SH>
-KernelFn tiled_fn_r(int r, int tile) {
+BlockFn block_fn_r(int r, int def) {
     switch (r) {
-        case 1: return tiled_fn<S, 1, SH>(tile);
-        case 2: return tiled_fn<S, 2, SH>(tile);
-        case 3: return tiled_fn<S, 3, SH>(tile);
-        case 4: return tiled_fn<S, 4, SH>(tile);
+        case 1: return block_fn<S, 1, SH>(def);
+        case 2: return block_fn<S, 2, SH>(def);
+        case 3: return block_fn<S, 3, SH>(def);
+        case 4: return block_fn<S, 4, SH>(def);
     }
     return nullptr;
 }
 
-KernelFn tiled_lookup(int storage, int shape, int r, int tile) {
+BlockFn block_lookup(int storage, int shape, int r, int def) {
     if (storage == ST_F32)
-        return shape == SHAPE_BOX ? tiled_fn_r<ST_F32, SHAPE_BOX>(r, tile) : tiled_fn_r<ST_F32, SHAPE_STAR>(r, tile);
+        return shape == SHAPE_BOX ? block_fn_r<ST_F32, SHAPE_BOX>(r, def) : block_fn_r<ST_F32, SHAPE_STAR>(r, def);
     if (storage == ST_BF16)
-        return shape == SHAPE_BOX ? tiled_fn_r<ST_BF16, SHAPE_BOX>(r, tile) : tiled_fn_r<ST_BF16, SHAPE_STAR>(r, tile);
+        return shape == SHAPE_BOX ? block_fn_r<ST_BF16, SHAPE_BOX>(r, def) : block_fn_r<ST_BF16, SHAPE_STAR>(r, def);
     if (storage == ST_F16)
-        return shape == SHAPE_BOX ? tiled_fn_r<ST_F16, SHAPE_BOX>(r, tile) : tiled_fn_r<ST_F16, SHAPE_STAR>(r, tile);
+        return shape == SHAPE_BOX ? block_fn_r<ST_F16, SHAPE_BOX>(r, def) : block_fn_r<ST_F16, SHAPE_STAR>(r, def);
     return nullptr;
+}
+
+// A pass on register tiles.
+int launch_block(const st_plan* p, const void* src, void* dst, int levels, hipStream_t s) {
+    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
+    if (c.tiles >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
+    const block::Def& d = block::kDefs[c.def];
+    BlockFn fn = block_lookup(p->storage, p->shape, p->radius, c.def);
+    if (!fn) return fail(ST_EUNSUPPORTED, "no tiled kernel for this storage/shape/radius/tile");
+    const size_t lds = block::lds_floats(p->radius, d.v, d.rw, d.nw) * sizeof(float);
+    if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
+    BlockArgs a;
+    a.src = src;
+    a.dst = dst;
+    a.rows = p->rows;
+    a.cols = p->cols;
+    a.tiles_x = c.tiles_x;
+    a.tiles = c.tiles;
+    a.stop = p->stop;
+    a.b = p->bq;
+    a.tb = levels;
+    std::memcpy(a.w, p->w, sizeof(a.w));
+    clear_stale_error();
+    hipLaunchKernelGGL(fn, dim3(unsigned(a.tiles)), dim3(64 * d.nw), lds, s, a);
+    ST_LAUNCH_CHECK("sweep_block");
+    return ST_OK;
 }
 
 template <int S, int SH>
@@ -326,12 +340,6 @@ KernelFn naive_lookup(int storage, int shape, int r) {
     return nullptr;
 }
 
-int tile_index(int tx, int ty) {
-    for (int i = 0; i < kNumTiles; ++i)
-        if (kTiles[i].tx == tx && kTiles[i].ty == ty) return i;
-    return -1;
-}
-
 void fill_args(const st_plan* p, const void* src, void* dst, const float* kappa, SweepArgs& a) {
     a.src = src;
     a.dst = dst;
@@ -343,6 +351,12 @@ void fill_args(const st_plan* p, const void* src, void* dst, const float* kappa,
 }
 
 }  // namespace
+
+int tile_index(int tx, int ty) {
+    for (int i = 0; i < kNumTiles; ++i)
+        if (kTiles[i].tx == tx && kTiles[i].ty == ty) return i;
+    return -1;
+}
 
 bool tile_supported(int shape, int radius, int tx, int ty) {
     (void)shape;
@@ -390,6 +404,21 @@ int launch_naive(const st_plan* p, const void* src, void* dst, const float* kapp
     return ST_OK;
 }
 
+// Passes of the tiled variant that the row-marching kernels run faster (columns per lane; 0: register
+// tiles).  Marching recomputes a few rows per segment instead of a margin around every tile, but needs a
+// grid that gives each wavefront the device holds a segment much longer than its warm-up.  Measured side
+// after side (GStencil/s, register tiles / marching): star r = 2 at tb 6, 2048^2 1000 / 1071, 3000^2
+// 1450 / 1573, 4096^2 1588 / 2201; box r = 1 at tb 6, 2000 x 3000 1550 / 1310, 4096^2 1802 / 2155.  Boxes
+// of r >= 3 hold few rows in flight either way, and one-column marching wins from 1.5 10^6 cells on (box
+// r = 3 at tb 2, 1000^2 168 / 153, 1448^2 218 / 251, 4096^2 424 / 491; at 16384^2 eight columns reach 720).
+int tiled_march_columns(const st_plan* p, int levels) {
+    if (p->kind != KIND_CONST || p->bc != ST_BC_CONST) return 0;
+    const int64_t cells = p->rows * p->cols;
+    const bool big_box = p->shape == SHAPE_BOX && p->radius >= 3;
+    const int vmax = cells < (big_box ? int64_t(1500000) : int64_t(8000000)) ? 0 : !big_box ? 4 : cells < (int64_t(1) << 25) ? 1 : 8;
+    return vmax && levels <= march_max_tb(p->shape, p->radius, vmax) ? vmax : 0;
+}
+
 int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa, int levels, hipStream_t s) {
     if (p->flags & ST_FLAG_NAIVE) {
         // the reference path: one launch per step through the workspace is handled by the caller
@@ -419,20 +448,9 @@ int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa
         ST_LAUNCH_CHECK("sweep_stream");
         return ST_OK;
     }
-    KernelFn fn = tiled_lookup(p->storage, p->shape, p->radius, ti);
-    if (!fn) return fail(ST_EUNSUPPORTED, "no tiled kernel for this storage/shape/radius/tile");
-    const size_t lds = lds_bytes(p->radius, levels, p->tile_x, p->tile_y);
-    SweepArgs a;
-    fill_args(p, src, dst, kappa, a);
-    a.tb = levels;
-    a.tiles_x = (p->cols + p->tile_x - 1) / p->tile_x;
-    a.tiles_y = (p->rows + p->tile_y - 1) / p->tile_y;
-    if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
-    const int64_t blocks = a.tiles_x * a.tiles_y;
-    clear_stale_error();
-    hipLaunchKernelGGL(fn, dim3(unsigned(blocks)), dim3(NT), lds, s, a);
-    ST_LAUNCH_CHECK("sweep_tiled");
-    return ST_OK;
+    if (p->variant == VARIANT_TILED)
+        if (const int vmax = tiled_march_columns(p, levels)) return launch_march(p, src, dst, levels, vmax, s);
+    return launch_block(p, src, dst, levels, s);
 }
 
 }  // namespace st

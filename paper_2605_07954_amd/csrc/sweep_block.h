@@ -1,0 +1,178 @@
+// Constant-weight Jacobi pass on register tiles (block_body.h): the kernels of ST_VARIANT_TILED and of
+// plans that were never tuned.  Per cell the FP32 order of Sec. IV-E (centre product, then one FMA per
+// footprint tap in row-major order), cells outside the grid hold b at every level (Sec. IV-A), and
+// 16-bit fields are rounded after every level, so results are those of every other variant.
+#pragma once
+
+#include "block_body.h"
+
+namespace st {
+
+struct BlockArgs {
+    const void* src;
+    void* dst;
+    int64_t rows, cols;
+    int64_t tiles_x, tiles;
+    const int* stop;  // nullable: when it holds a nonzero value the pass does nothing
+    float b;
+    int tb;           // levels of this pass
+    float w[MAXK];
+};
+using BlockFn = void (*)(BlockArgs);
+
+namespace block {
+
+// One row of a lane's cells with R columns from the neighbouring lanes at either side.
+template <int R, int V>
+__device__ __forceinline__ void with_sides(const float (&x)[V], float (&e)[V + 2 * R]) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) e[R + c] = x[c];
+#pragma unroll
+    for (int c = -1; c >= -R; --c) e[R + c] = prev_lane(e[R + c + V]);
+#pragma unroll
+    for (int c = V; c < V + R; ++c) e[R + c] = next_lane(e[R + c - V]);
+}
+
+template <int S, int R, int SHAPE, int V, int RW, int NW>
+__device__ __forceinline__ void level(const float* w, const float* buf, int wave, int lane, float (&o)[RW][V]) {
+    constexpr int K = 2 * R + 1, N = RW + 2 * R;
+    constexpr bool BOX = SHAPE == SHAPE_BOX;
+    constexpr int E = BOX ? V + 2 * R : V, C0 = BOX ? R : 0;
+    float x[N][E];  // rows -R .. RW + R - 1 of this wavefront's frame; a box needs the sides of all of them
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        float q[V];
+        if (k < R || k >= R + RW) {
+            halo_row<R, V, RW, NW>(buf, wave, lane, k - R, q);
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c) q[c] = o[k - R][c];
+        }
+        if constexpr (BOX) {
+            with_sides<R, V>(q, x[k]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c) x[k][c] = q[c];
+        }
+    }
+    // the rows that need no halo row first: they hide the LDS reads
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        const int k = RW <= 2 * R ? i : i < RW - 2 * R ? i + R : i < RW - R ? i - (RW - 2 * R) : i;
+        float acc[V];
+#pragma unroll
+        for (int c = 0; c < V; ++c) acc[c] = w[R * K + R] * x[k + R][C0 + c];
+#pragma unroll
+        for (int dy = -R; dy <= R; ++dy) {
+            if constexpr (BOX) {
+#pragma unroll
+                for (int dx = -R; dx <= R; ++dx) {
+                    if (dy == 0 && dx == 0) continue;
+#pragma unroll
+                    for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(w[(dy + R) * K + dx + R], x[k + R + dy][R + c + dx], acc[c]);
+                }
+            } else if (dy != 0) {
+#pragma unroll
+                for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(w[(dy + R) * K + R], x[k + R + dy][c], acc[c]);
+            } else {
+                float q[V], e[V + 2 * R];
+#pragma unroll
+                for (int c = 0; c < V; ++c) q[c] = x[k + R][c];
+                with_sides<R, V>(q, e);
+#pragma unroll
+                for (int dx = -R; dx <= R; ++dx) {
+                    if (dx == 0) continue;
+#pragma unroll
+                    for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(w[R * K + dx + R], e[R + c + dx], acc[c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < V; ++c) o[k][c] = Fmt<S>::rnd(acc[c]);
+    }
+}
+
+// Every level of a pass over the tile at `at`; EDGE tiles check rows and columns.
+template <int S, int R, int SHAPE, int V, int RW, int NW, bool EDGE>
+__device__ __forceinline__ void tile_levels(const BlockArgs& a, const TileAt& at, float* lds) {
+    const int lane = int(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int64_t y0 = at.ty + wave * RW, x0 = at.tx + lane * V;
+    bool col_ok[V];
+#pragma unroll
+    for (int c = 0; c < V; ++c) col_ok[c] = !EDGE || (x0 + c >= 0 && x0 + c < a.cols);
+    const bool all_cols = !EDGE || (x0 >= 0 && x0 + V <= a.cols);
+    float o[RW][V];
+#pragma unroll
+    for (int k = 0; k < RW; ++k) {
+        const int64_t y = y0 + k;
+        if constexpr (!EDGE) {
+            load_cells<S, V>(a.src, y * a.cols + x0, o[k]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c) o[k][c] = a.b;
+            if (y >= 0 && y < a.rows) {
+                if (all_cols) {
+                    load_cells<S, V>(a.src, y * a.cols + x0, o[k]);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < V; ++c)
+                        if (col_ok[c]) {
+                            float one[1];
+                            load_cells<S, 1>(a.src, y * a.cols + x0 + c, one);
+                            o[k][c] = one[0];
+                        }
+                }
+            }
+        }
+    }
+    constexpr size_t HALF = lds_floats(R, V, RW, NW) / 2;
+    for (int l = 0; l < a.tb; ++l) {
+        float* buf = lds + (l & 1) * HALF;
+        if (has_rows<RW, NW>(wave, R * l)) publish<R, V, RW>(buf, wave, lane, o);
+        __syncthreads();
+        if (!has_rows<RW, NW>(wave, R * (l + 1))) continue;
+        level<S, R, SHAPE, V, RW, NW>(a.w, buf, wave, lane, o);
+        if constexpr (EDGE) {
+#pragma unroll
+            for (int k = 0; k < RW; ++k) {
+                const bool row_ok = y0 + k >= 0 && y0 + k < a.rows;
+#pragma unroll
+                for (int c = 0; c < V; ++c) o[k][c] = row_ok && col_ok[c] ? o[k][c] : a.b;
+            }
+        }
+    }
+    const int H = R * a.tb, HL = margin_cols(R, a.tb, V) / V;
+    if (lane < HL || lane >= 64 - HL) return;
+#pragma unroll
+    for (int k = 0; k < RW; ++k) {
+        const int row = wave * RW + k;
+        const int64_t y = y0 + k;
+        if (row < H || row >= NW * RW - H || (EDGE && y >= a.rows)) continue;
+        if (all_cols) {
+            store_cells<S, V>(a.dst, y * a.cols + x0, o[k]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c)
+                if (col_ok[c]) {
+                    const float one[1] = {o[k][c]};
+                    store_cells<S, 1>(a.dst, y * a.cols + x0 + c, one);
+                }
+        }
+    }
+}
+
+}  // namespace block
+
+template <int S, int R, int SHAPE, int V, int RW, int NW>
+__global__ __launch_bounds__(64 * NW) void sweep_block(BlockArgs a) {
+    extern __shared__ float4 lds4[];
+    if (a.stop && __hip_atomic_load(a.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    const block::TileAt at =
+        block::tile_at<R, V, RW, NW>(block::xcd_order(blockIdx.x, a.tiles), a.tiles_x, a.rows, a.cols, a.tb);
+    float* lds = reinterpret_cast<float*>(lds4);
+    if (at.edge) block::tile_levels<S, R, SHAPE, V, RW, NW, true>(a, at, lds);
+    else block::tile_levels<S, R, SHAPE, V, RW, NW, false>(a, at, lds);
+}
+
+}  // namespace st
