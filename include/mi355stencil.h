@@ -316,8 +316,8 @@ int stencil_autotune(st_plan* plan, const void* in, void* out, void* workspace, 
                      int64_t sample_steps, int* tb_out, int* tile_x_out, int* tile_y_out, void* stream);
 
 /* stencil_autotune_varcoef -- the same for a varcoef plan (the conservative heat step with the
- * diffusivity field `kappa`, device FP32 rows x cols, only read): times its LDS-tile kernel at
- * every tile of stencil_tiles() and tb in {1, 2, 3, 4, 6, 8} within the LDS budget and keeps the
+ * diffusivity field `kappa`, device FP32 rows x cols, only read): times its register-tile kernel at
+ * every tile of stencil_tiles() and tb in {1, 2, 3, 4, 6, 8, 12, 16} within the plan's budget and keeps the
  * fastest.  Errors: as stencil_run_varcoef; ST_EINVAL for a constant-weight plan. */
 int stencil_autotune_varcoef(st_plan* plan, const float* in, const float* kappa, float* out, void* workspace,
                              size_t ws_bytes, int64_t sample_steps, int* tb_out, int* tile_x_out, int* tile_y_out,

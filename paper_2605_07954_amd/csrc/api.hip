@@ -438,7 +438,7 @@ static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa
         if (p->kind == KIND_3D)
             rc = launch_3d(p, src, dst, s);
         else if (p->kind == KIND_VARCOEF)
-            rc = varcoef_launch(p, static_cast<const float*>(src), static_cast<float*>(dst), kappa, naive ? 0 : levels, s);
+            rc = varcoef_launch(p, static_cast<const float*>(src), static_cast<float*>(dst), kappa, naive ? 0 : levels, 1, s);
         else if (naive)
             rc = launch_naive(p, src, dst, kappa, s);
         else
@@ -573,7 +573,7 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
         } else {
             // register tiles also pay at 12 and 16 levels (small grids, where launches cost most)
             for (int tb : kTb)
-                if (tb <= 8 || (var == VARIANT_TILED && plan->kind == KIND_CONST)) cands[nc++] = tb;
+                if (tb <= 8 || var == VARIANT_TILED) cands[nc++] = tb;
         }
         for (int k = 0; k < nc && rc == ST_OK; ++k) {
             const int tb = cands[k];

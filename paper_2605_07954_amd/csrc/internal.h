@@ -108,7 +108,9 @@ int tiled_march_columns(const st_plan* p, int levels);
 bool tile_supported(int shape, int radius, int tx, int ty);
 int supported_tiles(int* xy, int cap);
 int max_tb(const st_plan* p, int tx, int ty);
-int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, hipStream_t s);
+// `fields` fields one after another in src, kappa and dst (levels 0: the naive path, one field)
+int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, int fields,
+                   hipStream_t s);
 size_t tiled_lds_bytes(int r, int tb, int tx, int ty);
 size_t varcoef_lds_bytes(int tb, int tile_x, int tile_y);
 

@@ -5,10 +5,10 @@
 // acc = fma(0.5f * (kappa(c) + kappa(nb)), u(nb) - u(c), acc) for nb = N, W, E, S.
 //
 // varcoef_naive: one step per launch, one thread per cell.
-// varcoef_tiled: tb steps per launch; u and kappa tiles with a tb-deep halo staged in LDS,
-//                4-column x RS-row register blocks per thread, as in the constant-weight sweep.
+// varcoef_block: tb steps per launch on register tiles (block_body.h).
 #include <algorithm>
 
+#include "block_body.h"
 #include "internal.h"
 
 namespace st {
@@ -44,126 +44,158 @@ __global__ __launch_bounds__(NT) void varcoef_naive(SweepArgs a) {
     }
 }
 
-struct VGeo {
-    int H, off, bw, bh;
+// Depths that a plan accepts per tile: the LDS of two field buffers and kappa with their margins.
+size_t vlds_bytes(int tb, int TX, int TY) {
+    const int off = ((tb + 4 + 3) / 4) * 4;
+    const int bw = ((off + TX + tb + 8 + 3) / 4) * 4, bh = TY + 2 * tb;
+    return size_t(3) * size_t(bw) * size_t(bh) * sizeof(float);
+}
+
+struct VArgs {
+    const float* src;
+    const float* kappa;
+    float* dst;
+    int64_t rows, cols;
+    int64_t tiles_x, tiles;  // of one field
+    int fields;              // fields one after another in src, kappa and dst
+    float b;
+    int tb;
 };
 
-__host__ __device__ inline VGeo vgeometry(int tb, int TX, int TY) {
-    VGeo g;
-    g.H = tb;
-    g.off = ((g.H + 4 + 3) / 4) * 4;
-    g.bw = ((g.off + TX + g.H + 8 + 3) / 4) * 4;
-    g.bh = TY + 2 * g.H;
-    return g;
-}
-
-__host__ __device__ inline size_t vlds_bytes(int tb, int TX, int TY) {
-    VGeo g = vgeometry(tb, TX, TY);
-    return size_t(3) * size_t(g.bw) * size_t(g.bh) * sizeof(float);
-}
-
-template <int TX, int TY, int RS>
-__global__ __launch_bounds__(NT) void varcoef_tiled(SweepArgs a) {
-    extern __shared__ float4 lds4[];
-    float* lds = reinterpret_cast<float*>(lds4);
-    const int tb = a.tb;
-    const VGeo g = vgeometry(tb, TX, TY);
-    const int H = g.H, OFF = g.off, BW = g.bw, BH = g.bh;
-    float* buf0 = lds;
-    float* buf1 = lds + BH * BW;
-    float* kap = lds + 2 * BH * BW;
-    const int64_t tx = blockIdx.x % a.tiles_x, ty = blockIdx.x / a.tiles_x;
-    const int64_t y0 = ty * TY, x0 = tx * TX;
-    const int64_t rows = a.rows, cols = a.cols;
-    const float* src = static_cast<const float*>(a.src);
-    float* dst = static_cast<float*>(a.dst);
-    const float* kg = a.kappa;
-    const float b = a.b;
-
-    // stage u (out of grid: b) and kappa (out of grid: 0, never read for a live cell)
-    const int c_lo = OFF - H, c_hi = OFF + TX + H;
-    const int wdt = c_hi - c_lo;
-    for (int k = threadIdx.x; k < BH * wdt; k += NT) {
-        const int br = k / wdt, bc = c_lo + (k - br * wdt);
-        const int64_t gy = y0 - H + br, gx = x0 - OFF + bc;
-        const bool in = gy >= 0 && gy < rows && gx >= 0 && gx < cols;
-        buf0[br * BW + bc] = in ? src[gy * cols + gx] : b;
-        kap[br * BW + bc] = in ? kg[gy * cols + gx] : 0.0f;
-    }
-    __syncthreads();
-
-    for (int l = 1; l <= tb; ++l) {
-        const int E = tb - l;
-        const float* sb = (l & 1) ? buf0 : buf1;
-        float* db = (l & 1) ? buf1 : buf0;
-        const bool last = (l == tb);
-        const int g0 = (OFF - E) & ~3;
-        const int g1 = (OFF + TX + E + 3) & ~3;
-        const int ngx = (g1 - g0) >> 2;
-        const int HL = TY + 2 * E;
-        const int nseg = (HL + RS - 1) / RS;
-        for (int it = threadIdx.x; it < ngx * nseg; it += NT) {
-            const int seg = it / ngx;
-            const int bc = g0 + 4 * (it - seg * ngx);
-            const int r0 = H - E + seg * RS;
-            const int nr = min(RS, HL - seg * RS);
-            const int64_t gx0 = x0 - OFF + bc;
-            bool col_in[6];  // columns bc-1 .. bc+4 inside the grid
+// A pass on register tiles (block_body.h).  The diffusivity enters once per pass as face values,
+// 0.5f (kappa(c) + kappa(nb)), which two cells share: V north faces per row (one row more than the
+// wavefront's) and V + 1 west faces, so that a level is four subtractions and four FMAs per cell.
+// Rows and columns of kappa clamp at the grid's edge, which is the rule kappa(nb) := kappa(c).
+// Bound by the vector ALU: at 1024^2 x 16 steps the LDS-tile kernel this replaced took 80 us.
+template <int V, int RW, int NW, bool EDGE>
+__device__ __forceinline__ void vc_levels(const VArgs& a, const block::TileAt& at, int64_t field, float* lds) {
+    using namespace block;
+    const int lane = int(threadIdx.x & 63);
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int64_t y0 = at.ty + wave * RW, x0 = at.tx + lane * V;
+    const float* src = a.src + field;
+    const float* kap = a.kappa + field;
+    float* dst = a.dst + field;
+    bool col_ok[V];
 #pragma unroll
-            for (int c = 0; c < 6; ++c) col_in[c] = (gx0 - 1 + c) >= 0 && (gx0 - 1 + c) < cols;
-            float uv[RS + 2][6], kv[RS + 2][6];
+    for (int c = 0; c < V; ++c) col_ok[c] = !EDGE || (x0 + c >= 0 && x0 + c < a.cols);
+    const bool all_cols = !EDGE || (x0 >= 0 && x0 + V <= a.cols);
+    auto load_row = [&](const float* f, int64_t y, float (&q)[V]) {  // y inside the grid; columns clamped
+        if (all_cols) {
+            load_cells<ST_F32, V>(f, y * a.cols + x0, q);
+        } else {
 #pragma unroll
-            for (int j = 0; j < RS + 2; ++j) {
-                const int br = min(r0 - 1 + j, BH - 1);
-                const float* pu = sb + br * BW + bc;
-                const float* pk = kap + br * BW + bc;
-                const float4 u1 = *reinterpret_cast<const float4*>(pu);
-                const float4 k1 = *reinterpret_cast<const float4*>(pk);
-                uv[j][0] = pu[-1]; uv[j][1] = u1.x; uv[j][2] = u1.y; uv[j][3] = u1.z; uv[j][4] = u1.w; uv[j][5] = pu[4];
-                kv[j][0] = pk[-1]; kv[j][1] = k1.x; kv[j][2] = k1.y; kv[j][3] = k1.z; kv[j][4] = k1.w; kv[j][5] = pk[4];
-                if (j < 2) continue;
-                const int kr = j - 2;
-                if (kr >= nr) continue;
-                const int brow = r0 + kr;
-                const int64_t gy = y0 - H + brow;
-                const bool row_in = gy >= 0 && gy < rows;
-                const bool n_in = gy - 1 >= 0, s_in = gy + 1 < rows;
-                float o[4];
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float uc = uv[kr + 1][c + 1], kc = kv[kr + 1][c + 1];
-                    const float kn = n_in ? kv[kr][c + 1] : kc;
-                    const float ks = s_in ? kv[kr + 2][c + 1] : kc;
-                    const float kw = col_in[c] ? kv[kr + 1][c] : kc;
-                    const float ke = col_in[c + 2] ? kv[kr + 1][c + 2] : kc;
-                    const float v = vc_update(uc, kc, uv[kr][c + 1], kn, uv[kr + 1][c], kw, uv[kr + 1][c + 2], ke,
-                                              uv[kr + 2][c + 1], ks);
-                    o[c] = (row_in && col_in[c + 1]) ? v : b;
-                }
-                if (last) {
-                    if (!row_in) continue;
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (col_in[c + 1]) dst[gy * cols + gx0 + c] = o[c];
-                } else {
-                    *reinterpret_cast<float4*>(db + brow * BW + bc) = make_float4(o[0], o[1], o[2], o[3]);
-                }
+            for (int c = 0; c < V; ++c) {
+                const int64_t x = x0 + c < 0 ? 0 : x0 + c >= a.cols ? a.cols - 1 : x0 + c;
+                float one[1];
+                load_cells<ST_F32, 1>(f, y * a.cols + x, one);
+                q[c] = one[0];
             }
         }
+    };
+    auto clamp_row = [&](int64_t y) { return y < 0 ? int64_t(0) : y >= a.rows ? a.rows - 1 : y; };
+    float o[RW][V], fn[RW + 1][V], fw[RW][V + 1];
+    {
+        float k[RW + 2][V];
+#pragma unroll
+        for (int r = 0; r < RW + 2; ++r) load_row(kap, clamp_row(y0 - 1 + r), k[r]);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) load_row(src, clamp_row(y0 + r), o[r]);
+#pragma unroll
+        for (int r = 0; r <= RW; ++r)
+#pragma unroll
+            for (int c = 0; c < V; ++c) fn[r][c] = 0.5f * (k[r + 1][c] + k[r][c]);
+#pragma unroll
+        for (int r = 0; r < RW; ++r) {
+            const float kw = prev_lane(k[r + 1][V - 1]), ke = next_lane(k[r + 1][0]);
+#pragma unroll
+            for (int c = 0; c <= V; ++c)
+                fw[r][c] = 0.5f * ((c < V ? k[r + 1][c < V ? c : 0] : ke) + (c > 0 ? k[r + 1][c > 0 ? c - 1 : 0] : kw));
+        }
+    }
+    auto outside = [&]() {  // cells outside the grid hold b
+        if constexpr (EDGE) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                const bool row_ok = y0 + r >= 0 && y0 + r < a.rows;
+#pragma unroll
+                for (int c = 0; c < V; ++c) o[r][c] = row_ok && col_ok[c] ? o[r][c] : a.b;
+            }
+        }
+    };
+    outside();
+    constexpr size_t HALF = lds_floats(1, V, RW, NW) / 2;
+    for (int l = 0; l < a.tb; ++l) {
+        float* buf = lds + (l & 1) * HALF;
+        if (has_rows<RW, NW>(wave, l)) publish<1, V, RW>(buf, wave, lane, o);
         __syncthreads();
+        if (!has_rows<RW, NW>(wave, l + 1)) continue;
+        float x[RW + 2][V];
+        halo_row<1, V, RW, NW>(buf, wave, lane, -1, x[0]);
+        halo_row<1, V, RW, NW>(buf, wave, lane, RW, x[RW + 1]);
+#pragma unroll
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int c = 0; c < V; ++c) x[r + 1][c] = o[r][c];
+        // the rows that need no halo row first: they hide the LDS reads
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int r = i < RW - 2 ? i + 1 : i == RW - 2 ? 0 : RW - 1;
+            const float(&u)[V] = x[r + 1];
+            const float w = prev_lane(u[V - 1]), e = next_lane(u[0]);
+#pragma unroll
+            for (int c = 0; c < V; ++c) {
+                float acc = u[c];
+                acc = __builtin_fmaf(fn[r][c], x[r][c] - u[c], acc);
+                acc = __builtin_fmaf(fw[r][c], (c > 0 ? u[c > 0 ? c - 1 : 0] : w) - u[c], acc);
+                acc = __builtin_fmaf(fw[r][c + 1], (c + 1 < V ? u[c + 1 < V ? c + 1 : 0] : e) - u[c], acc);
+                acc = __builtin_fmaf(fn[r + 1][c], x[r + 2][c] - u[c], acc);
+                o[r][c] = acc;
+            }
+        }
+        outside();
+    }
+    const int HL = margin_cols(1, a.tb, V) / V;
+    if (lane < HL || lane >= 64 - HL) return;
+#pragma unroll
+    for (int r = 0; r < RW; ++r) {
+        const int row = wave * RW + r;
+        const int64_t y = y0 + r;
+        if (row < a.tb || row >= NW * RW - a.tb || (EDGE && y >= a.rows)) continue;
+        if (all_cols) {
+            store_cells<ST_F32, V>(dst, y * a.cols + x0, o[r]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < V; ++c)
+                if (col_ok[c]) {
+                    const float one[1] = {o[r][c]};
+                    store_cells<ST_F32, 1>(dst, y * a.cols + x0 + c, one);
+                }
+        }
     }
 }
 
-constexpr int VRS = 8;
+template <int V, int RW, int NW>
+__global__ __launch_bounds__(64 * NW) void varcoef_block(VArgs a) {
+    extern __shared__ float4 lds4[];
+    float* lds = reinterpret_cast<float*>(lds4);
+    const int64_t t = block::xcd_order(blockIdx.x, a.tiles * a.fields), f = t / a.tiles;
+    const block::TileAt at = block::tile_at<1, V, RW, NW>(t - f * a.tiles, a.tiles_x, a.rows, a.cols, a.tb);
+    const int64_t field = f * a.rows * a.cols;
+    if (at.edge) vc_levels<V, RW, NW, true>(a, at, field, lds);
+    else vc_levels<V, RW, NW, false>(a, at, field, lds);
+}
 
-using VcFn = void (*)(SweepArgs);
+using VcFn = void (*)(VArgs);
 
-// The tiles of the constant-weight sweep's set: small ones give a small grid enough workgroups.
-VcFn varcoef_lookup(int tx, int ty) {
-    if (tx == 64 && ty == 64) return varcoef_tiled<64, 64, VRS>;
-    if (tx == 128 && ty == 32) return varcoef_tiled<128, 32, VRS>;
-    if (tx == 128 && ty == 64) return varcoef_tiled<128, 64, VRS>;
-    if (tx == 256 && ty == 32) return varcoef_tiled<256, 32, VRS>;
+VcFn varcoef_lookup(int def) {
+    switch (def) {
+        case 0: return varcoef_block<1, 8, 8>;
+        case 1: return varcoef_block<2, 4, 8>;
+        case 2: return varcoef_block<2, 8, 8>;
+        case 3: return varcoef_block<4, 4, 8>;
+        case 4: return varcoef_block<2, 8, 16>;
+    }
     return nullptr;
 }
 
@@ -171,15 +203,16 @@ VcFn varcoef_lookup(int tx, int ty) {
 
 size_t varcoef_lds_bytes(int tb, int tx, int ty) { return vlds_bytes(tb, tx, ty); }
 
-int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, hipStream_t s) {
-    SweepArgs a;
-    a.src = src;
-    a.dst = dst;
-    a.kappa = kappa;
-    a.rows = p->rows;
-    a.cols = p->cols;
-    a.b = p->bq;
+int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, int fields,
+                   hipStream_t s) {
     if (levels <= 0) {  // naive reference path
+        SweepArgs a;
+        a.src = src;
+        a.dst = dst;
+        a.kappa = kappa;
+        a.rows = p->rows;
+        a.cols = p->cols;
+        a.b = p->bq;
         a.tb = 1;
         const int64_t n = p->rows * p->cols;
         clear_stale_error();
@@ -188,17 +221,17 @@ int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* 
         ST_LAUNCH_CHECK("varcoef_naive");
         return ST_OK;
     }
-    const int tx = p->tile_x, ty = p->tile_y;
-    VcFn fn = varcoef_lookup(tx, ty);
-    if (!fn) return fail(ST_EUNSUPPORTED, "no varcoef kernel for this tile");
-    const size_t lds = vlds_bytes(levels, tx, ty);
-    a.tb = levels;
-    a.tiles_x = (p->cols + tx - 1) / tx;
-    a.tiles_y = (p->rows + ty - 1) / ty;
+    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), 1, levels, p->rows, p->cols);
+    if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
+    if (c.tiles * fields >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
+    const block::Def& d = block::kDefs[c.def];
+    VcFn fn = varcoef_lookup(c.def);
+    const size_t lds = block::lds_floats(1, d.v, d.rw, d.nw) * sizeof(float);
     if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
+    const VArgs a{src, kappa, dst, p->rows, p->cols, c.tiles_x, c.tiles, fields, p->bq, levels};
     clear_stale_error();
-    hipLaunchKernelGGL(fn, dim3(unsigned(a.tiles_x * a.tiles_y)), dim3(NT), lds, s, a);
-    ST_LAUNCH_CHECK("varcoef_tiled");
+    hipLaunchKernelGGL(fn, dim3(unsigned(c.tiles * fields)), dim3(64 * d.nw), lds, s, a);
+    ST_LAUNCH_CHECK("varcoef_block");
     return ST_OK;
 }
 

@@ -1,4 +1,4 @@
-"""GPU parity of the register-tile kernels: constant-weight passes on
+"""GPU parity of the register-tile kernels: constant-weight passes and variable-coefficient steps on
 grids whose sides sit at the edges of the tiles, bit for bit against the FP32 oracle.
 
 Both sides run the same FP32 operations in the same order, so the tolerance is zero (up to the sign of
@@ -55,6 +55,31 @@ def test_register_tiles_bitwise(g, tile, shape, r, tb):
         ref = (oracle.stencil_f32(u0, W, b, steps) if storage == "f32"
                else oracle.stencil_lowp(oracle.to_bits(u0, storage), W, b, steps, storage))
         np.testing.assert_array_equal(got, ref, err_msg=f"{rows}x{cols} {storage} b {b} steps {steps}")
+
+
+@pytest.mark.parametrize("tile", sorted(TILES))
+@pytest.mark.parametrize("tb", [1, 4, 9, 16])
+def test_register_tiles_varcoef_bitwise(g, tile, tb):
+    import torch
+    import paper_2605_07954_amd as lib
+    for k, (rows, cols) in enumerate(zip(_sides(TILES[tile][1], tb), _sides(TILES[tile][0], tb)[::-1])):
+        rng = np.random.default_rng(k)
+        u0 = rng.random((rows, cols), dtype=np.float32)
+        kap = (0.05 + 0.15 * rng.random((rows, cols), dtype=np.float32)).astype(np.float32)
+        b, steps = (0.0, 0.5)[k % 2], tb + k
+        plan = lib.stencil_plan_varcoef(rows, cols, b, 0)
+        try:
+            try:
+                lib.stencil_set_blocking(plan, tb, *tile)
+            except lib.StencilError:
+                pytest.skip("depth beyond this tile's budget")
+            x, kd = g.to_dev(u0), g.to_dev(kap)
+            out, ws = torch.empty_like(x), torch.empty_like(x)
+            lib.stencil_run_varcoef(plan, x, kd, out, steps, ws)
+            got = g.to_host(out)
+        finally:
+            lib.stencil_destroy(plan)
+        np.testing.assert_array_equal(got, oracle.varcoef_f32(u0, kap, b, steps), err_msg=f"{rows}x{cols} steps {steps}")
 
 
 def test_tiled_plan_of_a_large_grid(g):
