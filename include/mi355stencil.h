@@ -51,7 +51,8 @@ extern "C" {
 
 /* ---- plan flags -------------------------------------------------------- */
 #define ST_FLAG_NAIVE  0x1u  /* one step per launch, no LDS tiling: the plain GPU reference path */
-#define ST_FLAG_GRAPH  0x2u  /* stencil_run replays its passes from a cached hipGraph            */
+#define ST_FLAG_GRAPH  0x2u  /* stencil_run replays its passes from a cached hipGraph (runs of more
+                                than 8 passes; shorter ones are faster enqueued directly)        */
 #define ST_FLAG_ALLOW_MFMA 0x4u /* stencil_autotune may pick ST_VARIANT_MFMA, whose results are
                                    within FP32 rounding of the canonical order, not bit for bit */
 

@@ -463,8 +463,12 @@ static int run_common(st_plan* plan, const void* in, void* out, const float* kap
             return fail(ST_EALIAS, "workspace overlaps in/out");
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // (the resident variant is one cooperative launch: it is not captured)
-    if (!(plan->flags & ST_FLAG_GRAPH) || steps == 0 || resident_run(plan))
+    // (the resident variant is one cooperative launch: it is not captured.)  A run of few passes is
+    // enqueued directly, too: a graph launch costs the host about 25 us and 1.2 us per pass, a kernel launch
+    // 2.8 us (one pass: 27 us a run as a graph, 10 us direct; seven: 31 and 28; thirteen: 40 and 51), and the
+    // kernels follow each other without a gap either way.
+    constexpr int64_t kDirectPasses = 8;
+    if (!(plan->flags & ST_FLAG_GRAPH) || n_passes(plan, steps) <= kDirectPasses || resident_run(plan))
         return enqueue_run(plan, in, out, kappa, steps, workspace, s);
 
     // graph path: capture the passes once per (in, kappa, out, workspace, steps, stream)
