@@ -13,6 +13,7 @@
 #pragma once
 
 #include "internal.h"
+#include "star_rows.h"
 #include "storage.h"
 
 namespace st {
@@ -70,6 +71,51 @@ __device__ __forceinline__ void halo_row(const float* buf, int wave, int lane, i
     const Pack<V> p = *reinterpret_cast<const Pack<V>*>(buf + ((w * PR + pub_slot(R, RW, k + up * RW)) * 64 + lane) * V);
 #pragma unroll
     for (int c = 0; c < V; ++c) x[c] = p.v[c];
+}
+
+// One row of a lane's cells with R columns from the neighbouring lanes at either side.
+template <int R, int V>
+__device__ __forceinline__ void with_sides(const float (&x)[V], float (&e)[V + 2 * R]) {
+#pragma unroll
+    for (int c = 0; c < V; ++c) e[R + c] = x[c];
+#pragma unroll
+    for (int c = -1; c >= -R; --c) e[R + c] = prev_lane(e[R + c + V]);
+#pragma unroll
+    for (int c = V; c < V + R; ++c) e[R + c] = next_lane(e[R + c - V]);
+}
+
+// A level's cells rounded to the storage type (16-bit types two at a time).
+template <int S, int V, int RW>
+__device__ __forceinline__ void round_rows(float (&o)[RW][V]) {
+    if constexpr (S != ST_F32) {
+        static_assert(RW * V % 2 == 0, "pairs");
+#pragma unroll
+        for (int i = 0; i < RW * V; i += 2) Fmt<S>::rnd2(o[i / V][i % V], o[(i + 1) / V][(i + 1) % V]);
+    }
+}
+
+// The side taps of a star on RW rows: o[k][c] += w[dx] x[k][c + dx], dx = -R .. -1, then 1 .. R.
+template <int R, int V, int RW>
+__device__ __forceinline__ void side_taps(float (&o)[RW][V], const float (*x)[V], const float* w) {
+    constexpr int N = V == 1 && RW >= 8 ? 8 : V == 4 ? 2 : 4;  // rows per block of StarRows
+    if constexpr (StarRows<R, V, N>::exists && RW % N == 0) {
+#pragma unroll
+        for (int k = 0; k < RW; k += N) StarRows<R, V, N>::apply(o + k, x + k, w);
+    } else {
+#pragma unroll
+        for (int k = 0; k < RW; ++k) {
+            float q[V], e[V + 2 * R];
+#pragma unroll
+            for (int c = 0; c < V; ++c) q[c] = x[k][c];
+            with_sides<R, V>(q, e);
+#pragma unroll
+            for (int d = -R; d <= R; ++d) {
+                if (d == 0) continue;
+#pragma unroll
+                for (int c = 0; c < V; ++c) o[k][c] = __builtin_fmaf(w[d < 0 ? d + R : d + R - 1], e[R + c + d], o[k][c]);
+            }
+        }
+    }
 }
 
 // Whether wavefront `wave` holds a row of [lo, NW RW - lo).

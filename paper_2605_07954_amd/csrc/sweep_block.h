@@ -22,19 +22,9 @@ using BlockFn = void (*)(BlockArgs);
 
 namespace block {
 
-// One row of a lane's cells with R columns from the neighbouring lanes at either side.
-template <int R, int V>
-__device__ __forceinline__ void with_sides(const float (&x)[V], float (&e)[V + 2 * R]) {
-#pragma unroll
-    for (int c = 0; c < V; ++c) e[R + c] = x[c];
-#pragma unroll
-    for (int c = -1; c >= -R; --c) e[R + c] = prev_lane(e[R + c + V]);
-#pragma unroll
-    for (int c = V; c < V + R; ++c) e[R + c] = next_lane(e[R + c - V]);
-}
-
+// One level: `w` the dense weights, `wx` those of a star's side taps.
 template <int S, int R, int SHAPE, int V, int RW, int NW>
-__device__ __forceinline__ void level(const float* w, const float* buf, int wave, int lane, float (&o)[RW][V]) {
+__device__ __forceinline__ void level(const float* w, const float* wx, const float* buf, int wave, int lane, float (&o)[RW][V]) {
     constexpr int K = 2 * R + 1, N = RW + 2 * R;
     constexpr bool BOX = SHAPE == SHAPE_BOX;
     constexpr int E = BOX ? V + 2 * R : V, C0 = BOX ? R : 0;
@@ -55,41 +45,41 @@ __device__ __forceinline__ void level(const float* w, const float* buf, int wave
             for (int c = 0; c < V; ++c) x[k][c] = q[c];
         }
     }
-    // the rows that need no halo row first: they hide the LDS reads
+    if constexpr (BOX) {
+        // the rows that need no halo row first: they hide the LDS reads
 #pragma unroll
-    for (int i = 0; i < RW; ++i) {
-        const int k = RW <= 2 * R ? i : i < RW - 2 * R ? i + R : i < RW - R ? i - (RW - 2 * R) : i;
-        float acc[V];
+        for (int i = 0; i < RW; ++i) {
+            const int k = RW <= 2 * R ? i : i < RW - 2 * R ? i + R : i < RW - R ? i - (RW - 2 * R) : i;
 #pragma unroll
-        for (int c = 0; c < V; ++c) acc[c] = w[R * K + R] * x[k + R][C0 + c];
+            for (int c = 0; c < V; ++c) o[k][c] = w[R * K + R] * x[k + R][C0 + c];
 #pragma unroll
-        for (int dy = -R; dy <= R; ++dy) {
-            if constexpr (BOX) {
+            for (int dy = -R; dy <= R; ++dy)
 #pragma unroll
                 for (int dx = -R; dx <= R; ++dx) {
                     if (dy == 0 && dx == 0) continue;
 #pragma unroll
-                    for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(w[(dy + R) * K + dx + R], x[k + R + dy][R + c + dx], acc[c]);
+                    for (int c = 0; c < V; ++c) o[k][c] = __builtin_fmaf(w[(dy + R) * K + dx + R], x[k + R + dy][C0 + c + dx], o[k][c]);
                 }
-            } else if (dy != 0) {
-#pragma unroll
-                for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(w[(dy + R) * K + R], x[k + R + dy][c], acc[c]);
-            } else {
-                float q[V], e[V + 2 * R];
-#pragma unroll
-                for (int c = 0; c < V; ++c) q[c] = x[k + R][c];
-                with_sides<R, V>(q, e);
-#pragma unroll
-                for (int dx = -R; dx <= R; ++dx) {
-                    if (dx == 0) continue;
-#pragma unroll
-                    for (int c = 0; c < V; ++c) acc[c] = __builtin_fmaf(w[R * K + dx + R], e[R + c + dx], acc[c]);
-                }
-            }
         }
+    } else {
 #pragma unroll
-        for (int c = 0; c < V; ++c) o[k][c] = Fmt<S>::rnd(acc[c]);
+        for (int k = 0; k < RW; ++k) {
+#pragma unroll
+            for (int c = 0; c < V; ++c) o[k][c] = w[R * K + R] * x[k + R][c];
+#pragma unroll
+            for (int dy = -R; dy < 0; ++dy)
+#pragma unroll
+                for (int c = 0; c < V; ++c) o[k][c] = __builtin_fmaf(w[(dy + R) * K + R], x[k + R + dy][c], o[k][c]);
+        }
+        side_taps<R, V, RW>(o, x + R, wx);
+#pragma unroll
+        for (int k = 0; k < RW; ++k)
+#pragma unroll
+            for (int dy = 1; dy <= R; ++dy)
+#pragma unroll
+                for (int c = 0; c < V; ++c) o[k][c] = __builtin_fmaf(w[(dy + R) * K + R], x[k + R + dy][c], o[k][c]);
     }
+    round_rows<S, V, RW>(o);
 }
 
 // Every level of a pass over the tile at `at`; EDGE tiles check rows and columns.
@@ -126,13 +116,16 @@ __device__ __forceinline__ void tile_levels(const BlockArgs& a, const TileAt& at
             }
         }
     }
+    float wx[2 * R];  // a star's side taps, in registers for the DPP instructions
+#pragma unroll
+    for (int i = 0; i < 2 * R; ++i) wx[i] = a.w[R * (2 * R + 1) + (i < R ? i : i + 1)];
     constexpr size_t HALF = lds_floats(R, V, RW, NW) / 2;
     for (int l = 0; l < a.tb; ++l) {
         float* buf = lds + (l & 1) * HALF;
         if (has_rows<RW, NW>(wave, R * l)) publish<R, V, RW>(buf, wave, lane, o);
         __syncthreads();
         if (!has_rows<RW, NW>(wave, R * (l + 1))) continue;
-        level<S, R, SHAPE, V, RW, NW>(a.w, buf, wave, lane, o);
+        level<S, R, SHAPE, V, RW, NW>(a.w, wx, buf, wave, lane, o);
         if constexpr (EDGE) {
 #pragma unroll
             for (int k = 0; k < RW; ++k) {
