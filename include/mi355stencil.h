@@ -97,7 +97,7 @@ int stencil_plan(st_plan** out, int64_t rows, int64_t cols, int radius, const fl
  * centre product, then one FMA per footprint tap in row-major (dz, dy, dx) order (star footprint --
  * the taps on the three axes -- when every other weight is zero, else the full box).
  * 1 <= r <= ST_MAX_RADIUS_3D; storage ST_F32 / ST_BF16 / ST_F16 (FP32 arithmetic, rounded every
- * step); flags: ST_FLAG_GRAPH only.  A 3D plan runs one step per pass (stencil_run, stencil_run_noalloc,
+ * step); flags: ST_FLAG_GRAPH only.  A 3D plan picks its own depth per pass (stencil_run, stencil_run_noalloc,
  * stencil_workspace_bytes and stencil_norms take it; the blocking, variant, boundary, autotune and
  * batch calls refuse it with ST_EUNSUPPORTED, and its norms' next-step mass is NaN).  Errors: as
  * stencil_plan, and planes < 1. */

@@ -38,7 +38,7 @@ size_t lds_limit() {
     return cached;
 }
 
-int resident_blocks(const void* fn, size_t lds, int* blocks) {
+int resident_blocks_of(const void* fn, size_t lds, int threads, int* blocks) {
     static std::mutex mu;
     static std::map<std::pair<const void*, size_t>, int> cache;
     std::lock_guard<std::mutex> lk(mu);
@@ -47,12 +47,14 @@ int resident_blocks(const void* fn, size_t lds, int* blocks) {
         int dev = 0, cus = 0, occ = 0;
         ST_HIP_CHECK(hipGetDevice(&dev));
         ST_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-        ST_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 256, lds));
+        ST_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, lds));
         it = cache.emplace(std::make_pair(fn, lds), std::max(1, cus * std::max(occ, 1))).first;
     }
     *blocks = it->second;
     return ST_OK;
 }
+
+int resident_blocks(const void* fn, size_t lds, int* blocks) { return resident_blocks_of(fn, lds, 256, blocks); }
 
 int prepare_lds(const void* fn, size_t bytes) {
     if (bytes > lds_limit()) return fail(ST_EUNSUPPORTED, "kernel needs more LDS than a workgroup may have");
@@ -395,7 +397,7 @@ static bool resident_run(const st_plan* p) {
 
 static int64_t n_passes(const st_plan* p, int64_t steps) {
     if (steps <= 0) return 0;
-    const int64_t tb = (p->flags & ST_FLAG_NAIVE) ? 1 : p->tb;
+    const int64_t tb = p->kind == KIND_3D ? std::max(1, p->levels3) : (p->flags & ST_FLAG_NAIVE) ? 1 : p->tb;
     return (steps + tb - 1) / tb;
 }
 
@@ -408,7 +410,8 @@ int stencil_workspace_bytes(const st_plan* plan, int64_t steps, size_t* bytes) {
                             : 0;
         return ST_OK;
     }
-    *bytes = n_passes(plan, steps) >= 2 ? size_t(field_cells(plan)) * elem_size(plan->storage) : 0;
+    // (a 3D run of two or more steps always takes the field, also where one pass does them all)
+    *bytes = (plan->kind == KIND_3D ? steps : n_passes(plan, steps)) >= 2 ? size_t(field_cells(plan)) * elem_size(plan->storage) : 0;
     return ST_OK;
 }
 
@@ -427,16 +430,18 @@ static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa
         return ST_OK;
     }
     if (resident_run(p)) return launch_resident(p, in, out, ws, steps, s);
+    if (p->kind == KIND_3D) max_levels_3d(p);
     const bool naive = p->flags & ST_FLAG_NAIVE;
     const int64_t tb = naive ? 1 : p->tb;
     const int64_t P = n_passes(p, steps);
     const void* src = in;
     for (int64_t k = 0; k < P; ++k) {
         void* dst = ((P - 1 - k) % 2 == 0) ? out : ws;
-        const int levels = int(std::min<int64_t>(tb, steps - k * tb));
+        // 3D passes are equally deep, give or take a level; the others tb deep but the last
+        const int levels = int(p->kind == KIND_3D ? steps / P + (k < steps % P) : std::min<int64_t>(tb, steps - k * tb));
         int rc;
         if (p->kind == KIND_3D)
-            rc = launch_3d(p, src, dst, s);
+            rc = launch_3d(p, src, dst, levels, s);
         else if (p->kind == KIND_VARCOEF)
             rc = varcoef_launch(p, static_cast<const float*>(src), static_cast<float*>(dst), kappa, naive ? 0 : levels, 1, s);
         else if (naive)
@@ -463,6 +468,7 @@ static int run_common(st_plan* plan, const void* in, void* out, const float* kap
             return fail(ST_EALIAS, "workspace overlaps in/out");
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (plan->kind == KIND_3D) max_levels_3d(plan);  // (n_passes counts by it)
     // (the resident variant is one cooperative launch: it is not captured.)  A run of few passes is
     // enqueued directly, too: a graph launch costs the host about 25 us and 1.2 us per pass, a kernel launch
     // 2.8 us (one pass: 27 us a run as a graph, 10 us direct; seven: 31 and 28; thirteen: 40 and 51), and the

@@ -70,6 +70,7 @@ struct st_plan {
     int kind;         // st::Kind
     int64_t rows, cols;
     int64_t planes;   // 3D plans: planes along z (1 for 2D plans)
+    int levels3;      // 3D plans: levels per pass (0: not chosen yet)
     float w3[st::MAXK3];  // 3D plans: dense (2r+1)^3 weights
     int radius;
     int shape;        // st::Shape
@@ -121,6 +122,8 @@ size_t lds_limit();
 int prepare_lds(const void* fn, size_t bytes);
 // Workgroups of NT threads with `lds` bytes of dynamic LDS that fit the device at once.
 int resident_blocks(const void* fn, size_t lds, int* blocks);
+// The same for workgroups of `threads` threads.
+int resident_blocks_of(const void* fn, size_t lds, int threads, int* blocks);
 bool stream_usable(const st_plan* p);
 // FP64 norms (norms.hip) with an optional device stop flag (NULL: always run).
 int launch_norms(const st_plan* plan, const void* u_prev, const void* u, double* out4, void* workspace, size_t ws_bytes,
@@ -138,8 +141,9 @@ int read_resident_status(const st_plan* p, const void* ws, int* status4, hipStre
 // FMA order bit for bit (within FP32 rounding of it).
 bool mfma_usable(const st_plan* p);
 int launch_mfma(const st_plan* p, const void* src, void* dst, hipStream_t s);
-// 3D pass (stencil3d.hip): one step of a 3D plan.
-int launch_3d(const st_plan* p, const void* src, void* dst, hipStream_t s);
+// 3D pass (stencil3d.hip): up to max_levels_3d steps of a 3D plan.
+int max_levels_3d(st_plan* p);
+int launch_3d(const st_plan* p, const void* src, void* dst, int levels, hipStream_t s);
 // Row-marching pass (march.hip): constant-weight plans of any storage, width and alignment, up to
 // vmax (1, 4 or 8) columns per lane; up to march_max_tb(shape, radius, vmax) levels per pass (vmax 4:
 // star 8 / 6 / 4 / 3 for r = 1 / 2 / 3 / 4, box 6 / 3 / 2 / 2; vmax 8: star 8 / 4 / 3 / 2, box

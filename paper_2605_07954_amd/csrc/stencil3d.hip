@@ -4,18 +4,21 @@
 // per cell acc = W_c u_c, then one FMA per footprint tap in row-major (dz, dy, dx) order (star:
 // the taps on the three axes; box: all of them).
 //
-// One workgroup owns a TY x TX column of the grid and marches along z over a segment of planes:
+// Stars, and boxes of radius 1, run several levels per pass on register tiles (sweep3d_block.h).
+//
+// Boxes of radius 2 (125 taps: their weights alone fill the scalar registers) run one level per pass on
+// LDS tiles.  One workgroup owns a TY x TX column of the grid and marches along z over a segment of planes:
 // the 2r + 1 input planes of the current output plane sit in an LDS ring, each with its r-deep
 // (y, x) halo; every iteration stores a plane fetched earlier into the slot the oldest plane leaves,
 // starts fetching the plane after next into registers (two register sets, so two planes are in
 // flight), and computes its cells of the output plane from the ring meanwhile.  A wavefront covers one row of the
 // tile (64 consecutive columns), so loads and stores are coalesced and LDS reads of one tap hit 64
-// consecutive words.  One level per pass (no temporal blocking): HBM-bound for the 7-point star
-// (8 bytes and 13 FLOP per update), LDS-bound for large boxes.
+// consecutive words.  Bound by LDS: one read per tap and cell.
 #include <algorithm>
 
 #include "internal.h"
 #include "storage.h"
+#include "sweep3d_block.h"
 
 namespace st {
 
@@ -69,7 +72,7 @@ __device__ __forceinline__ void store_plane(float* slot, const PlaneRegs<R>& p) 
     }
 }
 
-template <int S, int R, int SHAPE>
+template <int S, int R>
 __global__ __launch_bounds__(NT3) void sweep3d(Args3 a) {
     constexpr int K = 2 * R + 1;
     using P = PlaneRegs<R>;
@@ -107,8 +110,7 @@ __global__ __launch_bounds__(NT3) void sweep3d(Args3 a) {
                 for (int dy = -R; dy <= R; ++dy)
 #pragma unroll
                     for (int dx = -R; dx <= R; ++dx) {
-                        const int nz = (dz != 0) + (dy != 0) + (dx != 0);
-                        if (nz == 0 || (SHAPE == SHAPE_STAR && nz > 1)) continue;
+                        if (dz == 0 && dy == 0 && dx == 0) continue;
                         acc = __builtin_fmaf(a.w[((dz + R) * K + dy + R) * K + dx + R], pl[o + dy * PW + dx], acc);
                     }
             }
@@ -131,27 +133,147 @@ __global__ __launch_bounds__(NT3) void sweep3d(Args3 a) {
     }
 }
 
+// The kernel of boxes of radius 2 by storage type.
 using Fn3 = void (*)(Args3);
-
-template <int S, int SH>
-Fn3 lookup3(int r) {
-    if (r == 1) return sweep3d<S, 1, SH>;
-    if (r == 2) return sweep3d<S, 2, SH>;
+Fn3 box2_lookup(int storage) {
+    if (storage == ST_F32) return sweep3d<ST_F32, 2>;
+    if (storage == ST_BF16) return sweep3d<ST_BF16, 2>;
+    if (storage == ST_F16) return sweep3d<ST_F16, 2>;
     return nullptr;
 }
 
-Fn3 lookup3(int storage, int shape, int r) {
-    const bool box = shape == SHAPE_BOX;
-    if (storage == ST_F32) return box ? lookup3<ST_F32, SHAPE_BOX>(r) : lookup3<ST_F32, SHAPE_STAR>(r);
-    if (storage == ST_BF16) return box ? lookup3<ST_BF16, SHAPE_BOX>(r) : lookup3<ST_BF16, SHAPE_STAR>(r);
-    if (storage == ST_F16) return box ? lookup3<ST_F16, SHAPE_BOX>(r) : lookup3<ST_F16, SHAPE_STAR>(r);
+// Stars and boxes of radius 1 on register tiles (sweep3d_block.h): one column per lane, four rows per
+// wavefront; sixteen wavefronts (64 x 64 tiles) for stars, eight (64 x 32) for boxes, whose levels hold six
+// rows of three planes (two levels at 512^3: 650 GStencil/s, sixteen wavefronts 587, eight rows 575).
+constexpr int BV = 1, BRW = 4, BNW_STAR = 16, BNW_BOX = 8;
+constexpr int MAX_LEVELS_STAR1 = 6, MAX_LEVELS_STAR2 = 2, MAX_LEVELS_BOX1 = 2;
+
+template <int S>
+const void* block3(int shape, int r, int levels) {
+#define ST_STAR3(R, T) \
+    if (shape == SHAPE_STAR && r == R && levels == T) return reinterpret_cast<const void*>(sweep3d_block<S, R, T, BV, BRW, BNW_STAR>);
+#define ST_BOX3(T) \
+    if (shape == SHAPE_BOX && r == 1 && levels == T) return reinterpret_cast<const void*>(sweep3d_block_box<S, 1, T, BV, BRW, BNW_BOX>);
+    ST_STAR3(1, 1) ST_STAR3(1, 2) ST_STAR3(1, 3) ST_STAR3(1, 4) ST_STAR3(1, 5) ST_STAR3(1, 6)
+    ST_STAR3(2, 1) ST_STAR3(2, 2)
+    ST_BOX3(1) ST_BOX3(2)
+#undef ST_STAR3
+#undef ST_BOX3
     return nullptr;
+}
+
+const void* block3(const st_plan* p, int levels) {
+    if (p->storage == ST_F32) return block3<ST_F32>(p->shape, p->radius, levels);
+    if (p->storage == ST_BF16) return block3<ST_BF16>(p->shape, p->radius, levels);
+    if (p->storage == ST_F16) return block3<ST_F16>(p->shape, p->radius, levels);
+    return nullptr;
+}
+
+bool on_tiles(const st_plan* p) { return p->shape == SHAPE_STAR || p->radius == 1; }
+
+// How a pass of `levels` levels covers the grid, and its cost in units of one level's arithmetic on one
+// plane of a tile (0.235 us): a workgroup takes zseg + 2 r levels iterations of 3 + levels units (loads,
+// exchange and barrier, then the levels), and the launch as many rounds of workgroups as the device needs
+// for all of them; its bytes at 4.4 TB/s (a third of what the field takes when it fits the 256 MB cache)
+// and a launch of about 15 units are the other bounds.  The model ranks depths as measured: 512^3 1, 2, 3, 4, 5, 6
+// levels 424, 900, 1216, 1468, 1590, 1646 GStencil/s; 100^3 x 20 steps 193, 124, 112, 106, 144 us for
+// 1 .. 5; 40 x 500 x 500 439, 249, 210, 191, 228 us.
+struct Cover3 {
+    int64_t tiles_x, tiles, zseg;
+    double cost;
+};
+int cover3(const st_plan* p, int levels, Cover3* c) {
+    const int r = p->radius, nw = p->shape == SHAPE_STAR ? BNW_STAR : BNW_BOX;
+    const void* fn = block3(p, levels);
+    if (!fn) return fail(ST_EUNSUPPORTED, "no 3D kernel for this storage/shape/radius");
+    const size_t lds = block::lds_floats(r, BV, BRW, nw) * levels * sizeof(float);
+    if (int rc = prepare_lds(fn, lds)) return rc;
+    int slots = 0;
+    if (int rc = resident_blocks_of(fn, lds, 64 * nw, &slots)) return rc;
+    const int out_rows = nw * BRW - 2 * r * levels, out_cols = 64 * BV - 2 * block::margin_cols(r, levels, BV);
+    c->tiles_x = (p->cols + out_cols - 1) / out_cols;
+    c->tiles = c->tiles_x * ((p->rows + out_rows - 1) / out_rows);
+    double best = 0.0;
+    for (int64_t segs = 1; segs <= std::min<int64_t>(p->planes, 64); ++segs) {
+        const int64_t zs = (p->planes + segs - 1) / segs, n = (p->planes + zs - 1) / zs;
+        const double cost = double((c->tiles * n + slots - 1) / slots) * double(zs + 2 * r * levels) * (3 + levels);
+        if (best == 0.0 || cost < best) {
+            best = cost;
+            c->zseg = zs;
+        }
+    }
+    const double bytes = 2.0 * double(field_cells(p)) * double(elem_size(p->storage));
+    c->cost = std::max(best, bytes / 4.4e6 / 0.235 * (bytes > 2e8 ? 1.0 : 1.0 / 3.0)) + 15.0;
+    return ST_OK;
+}
+
+int launch_tiles(const st_plan* p, const void* src, void* dst, int levels, hipStream_t s) {
+    Cover3 c;
+    if (int rc = cover3(p, levels, &c)) return rc;
+    const int64_t grid = c.tiles * ((p->planes + c.zseg - 1) / c.zseg);
+    if (grid > (int64_t(1) << 31) - 1) return fail(ST_EUNSUPPORTED, "3D grid too large for one launch");
+    const int r = p->radius, k = 2 * r + 1, nw = p->shape == SHAPE_STAR ? BNW_STAR : BNW_BOX;
+    const size_t lds = block::lds_floats(r, BV, BRW, nw) * levels * sizeof(float);
+    auto fill = [&](auto& a) {
+        a.src = src;
+        a.dst = dst;
+        a.planes = p->planes;
+        a.rows = p->rows;
+        a.cols = p->cols;
+        a.tiles_x = c.tiles_x;
+        a.tiles = c.tiles;
+        a.zseg = c.zseg;
+        a.b = p->bq;
+    };
+    clear_stale_error();
+    if (p->shape == SHAPE_STAR) {
+        Args3B a;
+        fill(a);
+        const float* w = p->w3 + (r * k + r) * k + r;  // the centre weight
+        a.wc = w[0];
+        for (int i = 0; i < 2 * r; ++i) {
+            const int d = i < r ? i - r : i - r + 1;
+            a.wz[i] = w[d * k * k];
+            a.wy[i] = w[d * k];
+            a.wx[i] = w[d];
+        }
+        hipLaunchKernelGGL(reinterpret_cast<void (*)(Args3B)>(const_cast<void*>(block3(p, levels))), dim3(unsigned(grid)),
+                           dim3(64 * nw), lds, s, a);
+    } else {
+        Args3X a;
+        fill(a);
+        std::memcpy(a.w, p->w3, sizeof(a.w));
+        hipLaunchKernelGGL(reinterpret_cast<void (*)(Args3X)>(const_cast<void*>(block3(p, levels))), dim3(unsigned(grid)),
+                           dim3(64 * nw), lds, s, a);
+    }
+    ST_LAUNCH_CHECK("sweep3d_block");
+    return ST_OK;
 }
 
 }  // namespace
 
-int launch_3d(const st_plan* p, const void* src, void* dst, hipStream_t s) {
-    Fn3 fn = lookup3(p->storage, p->shape, p->radius);
+// Levels per pass: the depth of the least cost per step.
+int max_levels_3d(st_plan* p) {
+    if (!on_tiles(p)) return 1;
+    if (p->levels3 == 0) {
+        const int most = p->shape == SHAPE_BOX ? MAX_LEVELS_BOX1 : p->radius == 1 ? MAX_LEVELS_STAR1 : MAX_LEVELS_STAR2;
+        double best = 0.0;
+        for (int t = 1; t <= most; ++t) {
+            Cover3 c;
+            if (cover3(p, t, &c) != ST_OK) break;
+            if (best == 0.0 || c.cost / t < best) {
+                best = c.cost / t;
+                p->levels3 = t;
+            }
+        }
+        if (p->levels3 == 0) return 1;
+    }
+    return p->levels3;
+}
+
+int launch_3d(const st_plan* p, const void* src, void* dst, int levels, hipStream_t s) {
+    if (on_tiles(p)) return launch_tiles(p, src, dst, levels, s);
+    Fn3 fn = box2_lookup(p->storage);
     if (!fn) return fail(ST_EUNSUPPORTED, "no 3D kernel for this storage/shape/radius");
     Args3 a;
     a.src = src;

@@ -100,3 +100,38 @@ def test_tiled_plan_of_a_large_grid(g):
     finally:
         lib.stencil_destroy(plan)
     np.testing.assert_array_equal(got, oracle.stencil_f32(u0, W, 0.25, steps))
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("shape,r", [("star", 1), ("star", 2), ("box", 1)])
+def test_3d_register_tiles_bitwise(g, shape, r, storage):
+    """3D passes of one to several levels on grids at the tiles' edges (64 x 64 or 64 x 32 cells less the
+    margins) and with few and many planes per segment."""
+    import torch
+    import paper_2605_07954_amd as lib
+    rng = np.random.default_rng(r)
+    k = 2 * r + 1
+    W = rng.random((k, k, k))
+    if shape == "star":
+        W = np.where((np.indices((k, k, k)) != r).sum(0) <= 1, W, 0.0)
+    W = (W / W.sum()).astype(np.float32)
+    grids = [(1, 52, 53, 7), (2, 64, 65, 1), (71, 57, 63, 6), (9, 61, 129, 4), (150, 8, 5, 13), (33, 105, 31, 3), (5, 1, 200, 12)]
+    for planes, rows, cols, steps in grids:
+        b = (0.0, -0.75)[steps % 2]
+        u0 = rng.random((planes, rows, cols), dtype=np.float32)
+        x = u0 if storage == "f32" else oracle.to_bits(u0, storage)
+        plan = lib.stencil_plan3d(planes, rows, cols, r, W, b, storage, 0)
+        try:
+            xd = g.to_dev(x)
+            out, ws = torch.empty_like(xd), torch.empty_like(xd)
+            lib.stencil_run(plan, xd, out, steps, ws)
+            got = g.to_host(out)
+        finally:
+            lib.stencil_destroy(plan)
+        if storage == "f32":
+            ref = oracle.stencil3d_f32(u0, W, b, steps)
+        else:
+            ref = x
+            for _ in range(steps):
+                ref = oracle.to_bits(oracle.stencil3d_f32(oracle.from_bits(ref, storage), W, b, 1), storage)
+        np.testing.assert_array_equal(got, ref, err_msg=f"{planes}x{rows}x{cols} steps {steps}")
