@@ -499,7 +499,7 @@ int surrogate_crop(const float* src, float* dst, const int* yx, int n, int64_t r
  * For optimiser step s = 0 .. cfg->steps-1 and trajectory b = 0 .. cfg->batch-1 (index
  * i = s*batch + b):
  *   1. (u0, kappa) of rows x cols from coefficient row coef[i] (as surrogate_synth_fields);
- *   2. the target u_K = K steps of the plain varcoef stencil from u0 (an internal varcoef plan);
+ *   2. the target u_K = K steps of the plain varcoef stencil from u0 (on the window the crop depends on);
  *   3. crop x crop windows of u0, kappa and u_K at crop_yx[2i], crop_yx[2i+1] (row, col);
  *   4. masked MSE loss and gradient on the crops (surrogate_loss_grad); the mask drops the 6 cells
  *      next to a crop edge that cuts the grid (the network's receptive field), keeps domain edges;

@@ -443,7 +443,7 @@ static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa
         if (p->kind == KIND_3D)
             rc = launch_3d(p, src, dst, levels, s);
         else if (p->kind == KIND_VARCOEF)
-            rc = varcoef_launch(p, static_cast<const float*>(src), static_cast<float*>(dst), kappa, naive ? 0 : levels, 1, s);
+            rc = varcoef_launch(p, static_cast<const float*>(src), static_cast<float*>(dst), kappa, naive ? 0 : levels, s);
         else if (naive)
             rc = launch_naive(p, src, dst, kappa, s);
         else

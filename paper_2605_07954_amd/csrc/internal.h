@@ -109,9 +109,24 @@ int tiled_march_columns(const st_plan* p, int levels);
 bool tile_supported(int shape, int radius, int tx, int ty);
 int supported_tiles(int* xy, int cap);
 int max_tb(const st_plan* p, int tx, int ty);
-// `fields` fields one after another in src, kappa and dst (levels 0: the naive path, one field)
-int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, int fields,
-                   hipStream_t s);
+int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, hipStream_t s);
+
+// Windows of fields stacked one after another, each rows x cols: around the window-to-be of `reach` cells
+// beyond the point yx[2f], yx[2f + 1] (device), moved into the field.
+struct VcWindows {
+    const int* yx;  // nullptr: whole fields
+    int64_t reach, rows, cols;
+};
+// First row (column) of a window of n cells that starts `reach` cells before y where the field allows it.
+__host__ __device__ inline int64_t window_origin(int y, int64_t reach, int64_t field, int64_t n) {
+    const int64_t o = int64_t(y) - reach;
+    return o < 0 ? 0 : o + n > field ? field - n : o;
+}
+// `steps` varcoef steps (halo 0) on the rows x cols windows of `fields` fields, each window as a grid of its
+// own: exact on the cells `steps` or more away from window edges that are no grid edges.  out, scratch:
+// fields * rows * cols floats each (scratch for more than one pass of eight steps).
+int varcoef_windows(const float* u0, const float* kappa, const VcWindows& w, int64_t rows, int64_t cols, int fields,
+                    int64_t steps, float* out, float* scratch, hipStream_t s);
 size_t tiled_lds_bytes(int r, int tb, int tx, int ty);
 size_t varcoef_lds_bytes(int tb, int tile_x, int tile_y);
 

@@ -860,6 +860,22 @@ __global__ void crop_kernel(const float* src, float* dst, const int* yx, int n, 
     dst[idx] = (y >= 0 && y < rows && x >= 0 && x < cols) ? src[(int64_t(t) * rows + y) * cols + x] : 0.0f;
 }
 
+// The three crops of a training step in one launch: u0 and kappa from their fields, u_K from the windows
+// that varcoef_windows computed.
+__global__ __launch_bounds__(256) void crop3_kernel(const float* u0, const float* kappa, const float* uk, VcWindows w, int n,
+                                                    int wrows, int wcols, int h, float* cu0, float* ck, float* cuk) {
+    const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (idx >= int64_t(n) * h * h) return;
+    const int t = int(idx / (int64_t(h) * h));
+    const int i = int((idx / h) % h), j = int(idx % h);
+    const int y = w.yx[2 * t], x = w.yx[2 * t + 1];
+    const int64_t q = (int64_t(t) * w.rows + y + i) * w.cols + x + j;
+    cu0[idx] = u0[q];
+    ck[idx] = kappa[q];
+    cuk[idx] = uk[(int64_t(t) * wrows + (y - window_origin(y, w.reach, w.rows, wrows)) + i) * wcols +
+                  (x - window_origin(x, w.reach, w.cols, wcols)) + j];
+}
+
 // FP64 sums of (a - b)^2 and b^2 (judge error), two-stage fixed order
 __global__ void diff_norms(const float* a, const float* b, int64_t n, double* partial) {
     __shared__ double r0[256], r1[256];
@@ -1480,28 +1496,37 @@ int surrogate_train(sg_model* m, float* params, float* optim, const float* coef,
     float* grad = reinterpret_cast<float*>(ws + T.grad);
     int* yx = reinterpret_cast<int*>(ws + T.yx);
     ST_HIP_CHECK(hipMemcpyAsync(yx, crop_yx, size_t(n) * 8, hipMemcpyHostToDevice, s));
-    // the judge: the plain stencil, as deep per pass as this device's LDS allows, on 128 x 32 tiles
-    // (the fastest tile of the set for 1024^2 fields at depth 8; the result does not depend on it)
-    st_plan* judge = nullptr;
-    if (int rc = stencil_plan_varcoef(&judge, c.rows, c.cols, 0.0, 0)) return rc;
-    for (int tb : {8, 4, 2, 1})
-        if (stencil_set_blocking(judge, tb, 128, 32) == ST_OK) break;
+    // The targets: K plain steps of each field, on the window that its crop depends on (the crop and K
+    // cells around it, inside the grid).  All windows of a step advance together when there is room for
+    // their ping-pong copy, in the gradient's workspace, which is free until the gradient is computed;
+    // else one by one, with the copy of one field.
+    const int64_t wr = std::min<int64_t>(c.rows, c.crop + 2 * c.K), wc = std::min<int64_t>(c.cols, c.crop + 2 * c.K);
+    const bool together = size_t(B * wr * wc) * 4 <= T.total - T.sg;
     int rc = ST_OK;
     const int64_t field = c.rows * c.cols;
     for (int64_t st = 0; st < c.steps && rc == ST_OK; ++st) {
         if ((rc = surrogate_synth_fields(coef + st * B * COEF_ROW, B, c.rows, c.cols, U0, KP, stream))) break;
-        for (int b = 0; b < B && rc == ST_OK; ++b)
-            rc = stencil_run_varcoef(judge, U0 + b * field, KP + b * field, UK + b * field, c.K, ws + T.jws,
-                                     T.jws_bytes, stream);
+        const int* yx_s = yx + 2 * st * B;
+        const VcWindows w{yx_s, c.K, c.rows, c.cols};
+        if (together) {
+            rc = varcoef_windows(U0, KP, w, wr, wc, B, c.K, UK, reinterpret_cast<float*>(ws + T.sg), s);
+        } else {
+            for (int b = 0; b < B && rc == ST_OK; ++b)
+                rc = varcoef_windows(U0 + b * field, KP + b * field, VcWindows{yx_s + 2 * b, c.K, c.rows, c.cols}, wr, wc, 1,
+                                     c.K, UK + b * wr * wc, reinterpret_cast<float*>(ws + T.jws), s);
+        }
         if (rc) break;
         // the network's scale constants come from the whole trajectory field, as at inference
         float* scale = reinterpret_cast<float*>(ws + T.scale);
         if ((rc = compute_scale(U0, B, int(c.rows), int(c.cols), reinterpret_cast<double*>(ws + T.scalep), scale, s)))
             break;
-        const int* yx_s = yx + 2 * st * B;
-        if ((rc = surrogate_crop(U0, cu0, yx_s, B, c.rows, c.cols, c.crop, c.crop, stream))) break;
-        if ((rc = surrogate_crop(KP, ckp, yx_s, B, c.rows, c.cols, c.crop, c.crop, stream))) break;
-        if ((rc = surrogate_crop(UK, cuk, yx_s, B, c.rows, c.cols, c.crop, c.crop, stream))) break;
+        clear_stale_error();
+        hipLaunchKernelGGL(crop3_kernel, dim3(unsigned((B * c.crop * c.crop + 255) / 256)), dim3(256), 0, s, U0, KP, UK, w, B,
+                           int(wr), int(wc), int(c.crop), cu0, ckp, cuk);
+        if (hipError_t e = hipGetLastError(); e != hipSuccess) {
+            rc = fail(ST_EHIP, std::string("crop3: ") + hipGetErrorString(e));
+            break;
+        }
         int lohi[4 * MAXB];
         for (int b = 0; b < B; ++b) {
             const int y = crop_yx[2 * (st * B + b)], x = crop_yx[2 * (st * B + b) + 1];
@@ -1517,8 +1542,6 @@ int surrogate_train(sg_model* m, float* params, float* optim, const float* coef,
         const double lr = double(c.lr) * 0.5 * (1.0 + std::cos(3.14159265358979323846 * double(g) / double(c.total_steps)));
         rc = surrogate_adam(m, params, grad, optim, int(g + 1), float(lr), c.beta1, c.beta2, c.eps, stream);
     }
-    // the judge's kernels are enqueued: destroying the host-side plan does not wait for them
-    stencil_destroy(judge);
     return rc;
 }
 

@@ -60,6 +60,10 @@ struct VArgs {
     int fields;              // fields one after another in src, kappa and dst
     float b;
     int tb;
+    // windows of larger fields: rows x cols cells of each at window_origin(); kappa always, src if src_whole,
+    // is then the larger field, w.rows x w.cols, and dst holds the windows one after another
+    VcWindows w;
+    int src_whole;
 };
 
 // A pass on register tiles (block_body.h).  The diffusivity enters once per pass as face values,
@@ -68,27 +72,39 @@ struct VArgs {
 // Rows and columns of kappa clamp at the grid's edge, which is the rule kappa(nb) := kappa(c).
 // Bound by the vector ALU: at 1024^2 x 16 steps the LDS-tile kernel this replaced took 80 us.
 template <int V, int RW, int NW, bool EDGE>
-__device__ __forceinline__ void vc_levels(const VArgs& a, const block::TileAt& at, int64_t field, float* lds) {
+__device__ __forceinline__ void vc_levels(const VArgs& a, const block::TileAt& at, int64_t f, float* lds) {
     using namespace block;
     const int lane = int(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
     const int64_t y0 = at.ty + wave * RW, x0 = at.tx + lane * V;
+    const int64_t field = f * a.rows * a.cols;
     const float* src = a.src + field;
     const float* kap = a.kappa + field;
+    int64_t pitch = a.cols, src_pitch = a.cols;
+    if (a.w.yx) {
+        pitch = a.w.cols;
+        const int64_t at0 = f * a.w.rows * pitch + window_origin(a.w.yx[2 * f], a.w.reach, a.w.rows, a.rows) * pitch +
+                            window_origin(a.w.yx[2 * f + 1], a.w.reach, pitch, a.cols);
+        kap = a.kappa + at0;
+        if (a.src_whole) {
+            src = a.src + at0;
+            src_pitch = pitch;
+        }
+    }
     float* dst = a.dst + field;
     bool col_ok[V];
 #pragma unroll
     for (int c = 0; c < V; ++c) col_ok[c] = !EDGE || (x0 + c >= 0 && x0 + c < a.cols);
     const bool all_cols = !EDGE || (x0 >= 0 && x0 + V <= a.cols);
-    auto load_row = [&](const float* f, int64_t y, float (&q)[V]) {  // y inside the grid; columns clamped
+    auto load_row = [&](const float* base, int64_t pitch, int64_t y, float (&q)[V]) {  // y inside the grid; columns clamped
         if (all_cols) {
-            load_cells<ST_F32, V>(f, y * a.cols + x0, q);
+            load_cells<ST_F32, V>(base, y * pitch + x0, q);
         } else {
 #pragma unroll
             for (int c = 0; c < V; ++c) {
                 const int64_t x = x0 + c < 0 ? 0 : x0 + c >= a.cols ? a.cols - 1 : x0 + c;
                 float one[1];
-                load_cells<ST_F32, 1>(f, y * a.cols + x, one);
+                load_cells<ST_F32, 1>(base, y * pitch + x, one);
                 q[c] = one[0];
             }
         }
@@ -98,9 +114,9 @@ __device__ __forceinline__ void vc_levels(const VArgs& a, const block::TileAt& a
     {
         float k[RW + 2][V];
 #pragma unroll
-        for (int r = 0; r < RW + 2; ++r) load_row(kap, clamp_row(y0 - 1 + r), k[r]);
+        for (int r = 0; r < RW + 2; ++r) load_row(kap, pitch, clamp_row(y0 - 1 + r), k[r]);
 #pragma unroll
-        for (int r = 0; r < RW; ++r) load_row(src, clamp_row(y0 + r), o[r]);
+        for (int r = 0; r < RW; ++r) load_row(src, src_pitch, clamp_row(y0 + r), o[r]);
 #pragma unroll
         for (int r = 0; r <= RW; ++r)
 #pragma unroll
@@ -181,9 +197,8 @@ __global__ __launch_bounds__(64 * NW) void varcoef_block(VArgs a) {
     float* lds = reinterpret_cast<float*>(lds4);
     const int64_t t = block::xcd_order(blockIdx.x, a.tiles * a.fields), f = t / a.tiles;
     const block::TileAt at = block::tile_at<1, V, RW, NW>(t - f * a.tiles, a.tiles_x, a.rows, a.cols, a.tb);
-    const int64_t field = f * a.rows * a.cols;
-    if (at.edge) vc_levels<V, RW, NW, true>(a, at, field, lds);
-    else vc_levels<V, RW, NW, false>(a, at, field, lds);
+    if (at.edge) vc_levels<V, RW, NW, true>(a, at, f, lds);
+    else vc_levels<V, RW, NW, false>(a, at, f, lds);
 }
 
 using VcFn = void (*)(VArgs);
@@ -203,8 +218,24 @@ VcFn varcoef_lookup(int def) {
 
 size_t varcoef_lds_bytes(int tb, int tx, int ty) { return vlds_bytes(tb, tx, ty); }
 
-int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, int fields,
-                   hipStream_t s) {
+// A pass of `levels` levels on register tiles over `fields` fields (or windows) of rows x cols cells.
+static int launch_vc_block(int tile, VArgs a, hipStream_t s) {
+    const block::Cover c = block::cover(tile, 1, a.tb, a.rows, a.cols);
+    if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
+    if (c.tiles * a.fields >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
+    const block::Def& d = block::kDefs[c.def];
+    VcFn fn = varcoef_lookup(c.def);
+    const size_t lds = block::lds_floats(1, d.v, d.rw, d.nw) * sizeof(float);
+    if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
+    a.tiles_x = c.tiles_x;
+    a.tiles = c.tiles;
+    clear_stale_error();
+    hipLaunchKernelGGL(fn, dim3(unsigned(c.tiles * a.fields)), dim3(64 * d.nw), lds, s, a);
+    ST_LAUNCH_CHECK("varcoef_block");
+    return ST_OK;
+}
+
+int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* kappa, int levels, hipStream_t s) {
     if (levels <= 0) {  // naive reference path
         SweepArgs a;
         a.src = src;
@@ -221,17 +252,21 @@ int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* 
         ST_LAUNCH_CHECK("varcoef_naive");
         return ST_OK;
     }
-    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), 1, levels, p->rows, p->cols);
-    if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
-    if (c.tiles * fields >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
-    const block::Def& d = block::kDefs[c.def];
-    VcFn fn = varcoef_lookup(c.def);
-    const size_t lds = block::lds_floats(1, d.v, d.rw, d.nw) * sizeof(float);
-    if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
-    const VArgs a{src, kappa, dst, p->rows, p->cols, c.tiles_x, c.tiles, fields, p->bq, levels};
-    clear_stale_error();
-    hipLaunchKernelGGL(fn, dim3(unsigned(c.tiles * fields)), dim3(64 * d.nw), lds, s, a);
-    ST_LAUNCH_CHECK("varcoef_block");
+    return launch_vc_block(tile_index(p->tile_x, p->tile_y),
+                           VArgs{src, kappa, dst, p->rows, p->cols, 0, 0, 1, p->bq, levels, VcWindows{}, 0}, s);
+}
+
+int varcoef_windows(const float* u0, const float* kappa, const VcWindows& w, int64_t rows, int64_t cols, int fields,
+                    int64_t steps, float* out, float* scratch, hipStream_t s) {
+    constexpr int kDepth = 8;  // 64 x 64 tiles that store 48 x 48: the fastest for windows of a few hundred cells
+    const int64_t passes = (steps + kDepth - 1) / kDepth;
+    const float* src = u0;
+    for (int64_t k = 0; k < passes; ++k) {
+        float* dst = (passes - 1 - k) % 2 == 0 ? out : scratch;
+        const int levels = int(steps / passes + (k < steps % passes));
+        if (int rc = launch_vc_block(0, VArgs{src, kappa, dst, rows, cols, 0, 0, fields, 0.0f, levels, w, k == 0}, s)) return rc;
+        src = dst;
+    }
     return ST_OK;
 }
 
