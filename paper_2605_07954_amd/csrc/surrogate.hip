@@ -657,17 +657,38 @@ __global__ __launch_bounds__(320) void l6_bwd_weight(const uint16_t* A5, const f
     if (j < 9 * C + 1) partial[int64_t(blk) * (9 * C + 1) + j] = acc;
 }
 
-// layers 2-5: dW[t][ci][co] = sum_p A[p + t][ci] dZ[p][co] on MFMA.  The region is processed in
-// 8-row chunks; per chunk the activation tile (with halo) is staged channel-major three times,
-// shifted by 0, 1, 2 pixels in x, and the gradient tile channel-major, so that each MFMA
-// operand (8 consecutive pixels of one channel) is one aligned 16-byte LDS read.
-// Wave w owns the output quarter (ci half w/2, co half w%2) for all 9 taps.
+// layers 2-5: dW[t][ci][co] = sum_p A[p + t][ci] dZ[p][co] on MFMA, K = the 32 pixels of a region row.
+// The operands want 8 consecutive pixels of one channel, memory holds the channels of one pixel side by
+// side: tiles are staged as they lie, 16 bytes at a time, and ds_read_b64_tr_b16 transposes on the way to
+// the registers.  (Within 16 lanes, lane 4 j + q addresses four channels from 4 q of pixel j, and lane i
+// receives channel i of the four pixels.)  The region is processed in 8-row chunks, the next one loaded
+// into registers while this one computes; a row's three x-shifted operands serve the three output rows
+// that read it.  Wave w owns the output quarter (ci half w/2, co half w%2) for all 9 taps.  Staging the
+// transposed tiles element by element, three shifted copies of the activations, took 47 us per layer at
+// 8 x 256^2; this takes 20.
 // db[co] = sum_p dZ[p][co] is accumulated from the staged gradient tile.
 constexpr int CH = 8;  // rows per chunk
+constexpr int ATP = (CH + 2) * (RW + 2), GTP = CH * RW;  // pixels of the staged tiles
+constexpr int ANU = (ATP * 4 + 255) / 256, GNU = GTP * 4 / 256;  // 16-byte chunks per thread
+
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+// 8 consecutive pixels from `pix` (per group of 16 lanes) of channel lane % 16 beyond c0.
+__device__ __forceinline__ bf16x8_t pixels8(const uint4* tile, int pix, int c0, int lane) {
+    using L = __attribute__((address_space(3))) s16x4_t;
+    const int s = lane & 15;
+    const char* at = reinterpret_cast<const char*>(tile) + (pix + s / 4) * (PSTRIDE * 16) + (c0 + 4 * (s % 4)) * 2;
+    struct {
+        s16x4_t lo, hi;
+    } r;
+    r.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L*)(at));
+    r.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((L*)(at + 4 * (PSTRIDE * 16)));
+    return __builtin_bit_cast(bf16x8_t, r);
+}
+
 __global__ __launch_bounds__(256) void mfma_bwd_weight(const uint16_t* A, const uint16_t* dZ, int nb, int H, int W,
                                                        float* partial) {
-    __shared__ uint16_t at[3][C][CH + 2][RW];  // [shift][ci][row][x]: A at (row-1, x+shift-1) of the chunk
-    __shared__ uint16_t gt[C][CH][RW];         // [co][row][x]
+    __shared__ uint4 at[ATP * PSTRIDE];  // pixel (row, x): A at (row - 1, x - 1) of the chunk
+    __shared__ uint4 gt[GTP * PSTRIDE];
     __shared__ float bsum[4][C];
     const int rx = (W + RW - 1) / RW, ry = (H + RH - 1) / RH;
     const int blk = blockIdx.x;
@@ -678,63 +699,63 @@ __global__ __launch_bounds__(256) void mfma_bwd_weight(const uint16_t* A, const 
     f32x4_t acc[9];
 #pragma unroll
     for (int t = 0; t < 9; ++t) acc[t] = f32x4_t{0, 0, 0, 0};
-    float bacc = 0.0f;  // thread c < 32: running bias sum of channel c... computed below
     if (threadIdx.x < 4 * C) bsum[threadIdx.x / C][threadIdx.x % C] = 0.0f;
+    // both tiles of a chunk (zero outside the field) into registers
+    uint4 ra[ANU], rg[GNU];
+    auto fetch = [&](int cy0) {
+#pragma unroll
+        for (int j = 0; j < ANU; ++j) {
+            const int k = int(threadIdx.x) + 256 * j, pix = k >> 2;
+            const int yy = cy0 - 1 + pix / (RW + 2), xx = x0 - 1 + pix % (RW + 2);
+            ra[j] = make_uint4(0, 0, 0, 0);
+            if (k < ATP * 4 && yy >= 0 && yy < H && xx >= 0 && xx < W)
+                ra[j] = reinterpret_cast<const uint4*>(A + ((int64_t(b) * H + yy) * W + xx) * C)[k & 3];
+        }
+#pragma unroll
+        for (int j = 0; j < GNU; ++j) {
+            const int k = int(threadIdx.x) + 256 * j, pix = k >> 2;
+            const int yy = cy0 + pix / RW, xx = x0 + pix % RW;
+            rg[j] = make_uint4(0, 0, 0, 0);
+            if (yy < H && xx < W) rg[j] = reinterpret_cast<const uint4*>(dZ + ((int64_t(b) * H + yy) * W + xx) * C)[k & 3];
+        }
+    };
+    fetch(y0);
     for (int c0 = 0; c0 < RH; c0 += CH) {
-        const int cy0 = y0 + c0;
-        __syncthreads();
-        // stage A: rows cy0-1 .. cy0+CH, cols x0-1 .. x0+RW (34 pixels), 4 chunks of 8 channels each
-        for (int k = threadIdx.x; k < (CH + 2) * (RW + 2) * 4; k += 256) {
-            const int pix = k >> 2, cq = k & 3;
-            const int row = pix / (RW + 2), col = pix % (RW + 2);
-            const int yy = cy0 - 1 + row, xx = x0 - 1 + col;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (yy >= 0 && yy < H && xx >= 0 && xx < W)
-                v = reinterpret_cast<const uint4*>(A + ((int64_t(b) * H + yy) * W + xx) * C)[cq];
-            const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
+        __syncthreads();  // the previous chunk is no longer read
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const uint16_t h = uint16_t(e & 1 ? wd[e >> 1] >> 16 : wd[e >> 1] & 0xffffu);
-                const int ci = cq * 8 + e;
-#pragma unroll
-                for (int s = 0; s < 3; ++s) {
-                    const int x = col - s;  // tile column col holds A(x0-1+col); copy s at x holds A(x0-1+x+s)
-                    if (x >= 0 && x < RW) at[s][ci][row][x] = h;
-                }
-            }
+        for (int j = 0; j < ANU; ++j) {
+            const int k = int(threadIdx.x) + 256 * j;
+            if (k < ATP * 4) at[slot(k >> 2, k & 3)] = ra[j];
         }
-        // stage dZ: rows cy0 .. cy0+CH-1, cols x0 .. x0+RW-1 (zero outside the field)
-        for (int k = threadIdx.x; k < CH * RW * 4; k += 256) {
-            const int pix = k >> 2, cq = k & 3;
-            const int row = pix / RW, col = pix % RW;
-            const int yy = cy0 + row, xx = x0 + col;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (yy < H && xx < W) v = reinterpret_cast<const uint4*>(dZ + ((int64_t(b) * H + yy) * W + xx) * C)[cq];
-            const uint32_t wd[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                gt[cq * 8 + e][row][col] = uint16_t(e & 1 ? wd[e >> 1] >> 16 : wd[e >> 1] & 0xffffu);
+        for (int j = 0; j < GNU; ++j) {
+            const int k = int(threadIdx.x) + 256 * j;
+            gt[slot(k >> 2, k & 3)] = rg[j];
         }
         __syncthreads();
+        if (c0 + CH < RH) fetch(y0 + c0 + CH);
         // bias partial: thread j < 128 sums channel j%32 over a quarter of the chunk's pixels
         if (threadIdx.x < 4 * C) {
             const int co = threadIdx.x % C, q = threadIdx.x / C;
+            const uint16_t* g16 = reinterpret_cast<const uint16_t*>(gt) + co;
             float s = 0.0f;
-            for (int rr = q * (CH / 4); rr < (q + 1) * (CH / 4); ++rr)
-                for (int x = 0; x < RW; ++x) s += bf2f(gt[co][rr][x]);
+            for (int p = q * (GTP / 4); p < (q + 1) * (GTP / 4); ++p) s += bf2f(g16[p * (PSTRIDE * 8)]);
             bsum[q][co] += s;
         }
-        // MFMA over the chunk: K = 32 pixels of one row per instruction
+        const int px = 8 * (lane >> 4);
+        bf16x8_t av[3][3];  // [input row mod 3][x shift]
+#pragma unroll
+        for (int row = 0; row < 2; ++row)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) av[row][kx] = pixels8(at, row * (RW + 2) + kx + px, 16 * mh, lane);
 #pragma unroll
         for (int rr = 0; rr < CH; ++rr) {
-            const bf16x8_t bv = *reinterpret_cast<const bf16x8_t*>(&gt[nh * 16 + (lane & 15)][rr][8 * (lane >> 4)]);
+            const bf16x8_t bv = pixels8(gt, rr * RW + px, 16 * nh, lane);
 #pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const int ky = t / 3, kx = t % 3;
-                const bf16x8_t av =
-                    *reinterpret_cast<const bf16x8_t*>(&at[kx][mh * 16 + (lane & 15)][rr + ky][8 * (lane >> 4)]);
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[t], 0, 0, 0);
-            }
+            for (int kx = 0; kx < 3; ++kx) av[(rr + 2) % 3][kx] = pixels8(at, (rr + 2) * (RW + 2) + kx + px, 16 * mh, lane);
+#pragma unroll
+            for (int t = 0; t < 9; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[(rr + t / 3) % 3][t % 3], bv, acc[t], 0, 0, 0);
         }
     }
     __syncthreads();
@@ -749,7 +770,6 @@ __global__ __launch_bounds__(256) void mfma_bwd_weight(const uint16_t* A, const 
         }
     if (threadIdx.x < C) out[9 * C * C + threadIdx.x] = ((bsum[0][threadIdx.x] + bsum[1][threadIdx.x]) +
                                                           bsum[2][threadIdx.x]) + bsum[3][threadIdx.x];
-    (void)bacc;
 }
 
 // grad[off + j] = sum_{blk} partial[blk][j] in block order (FP64 accumulation)
