@@ -574,87 +574,131 @@ constexpr int RH = 32, RW = 32;  // pixels per partial block
 constexpr int WCH = 8;  // rows per staged chunk
 
 // layer 1: dW1[t][ci][co] = sum_p X0[p + t][ci] dZ1[p][co], db1[co] = sum_p dZ1[p][co]  (all FP32)
-// one thread per (t, ci, co) output (576) plus 32 bias threads.
-__global__ __launch_bounds__(640) void l1_bwd_weight(const float* u0, const float* kappa, const float* scale,
+// one thread per (dy, ci, co) and its three dx (192 threads), plus 32 bias threads: along a row a thread
+// reads each gradient once and each input once for three FMAs (a thread per output read both for every
+// FMA: 61 us at 8 x 256^2, bound by LDS).
+__global__ __launch_bounds__(256) void l1_bwd_weight(const float* u0, const float* kappa, const float* scale,
                                                      const float* dZ1, int nb, int H, int W, float* partial) {
-    __shared__ float gz[WCH][RW][C];           // dZ1 of the chunk
-    __shared__ float xin[WCH + 2][RW + 2][2];  // X0 (scaled u0, centred kappa) with halo
+    constexpr int XP = RW + 4;  // padded row
+    __shared__ float gz[WCH][RW][C];                        // dZ1 of the chunk
+    __shared__ __align__(16) float xin[2][WCH + 2][XP];     // X0 (scaled u0, centred kappa) with halo
     const int rx = (W + RW - 1) / RW, ry = (H + RH - 1) / RH;
     const int blk = blockIdx.x;
     const int b = blk / (rx * ry), r = blk % (rx * ry);
     const int y0 = (r / rx) * RH, x0 = (r % rx) * RW;
     const int j = threadIdx.x;
     const float inv = scale[2 * b];
-    const int t = j / (2 * C), ci = (j / C) % 2, co = j % C;
-    const int dy = t / 3 - 1, dx = t % 3 - 1;
-    float acc = 0.0f;
+    const int co = j % C, ci = (j / C) % 2, dy = j / (2 * C);  // dy 0 .. 2: rows y - 1 .. y + 1
+    float acc[3] = {0.0f, 0.0f, 0.0f};
     for (int c0 = y0; c0 < y0 + RH; c0 += WCH) {
         __syncthreads();  // the previous chunk is no longer read
-        for (int e = j; e < WCH * RW * C; e += 640) {
-            const int k = e % C, x = (e / C) % RW, y = e / (C * RW);
+        for (int e = j; e < WCH * RW * (C / 4); e += 256) {
+            const int k = e % (C / 4), x = (e / (C / 4)) % RW, y = e / (C / 4 * RW);
             const int gy = c0 + y, gx = x0 + x;
-            gz[y][x][k] = (gy < H && gx < W) ? dZ1[((int64_t(b) * H + gy) * W + gx) * C + k] : 0.0f;
+            reinterpret_cast<float4*>(&gz[y][x][0])[k] =
+                (gy < H && gx < W) ? reinterpret_cast<const float4*>(dZ1 + ((int64_t(b) * H + gy) * W + gx) * C)[k]
+                                   : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         }
-        for (int e = j; e < (WCH + 2) * (RW + 2); e += 640) {
+        for (int e = j; e < (WCH + 2) * (RW + 2); e += 256) {
             const int x = e % (RW + 2), y = e / (RW + 2);
             const int gy = c0 + y - 1, gx = x0 + x - 1;
             const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
             const int64_t q = (int64_t(b) * H + gy) * W + gx;
-            xin[y][x][0] = in ? u0[q] * inv : 0.0f;
-            xin[y][x][1] = in ? (kappa[q] - KMID) / KHALF : 0.0f;
+            xin[0][y][x] = in ? u0[q] * inv : 0.0f;
+            xin[1][y][x] = in ? (kappa[q] - KMID) / KHALF : 0.0f;
         }
         __syncthreads();
-        if (j < 9 * 2 * C) {
+        if (j < 3 * 2 * C) {
+            for (int y = 0; y < WCH; ++y) {
+                const float* xr = xin[ci][y + dy];
+                float a0 = xr[0], a1 = xr[1];
+#pragma unroll 8
+                for (int x = 0; x < RW; ++x) {
+                    const float a2 = xr[x + 2], g = gz[y][x][co];
+                    acc[0] = __builtin_fmaf(a0, g, acc[0]);
+                    acc[1] = __builtin_fmaf(a1, g, acc[1]);
+                    acc[2] = __builtin_fmaf(a2, g, acc[2]);
+                    a0 = a1;
+                    a1 = a2;
+                }
+            }
+        } else if (j < 3 * 2 * C + C) {
             for (int y = 0; y < WCH; ++y)
 #pragma unroll 8
-                for (int x = 0; x < RW; ++x) acc = __builtin_fmaf(xin[y + 1 + dy][x + 1 + dx][ci], gz[y][x][co], acc);
-        } else if (j < 9 * 2 * C + C) {
-            const int cb = j - 9 * 2 * C;
-            for (int y = 0; y < WCH; ++y)
-#pragma unroll 8
-                for (int x = 0; x < RW; ++x) acc += gz[y][x][cb];
+                for (int x = 0; x < RW; ++x) acc[0] += gz[y][x][co];
         }
     }
-    if (j < 9 * 2 * C + C) partial[int64_t(blk) * (9 * 2 * C + C) + j] = acc;
+    float* out = partial + int64_t(blk) * (9 * 2 * C + C);
+    if (j < 3 * 2 * C) {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) out[((dy * 3 + dx) * 2 + ci) * C + co] = acc[dx];
+    } else if (j < 3 * 2 * C + C) {
+        out[9 * 2 * C + co] = acc[0];
+    }
 }
 
 // layer 6: dW6[t][ci] = sum_p A5[p + t][ci] dF[p], db6 = sum_p dF[p]
-__global__ __launch_bounds__(320) void l6_bwd_weight(const uint16_t* A5, const float* dF, int nb, int H, int W,
+// one thread per (dy, ci) and its three dx (96 threads), and a bias thread; activations stay BF16 in LDS.
+// Along a row a thread reads each activation once for three FMAs and four gradients at a time (a thread
+// per output read both for every FMA: 78 us at 8 x 256^2, bound by LDS).
+__global__ __launch_bounds__(128) void l6_bwd_weight(const uint16_t* A5, const float* dF, int nb, int H, int W,
                                                      float* partial) {
-    __shared__ float at[WCH + 2][RW + 2][C + 1];  // A5 with halo (padded: lanes of one row differ in ci)
-    __shared__ float gf[WCH][RW];
+    constexpr int ARU = (RW + 2) * 4 + 4;  // 16-byte chunks per row, padded: the rows of a wave's two halves hit other banks
+    __shared__ uint4 at[WCH + 2][ARU];     // A5 with halo
+    __shared__ __align__(16) float gf[WCH][RW];
     const int rx = (W + RW - 1) / RW, ry = (H + RH - 1) / RH;
     const int blk = blockIdx.x;
     const int b = blk / (rx * ry), r = blk % (rx * ry);
     const int y0 = (r / rx) * RH, x0 = (r % rx) * RW;
     const int j = threadIdx.x;
-    const int t = j / C, ci = j % C;
-    const int dy = t / 3 - 1, dx = t % 3 - 1;
-    float acc = 0.0f;
+    const int ci = j % C, dy = j / C;  // dy 0 .. 2: rows y - 1 .. y + 1
+    float acc[3] = {0.0f, 0.0f, 0.0f};
     for (int c0 = y0; c0 < y0 + RH; c0 += WCH) {
         __syncthreads();
-        for (int e = j; e < (WCH + 2) * (RW + 2) * C; e += 320) {
-            const int k = e % C, x = (e / C) % (RW + 2), y = e / (C * (RW + 2));
+        for (int e = j; e < (WCH + 2) * (RW + 2) * 4; e += 128) {
+            const int k = e & 3, x = (e >> 2) % (RW + 2), y = (e >> 2) / (RW + 2);
             const int gy = c0 + y - 1, gx = x0 + x - 1;
-            at[y][x][k] = (gy >= 0 && gy < H && gx >= 0 && gx < W)
-                              ? bf2f(A5[((int64_t(b) * H + gy) * W + gx) * C + k]) : 0.0f;
+            at[y][4 * x + k] = (gy >= 0 && gy < H && gx >= 0 && gx < W)
+                                   ? reinterpret_cast<const uint4*>(A5 + ((int64_t(b) * H + gy) * W + gx) * C)[k]
+                                   : make_uint4(0, 0, 0, 0);
         }
-        for (int e = j; e < WCH * RW; e += 320) {
+        for (int e = j; e < WCH * RW; e += 128) {
             const int x = e % RW, y = e / RW;
             const int gy = c0 + y, gx = x0 + x;
             gf[y][x] = (gy < H && gx < W) ? dF[(int64_t(b) * H + gy) * W + gx] : 0.0f;
         }
         __syncthreads();
-        if (j < 9 * C) {
+        if (j < 3 * C) {
+            for (int y = 0; y < WCH; ++y) {
+                const uint16_t* ar = reinterpret_cast<const uint16_t*>(at[y + dy]) + ci;
+                float a0 = bf2f(ar[0]), a1 = bf2f(ar[C]);
+#pragma unroll 2
+                for (int x = 0; x < RW; x += 4) {
+                    const float4 g4 = *reinterpret_cast<const float4*>(&gf[y][x]);
+                    const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float a2 = bf2f(ar[(x + i + 2) * C]);
+                        acc[0] = __builtin_fmaf(a0, g[i], acc[0]);
+                        acc[1] = __builtin_fmaf(a1, g[i], acc[1]);
+                        acc[2] = __builtin_fmaf(a2, g[i], acc[2]);
+                        a0 = a1;
+                        a1 = a2;
+                    }
+                }
+            }
+        } else if (j == 3 * C) {
             for (int y = 0; y < WCH; ++y)
-#pragma unroll 8
-                for (int x = 0; x < RW; ++x) acc = __builtin_fmaf(at[y + 1 + dy][x + 1 + dx][ci], gf[y][x], acc);
-        } else if (j == 9 * C) {
-            for (int y = 0; y < WCH; ++y)
-                for (int x = 0; x < RW; ++x) acc += gf[y][x];
+                for (int x = 0; x < RW; ++x) acc[0] += gf[y][x];
         }
     }
-    if (j < 9 * C + 1) partial[int64_t(blk) * (9 * C + 1) + j] = acc;
+    float* out = partial + int64_t(blk) * (9 * C + 1);
+    if (j < 3 * C) {
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx) out[(dy * 3 + dx) * C + ci] = acc[dx];
+    } else if (j == 3 * C) {
+        out[9 * C] = acc[0];
+    }
 }
 
 // layers 2-5: dW[t][ci][co] = sum_p A[p + t][ci] dZ[p][co] on MFMA, K = the 32 pixels of a region row.
@@ -1335,7 +1379,7 @@ static int loss_grad_impl(const float* params, const float* u0, const float* kap
     float* partial = reinterpret_cast<float*>(ws + L.partial);
     const unsigned grg = unsigned(L.nblk_rg);
     // layer 6
-    hipLaunchKernelGGL(l6_bwd_weight, dim3(grg), dim3(320), 0, s, act(4), dF, nb, H, W, partial);
+    hipLaunchKernelGGL(l6_bwd_weight, dim3(grg), dim3(128), 0, s, act(4), dF, nb, H, W, partial);
     ST_LAUNCH_CHECK("l6_bwd_weight");
     hipLaunchKernelGGL(reduce_partials, dim3((9 * C + 1 + 63) / 64), dim3(64 * RP_WAVES), 0, s, partial, L.nblk_rg, 9 * C + 1,
                        grad + woff(5));
@@ -1368,7 +1412,7 @@ static int loss_grad_impl(const float* params, const float* u0, const float* kap
         cur ^= 1;
     }
     // layer 1
-    hipLaunchKernelGGL(l1_bwd_weight, dim3(grg), dim3(640), 0, s, u0, kappa, scale, dz1, nb, H, W, partial);
+    hipLaunchKernelGGL(l1_bwd_weight, dim3(grg), dim3(256), 0, s, u0, kappa, scale, dz1, nb, H, W, partial);
     ST_LAUNCH_CHECK("l1_bwd_weight");
     hipLaunchKernelGGL(reduce_partials, dim3((9 * 2 * C + C + 63) / 64), dim3(64 * RP_WAVES), 0, s, partial, L.nblk_rg,
                        9 * 2 * C + C, grad + woff(0));
