@@ -576,11 +576,11 @@ constexpr int WCH = 8;  // rows per staged chunk
 // layer 1: dW1[t][ci][co] = sum_p X0[p + t][ci] dZ1[p][co], db1[co] = sum_p dZ1[p][co]  (all FP32)
 // one thread per (dy, ci, co) and its three dx (192 threads), plus 32 bias threads: along a row a thread
 // reads each gradient once and each input once for three FMAs (a thread per output read both for every
-// FMA: 61 us at 8 x 256^2, bound by LDS).
+// FMA: 61 us at 8 x 256^2, bound by LDS; this takes 30).
 __global__ __launch_bounds__(256) void l1_bwd_weight(const float* u0, const float* kappa, const float* scale,
                                                      const float* dZ1, int nb, int H, int W, float* partial) {
     constexpr int XP = RW + 4;  // padded row
-    __shared__ float gz[WCH][RW][C];                        // dZ1 of the chunk
+    __shared__ __align__(16) float gz[WCH][RW][C];                        // dZ1 of the chunk
     __shared__ __align__(16) float xin[2][WCH + 2][XP];     // X0 (scaled u0, centred kappa) with halo
     const int rx = (W + RW - 1) / RW, ry = (H + RH - 1) / RH;
     const int blk = blockIdx.x;
@@ -590,24 +590,40 @@ __global__ __launch_bounds__(256) void l1_bwd_weight(const float* u0, const floa
     const float inv = scale[2 * b];
     const int co = j % C, ci = (j / C) % 2, dy = j / (2 * C);  // dy 0 .. 2: rows y - 1 .. y + 1
     float acc[3] = {0.0f, 0.0f, 0.0f};
+    // a chunk (zero outside the field) into registers: the next one loads while this one computes
+    constexpr int NG = WCH * RW * (C / 4) / 256, NX = ((WCH + 2) * (RW + 2) + 255) / 256;
+    float4 rg[NG];
+    float2 rx2[NX];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+            const int e = j + 256 * n, k = e % (C / 4), gx = x0 + (e / (C / 4)) % RW, gy = c0 + e / (C / 4 * RW);
+            rg[n] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (gy < H && gx < W) rg[n] = reinterpret_cast<const float4*>(dZ1 + ((int64_t(b) * H + gy) * W + gx) * C)[k];
+        }
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            const int e = j + 256 * n, gy = c0 + e / (RW + 2) - 1, gx = x0 + e % (RW + 2) - 1;
+            const bool in = e < (WCH + 2) * (RW + 2) && gy >= 0 && gy < H && gx >= 0 && gx < W;
+            const int64_t q = (int64_t(b) * H + gy) * W + gx;
+            rx2[n] = in ? make_float2(u0[q] * inv, (kappa[q] - KMID) / KHALF) : make_float2(0.0f, 0.0f);
+        }
+    };
+    fetch(y0);
     for (int c0 = y0; c0 < y0 + RH; c0 += WCH) {
         __syncthreads();  // the previous chunk is no longer read
-        for (int e = j; e < WCH * RW * (C / 4); e += 256) {
-            const int k = e % (C / 4), x = (e / (C / 4)) % RW, y = e / (C / 4 * RW);
-            const int gy = c0 + y, gx = x0 + x;
-            reinterpret_cast<float4*>(&gz[y][x][0])[k] =
-                (gy < H && gx < W) ? reinterpret_cast<const float4*>(dZ1 + ((int64_t(b) * H + gy) * W + gx) * C)[k]
-                                   : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        }
-        for (int e = j; e < (WCH + 2) * (RW + 2); e += 256) {
-            const int x = e % (RW + 2), y = e / (RW + 2);
-            const int gy = c0 + y - 1, gx = x0 + x - 1;
-            const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
-            const int64_t q = (int64_t(b) * H + gy) * W + gx;
-            xin[0][y][x] = in ? u0[q] * inv : 0.0f;
-            xin[1][y][x] = in ? (kappa[q] - KMID) / KHALF : 0.0f;
+#pragma unroll
+        for (int n = 0; n < NG; ++n) reinterpret_cast<float4*>(&gz[0][0][0])[j + 256 * n] = rg[n];
+#pragma unroll
+        for (int n = 0; n < NX; ++n) {
+            const int e = j + 256 * n;
+            if (e < (WCH + 2) * (RW + 2)) {
+                xin[0][e / (RW + 2)][e % (RW + 2)] = rx2[n].x;
+                xin[1][e / (RW + 2)][e % (RW + 2)] = rx2[n].y;
+            }
         }
         __syncthreads();
+        if (c0 + WCH < y0 + RH) fetch(c0 + WCH);
         if (j < 3 * 2 * C) {
             for (int y = 0; y < WCH; ++y) {
                 const float* xr = xin[ci][y + dy];
@@ -640,8 +656,8 @@ __global__ __launch_bounds__(256) void l1_bwd_weight(const float* u0, const floa
 // layer 6: dW6[t][ci] = sum_p A5[p + t][ci] dF[p], db6 = sum_p dF[p]
 // one thread per (dy, ci) and its three dx (96 threads), and a bias thread; activations stay BF16 in LDS.
 // Along a row a thread reads each activation once for three FMAs and four gradients at a time (a thread
-// per output read both for every FMA: 78 us at 8 x 256^2, bound by LDS).
-__global__ __launch_bounds__(128) void l6_bwd_weight(const uint16_t* A5, const float* dF, int nb, int H, int W,
+// per output read both for every FMA: 78 us at 8 x 256^2, bound by LDS; this takes 27).
+__global__ __launch_bounds__(256) void l6_bwd_weight(const uint16_t* A5, const float* dF, int nb, int H, int W,
                                                      float* partial) {
     constexpr int ARU = (RW + 2) * 4 + 4;  // 16-byte chunks per row, padded: the rows of a wave's two halves hit other banks
     __shared__ uint4 at[WCH + 2][ARU];     // A5 with halo
@@ -653,21 +669,34 @@ __global__ __launch_bounds__(128) void l6_bwd_weight(const uint16_t* A5, const f
     const int j = threadIdx.x;
     const int ci = j % C, dy = j / C;  // dy 0 .. 2: rows y - 1 .. y + 1
     float acc[3] = {0.0f, 0.0f, 0.0f};
-    for (int c0 = y0; c0 < y0 + RH; c0 += WCH) {
-        __syncthreads();
-        for (int e = j; e < (WCH + 2) * (RW + 2) * 4; e += 128) {
-            const int k = e & 3, x = (e >> 2) % (RW + 2), y = (e >> 2) / (RW + 2);
+    // a chunk (zero outside the field) into registers: the next one loads while this one computes
+    constexpr int NA = ((WCH + 2) * (RW + 2) * 4 + 255) / 256;
+    uint4 ra[NA];
+    float rf;
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+            const int e = j + 256 * n, k = e & 3, x = (e >> 2) % (RW + 2), y = (e >> 2) / (RW + 2);
             const int gy = c0 + y - 1, gx = x0 + x - 1;
-            at[y][4 * x + k] = (gy >= 0 && gy < H && gx >= 0 && gx < W)
-                                   ? reinterpret_cast<const uint4*>(A5 + ((int64_t(b) * H + gy) * W + gx) * C)[k]
-                                   : make_uint4(0, 0, 0, 0);
+            ra[n] = make_uint4(0, 0, 0, 0);
+            if (y < WCH + 2 && gy >= 0 && gy < H && gx >= 0 && gx < W)
+                ra[n] = reinterpret_cast<const uint4*>(A5 + ((int64_t(b) * H + gy) * W + gx) * C)[k];
         }
-        for (int e = j; e < WCH * RW; e += 128) {
-            const int x = e % RW, y = e / RW;
-            const int gy = c0 + y, gx = x0 + x;
-            gf[y][x] = (gy < H && gx < W) ? dF[(int64_t(b) * H + gy) * W + gx] : 0.0f;
+        const int gy = c0 + j / RW, gx = x0 + j % RW;
+        rf = (gy < H && gx < W) ? dF[(int64_t(b) * H + gy) * W + gx] : 0.0f;
+    };
+    static_assert(WCH * RW == 256, "a gradient per thread and chunk");
+    fetch(y0);
+    for (int c0 = y0; c0 < y0 + RH; c0 += WCH) {
+        __syncthreads();  // the previous chunk is no longer read
+#pragma unroll
+        for (int n = 0; n < NA; ++n) {
+            const int e = j + 256 * n, y = (e >> 2) / (RW + 2);
+            if (y < WCH + 2) at[y][4 * ((e >> 2) % (RW + 2)) + (e & 3)] = ra[n];
         }
+        gf[j / RW][j % RW] = rf;
         __syncthreads();
+        if (c0 + WCH < y0 + RH) fetch(c0 + WCH);
         if (j < 3 * C) {
             for (int y = 0; y < WCH; ++y) {
                 const uint16_t* ar = reinterpret_cast<const uint16_t*>(at[y + dy]) + ci;
@@ -1379,7 +1408,7 @@ static int loss_grad_impl(const float* params, const float* u0, const float* kap
     float* partial = reinterpret_cast<float*>(ws + L.partial);
     const unsigned grg = unsigned(L.nblk_rg);
     // layer 6
-    hipLaunchKernelGGL(l6_bwd_weight, dim3(grg), dim3(128), 0, s, act(4), dF, nb, H, W, partial);
+    hipLaunchKernelGGL(l6_bwd_weight, dim3(grg), dim3(256), 0, s, act(4), dF, nb, H, W, partial);
     ST_LAUNCH_CHECK("l6_bwd_weight");
     hipLaunchKernelGGL(reduce_partials, dim3((9 * C + 1 + 63) / 64), dim3(64 * RP_WAVES), 0, s, partial, L.nblk_rg, 9 * C + 1,
                        grad + woff(5));
