@@ -103,6 +103,12 @@ size_t elem_size(int storage);
 
 // launchers (sweep.hip / varcoef.hip); return ST_OK or an error code
 int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa, int levels, hipStream_t s);
+// A pass on register tiles that also writes per tile the sums, over the tile's cells x, of (x - x before the
+// last level)^2 and of x^2: 2 doubles for each of sums_tiles() tiles (0: no such pass for this plan).
+int launch_sums(const st_plan* p, const void* src, void* dst, int levels, double* sums, int64_t* tiles, hipStream_t s);
+int64_t sums_tiles(const st_plan* p, int levels);
+// Cells a pass of `levels` levels on register tiles computes, margins included.
+double block_work(const st_plan* p, int levels);
 int launch_naive(const st_plan* p, const void* src, void* dst, const float* kappa, hipStream_t s);
 // columns per lane when the marching kernels run a pass of the tiled variant, else 0 (sweep.hip)
 int tiled_march_columns(const st_plan* p, int levels);

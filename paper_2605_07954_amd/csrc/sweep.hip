@@ -271,13 +271,13 @@ BlockFn block_lookup(int storage, int shape, int r, int def) {
     return nullptr;
 }
 
-// A pass on register tiles.
-int launch_block(const st_plan* p, const void* src, void* dst, int levels, hipStream_t s) {
+// A pass on register tiles; with `sums` its last level's sums per tile (sweep_block_sums), `tiles` of them.
+int launch_block(const st_plan* p, const void* src, void* dst, int levels, double* sums, int64_t* tiles, hipStream_t s) {
     const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
     if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
     if (c.tiles >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
     const block::Def& d = block::kDefs[c.def];
-    BlockFn fn = block_lookup(p->storage, p->shape, p->radius, c.def);
+    BlockFn fn = sums ? sums_lookup(p->storage, p->shape, p->radius, c.def) : block_lookup(p->storage, p->shape, p->radius, c.def);
     if (!fn) return fail(ST_EUNSUPPORTED, "no tiled kernel for this storage/shape/radius/tile");
     const size_t lds = block::lds_floats(p->radius, d.v, d.rw, d.nw) * sizeof(float);
     if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
@@ -291,10 +291,12 @@ int launch_block(const st_plan* p, const void* src, void* dst, int levels, hipSt
     a.stop = p->stop;
     a.b = p->bq;
     a.tb = levels;
+    a.sums = sums;
     std::memcpy(a.w, p->w, sizeof(a.w));
     clear_stale_error();
     hipLaunchKernelGGL(fn, dim3(unsigned(a.tiles)), dim3(64 * d.nw), lds, s, a);
     ST_LAUNCH_CHECK("sweep_block");
+    if (tiles) *tiles = c.tiles;
     return ST_OK;
 }
 
@@ -450,7 +452,24 @@ int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa
     }
     if (p->variant == VARIANT_TILED)
         if (const int vmax = tiled_march_columns(p, levels)) return launch_march(p, src, dst, levels, vmax, s);
-    return launch_block(p, src, dst, levels, s);
+    return launch_block(p, src, dst, levels, nullptr, nullptr, s);
+}
+
+int64_t sums_tiles(const st_plan* p, int levels) {
+    if (p->kind != KIND_CONST || p->bc != ST_BC_CONST) return 0;
+    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    return c.def < 0 || c.tiles >= int64_t(1) << 31 ? 0 : c.tiles;
+}
+
+double block_work(const st_plan* p, int levels) {
+    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    if (c.def < 0) return HUGE_VAL;
+    const block::Def& d = block::kDefs[c.def];
+    return double(c.tiles) * (64 * d.v * d.rw * d.nw) * levels;
+}
+
+int launch_sums(const st_plan* p, const void* src, void* dst, int levels, double* sums, int64_t* tiles, hipStream_t s) {
+    return launch_block(p, src, dst, levels, sums, tiles, s);
 }
 
 }  // namespace st
