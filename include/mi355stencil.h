@@ -135,9 +135,9 @@ int stencil_set_blocking(st_plan* plan, int tb, int tile_x, int tile_y);
                                  register ring, side columns by lane shifts; tb up to 8 / 6 /
                                  4 / 3 (star, r = 1 / 2 / 3 / 4) or 6 / 3 / 2 / 2 (box); the
                                  tile is ignored; any storage, width and alignment (four
-                                 columns per lane: one vector access per lane and row when
-                                 cols % 4 == 0 and the buffers are 16-byte aligned, else one
-                                 element access per column)                                     */
+                                 columns per lane: one vector access per lane and row, or on
+                                 grids of less than 256 columns and cols % 4 != 0 one element
+                                 access per column)                                             */
 #define ST_VARIANT_MARCH8  3  /* the same marching pass with eight columns per lane when
                                  cols % 8 == 0 and the buffers are 16-byte aligned (else as
                                  ST_VARIANT_MARCH); tb up to 8 / 4 / 3 / 2 (star) or

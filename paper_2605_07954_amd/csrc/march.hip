@@ -4,7 +4,7 @@
 // BF16 or FP16; arithmetic is FP32 and every level is rounded to the storage type.
 //
 // One wavefront owns a band of columns, V per lane (V = 8 or 4 with one or two 16-byte loads, or one
-// 8-byte load, per lane and row; for any other width or alignment V = 4 with one element access
+// 8-byte load, per lane and row; for narrow grids of an odd width V = 4 with one element access
 // per column; or V = 1, many short tasks for small grids), and walks down a segment of rows.  Each
 // input row is read from HBM once per band; the r columns a lane needs on either side
 // come from neighbouring lanes through DPP wave shifts (the value at column c < 0 is the previous
@@ -67,15 +67,17 @@ int march_max_tb(int shape, int radius, int vmax) {
 bool march_usable(const st_plan* p) { return p->kind == KIND_CONST && p->radius <= 4; }
 
 int launch_march(const st_plan* p, const void* src, void* dst, int levels, int vmax, hipStream_t s) {
-    // V columns per lane with one vector access per lane and row when every row starts on a
-    // 16-byte boundary (cols % V == 0 and aligned buffers; four 16-bit cells are 8 bytes, which the
-    // same condition covers); else four columns per lane with element accesses (mode 0); vmax 1:
-    // one column per lane, any width and alignment
+    // Four columns per lane with one vector access per lane and row, at any width and alignment, when no
+    // lane's vector straddles the grid's side (march_layout.h; 4099 x 5003, halo 1.5, us a pass with four
+    // element accesses / one vector: star r = 3 at tb 1 42 / 34, tb 3 48 / 46, box r = 3 at tb 2 99 / 78);
+    // else, on narrow grids, element accesses (mode 0).  Eight columns per lane where rows are whole and
+    // aligned vectors of eight (at other widths four are faster: star r = 2 at tb 4 41.5 / 46.8, box r = 3
+    // at tb 2 76 / 98).  vmax 1: one column per lane, any width.  48 steps of the tuned plan: 704 -> 607 us.
     // (periodic and framed grids have no eight-column kernels: they take four columns per lane)
     const bool xbc = p->bc != ST_BC_CONST;
     if (xbc && vmax == 8) vmax = 4;
     const bool aligned = (reinterpret_cast<uintptr_t>(src) % 16) == 0 && (reinterpret_cast<uintptr_t>(dst) % 16) == 0;
-    const int mode = vmax == 1 ? 1 : aligned && vmax == 8 && p->cols % 8 == 0 ? 8 : aligned && p->cols % 4 == 0 ? 4 : 0;
+    const int mode = vmax == 1 ? 1 : vmax == 8 && aligned && p->cols % 8 == 0 ? 8 : march::whole_lanes(p->cols, 4) ? 4 : 0;
     const int V = mode == 8 ? 8 : mode == 1 ? 1 : 4;
     MarchFn fn = march_lookup(p->storage, mode, p->shape, p->radius, levels, xbc, p->bc == ST_BC_PERIODIC);
     if (!fn) return fail(ST_EUNSUPPORTED, "no row-marching kernel for this shape/radius/depth");

@@ -140,8 +140,8 @@ template <int S, int V>
 struct Elems {
     typename Fmt<S>::T v[V];
 };
-// VEC: one vector access per lane and row (cols % V == 0, 16-byte aligned rows); otherwise V
-// element accesses.  V = 1 is the same either way.
+// VEC: one vector access per lane and row, where no lane's vector straddles the grid's side (march_layout.h);
+// otherwise V element accesses.  V = 1 is the same either way.
 template <int S, int V, bool VEC>
 struct RawTSel {
     using type = Elems<S, V>;
@@ -158,7 +158,7 @@ template <int S, int V, bool VEC>
 using RawT = typename RawTSel<S, V, VEC>::type;
 
 // Which of a lane's V columns lie inside the grid.  With vector accesses (and V = 1) all or none,
-// since cols % V == 0; with element accesses each column on its own.
+// since no lane straddles a side; with element accesses each column on its own.
 template <int V>
 struct ColMask {
     bool ok[V];
@@ -199,30 +199,34 @@ template <>
 struct Bits<16> {
     using type = unsigned __attribute__((ext_vector_type(4)));
 };
-template <typename X>
+// Global memory takes vector accesses that are only element-aligned, so rows of any length and start load
+// and store whole vectors: T is the element.
+template <typename T, int N>
+using VecAt __attribute__((aligned(sizeof(T)))) = typename Bits<N>::type;
+template <typename X, typename T>
 __device__ __forceinline__ X gload(const void* p) {
     if constexpr (sizeof(X) == 32) {  // two 16-byte halves
-        using H = typename Bits<16>::type;
+        using H = VecAt<T, 16>;
         struct Two {
-            H a, b;
+            typename Bits<16>::type a, b;
         } t;
         t.a = ((const Glob<H>*)p)[0];
         t.b = ((const Glob<H>*)p)[1];
         return __builtin_bit_cast(X, t);
     } else {
-        using B = typename Bits<sizeof(X)>::type;
-        return __builtin_bit_cast(X, *(const Glob<B>*)p);
+        const typename Bits<sizeof(X)>::type b = *(const Glob<VecAt<T, sizeof(X)>>*)p;
+        return __builtin_bit_cast(X, b);
     }
 }
-template <typename X>
+template <typename T, typename X>
 __device__ __forceinline__ void gstore(void* p, const X& x) {
-    using B = typename Bits<sizeof(X)>::type;
-    *(Glob<B>*)p = __builtin_bit_cast(B, x);
+    *(Glob<VecAt<T, sizeof(X)>>*)p = __builtin_bit_cast(typename Bits<sizeof(X)>::type, x);
 }
 
 template <int S, int V>
 __device__ __forceinline__ Raw<S, V> load_raw(const void* src, int64_t off) {
-    return gload<Raw<S, V>>(static_cast<const typename Fmt<S>::T*>(src) + off);
+    using T = typename Fmt<S>::T;
+    return gload<Raw<S, V>, T>(static_cast<const T*>(src) + off);
 }
 
 // Interior tasks address a lane's cells as a wavefront-uniform pointer (row start plus the band's
@@ -235,7 +239,7 @@ __device__ __forceinline__ uint32_t lane_bytes() {
 template <int S, int V>
 __device__ __forceinline__ Raw<S, V> load_lane(const void* src, int64_t first, uint32_t loff) {
     const char* p = reinterpret_cast<const char*>(static_cast<const typename Fmt<S>::T*>(src) + first);
-    return gload<Raw<S, V>>(p + loff);
+    return gload<Raw<S, V>, typename Fmt<S>::T>(p + loff);
 }
 
 // The rows a task loads: its input rows y0 - R TB .. y1 - 1 + R TB, cut to the grid.  Fetches past
@@ -301,17 +305,17 @@ template <int S, int V>
 __device__ __forceinline__ void store_cells(void* dst, int64_t off, const Cells<V>& q) {
     using T = typename Fmt<S>::T;
     if constexpr (V == 1) {
-        gstore(static_cast<T*>(dst) + off, Fmt<S>::st(q.c[0]));
+        gstore<T>(static_cast<T*>(dst) + off, Fmt<S>::st(q.c[0]));
     } else if constexpr (S != ST_F32) {  // four (eight) 16-bit cells: one 8-byte (16-byte) store
         uint32_t w[V / 2];
 #pragma unroll
         for (int k = 0; k < V / 2; ++k) w[k] = Fmt<S>::st2(q.c[2 * k], q.c[2 * k + 1]);
-        gstore(static_cast<T*>(dst) + off, w);
+        gstore<T>(static_cast<T*>(dst) + off, w);
     } else {
 #pragma unroll
         for (int k = 0; k < V; k += 4) {
             const float v4[4] = {q.c[k], q.c[k + 1], q.c[k + 2], q.c[k + 3]};
-            gstore(static_cast<T*>(dst) + off + k, v4);
+            gstore<T>(static_cast<T*>(dst) + off + k, v4);
         }
     }
 }
@@ -348,7 +352,7 @@ __device__ __forceinline__ void set_own(Row<R, V>& x, const Cells<V>& q) {
 // (which EDGE tasks cut to the grid; the cells a clamped row stands for are replaced by their
 // outside value when it is used, see `cells_of`, or never feed a stored output), and EDGE tasks
 // clamp columns into the grid too, or wrap row and columns on a periodic grid.  A lane's vector
-// never straddles the grid's side (cols % V == 0, and so is its first column), so it wraps whole.
+// never straddles the grid's side, so it wraps whole.
 template <int S, int V, bool VEC, bool EDGE, int XBC, bool UP = false>
 __device__ __forceinline__ RawT<S, V, VEC> fetch_raw(const MarchView& a, int64_t gy, int64_t gx, const ColMask<V>& m,
                                                      int64_t X0, const RowSpan& sp) {
@@ -368,7 +372,7 @@ __device__ __forceinline__ RawT<S, V, VEC> fetch_raw(const MarchView& a, int64_t
         const typename Fmt<S>::T* row = static_cast<const typename Fmt<S>::T*>(a.src) + g * cols;
 #pragma unroll
         for (int c = 0; c < V; ++c)
-            r.v[c] = gload<typename Fmt<S>::T>(row + (wrap ? wrap_index(gx + c, cols) : (EDGE && !m.ok[c] ? 0 : gx + c)));
+            r.v[c] = gload<typename Fmt<S>::T, typename Fmt<S>::T>(row + (wrap ? wrap_index(gx + c, cols) : (EDGE && !m.ok[c] ? 0 : gx + c)));
         return r;
     }
 }
@@ -426,7 +430,7 @@ __device__ __forceinline__ void store_row(void* dst, int64_t row_off, int64_t gx
         typename Fmt<S>::T* row = static_cast<typename Fmt<S>::T*>(dst) + row_off;
 #pragma unroll
         for (int c = 0; c < V; ++c)
-            if (!EDGE || m.ok[c]) gstore(row + gx + c, Fmt<S>::st(q.c[c]));
+            if (!EDGE || m.ok[c]) gstore<typename Fmt<S>::T>(row + gx + c, Fmt<S>::st(q.c[c]));
     }
 }
 
@@ -499,12 +503,13 @@ __device__ __forceinline__ Cells<V> apply(const Row<R, V>* ring, int base, const
 // UP marches the segment from its last row to its first: the same steps with the row order
 // reversed (iteration i computes level-1 row y1 - 1 + R(TB-1) - i, and so on), and each ring read
 // through the reversed slot order, so that every cell still takes its taps in row-major order.
-template <int S, int R, int V, int SHAPE, int TB, int D, bool EDGE, bool VEC, int XBC, bool UP = false,
+template <int S, int R, int V, int SHAPE, int TB, int D, bool EDGE, bool VECS, int XBC, bool UP = false,
           bool SHARE = false>
 __device__ __forceinline__ void march_levels(const MarchView& a, const float* w, int lane, int64_t y0, int64_t y1,
                                              int64_t X0, const SharedRows& sh = SharedRows{nullptr, 0, 0},
                                              int lo = -1, int hi = -1) {
     constexpr int N = 2 * R + 1;
+    constexpr bool VEC = VECS || !EDGE;
     static_assert(D % N == 0, "the FIFO length must be a multiple of the ring length");
     constexpr int U = D > 0 ? D : N;  // unroll
     constexpr int H = halo_lanes(R, TB, V);
@@ -707,23 +712,24 @@ __device__ __forceinline__ void march_task_dir(const MarchView& a, const float* 
 template <int S, int R, int V, int TB, bool VEC = true>
 __device__ __forceinline__ void stage_rows(const MarchView& a, int lane, int64_t y0, int64_t y1, int64_t X0,
                                            int64_t r0, int64_t o0, float4* dst) {
-    using RawR = RawT<S, V, VEC>;
     constexpr int RT = R * TB;
     const int64_t gx = X0 + V * lane;
     const ColMask<V> cm = col_mask<V, VEC>(gx, a.cols);
     const int64_t need_lo = y0 - R * TB, need_hi = y1 - 1 + R * TB;
-    RawR raw[RT];
+    float4 raw[RT];
     if (task_edge<R, TB>(a, y0, y1, X0, V)) {
         const RowSpan sp{need_lo < 0 ? 0 : need_lo, need_hi > a.rows - 1 ? a.rows - 1 : need_hi};
 #pragma unroll
-        for (int t = 0; t < RT; ++t) raw[t] = fetch_raw<S, V, VEC, true, XBC_CONST>(a, r0 + t, gx, cm, X0, sp);
+        for (int t = 0; t < RT; ++t)
+            raw[t] = __builtin_bit_cast(float4, fetch_raw<S, V, VEC, true, XBC_CONST>(a, r0 + t, gx, cm, X0, sp));
     } else {
         const RowSpan sp{need_lo, need_hi};
 #pragma unroll
-        for (int t = 0; t < RT; ++t) raw[t] = fetch_raw<S, V, VEC, false, XBC_CONST>(a, r0 + t, gx, cm, X0, sp);
+        for (int t = 0; t < RT; ++t)
+            raw[t] = __builtin_bit_cast(float4, fetch_raw<S, V, true, false, XBC_CONST>(a, r0 + t, gx, cm, X0, sp));
     }
 #pragma unroll
-    for (int t = 0; t < RT; ++t) dst[(r0 + t - o0) * 64 + lane] = __builtin_bit_cast(float4, raw[t]);
+    for (int t = 0; t < RT; ++t) dst[(r0 + t - o0) * 64 + lane] = raw[t];
 }
 
 }  // namespace march

@@ -7,7 +7,9 @@
 // halo of +0 the lane shifts bring 0 into lanes 0 and 63, which is the halo's value at every level:
 // then the first band starts at column 0 and stores its first H lanes too, and the last band ends at
 // the last column and stores its last H ("zero sides": a grid needs up to two bands fewer and its
-// side bands take no column checks).
+// side bands take no column checks).  Elsewhere, where V does not divide the columns of a grid of at least
+// 64 V, the last band is moved left so that the grid's side falls between two of its lanes, and so is any
+// other that would load beyond that side: no lane's vector straddles it (whole_lanes).
 //
 // Tasks that take the edge checks (the two outer bands unless the sides are zero, and the segments
 // within r * levels rows of the grid's top or bottom) spend about 1.5 more instructions per cell and
@@ -86,6 +88,9 @@ __host__ __device__ inline TaskRows task_rows(const TaskMap& m, int64_t task) {
     return r;
 }
 
+// Whether every lane of a layout holds V columns of the grid or none.
+__host__ __device__ constexpr bool whole_lanes(int64_t cols, int V) { return cols % V == 0 || cols >= 64 * int64_t(V); }
+
 struct BandCols {
     int64_t x0;  // first loaded column (negative: the band starts in the halo)
     int lo, hi;  // stored lanes [lo, hi); -1: the default [H, 64 - H)
@@ -109,6 +114,9 @@ __host__ __device__ inline BandCols band_cols(const TaskMap& m, int64_t band, in
             c.x0 = (band - 1) * outw + int64_t(V) * (64 - 2 * H);
             if (c.x0 > last) c.x0 = last;
         }
+    } else if (m.cols % V && m.cols >= 64 * int64_t(V)) {
+        const int64_t last = band == m.bands - 1 ? m.cols - int64_t(V) * (64 - H) : m.cols - 64 * int64_t(V);
+        if (c.x0 > last) c.x0 = last;  // (the overlap stores the same values)
     }
     return c;
 }
