@@ -347,14 +347,15 @@ int stencil_solve(st_plan* plan, const void* in, void* out, int64_t max_steps, i
 
 /* stencil_batch_create -- group n plans (FP32, constant weights, r <= 3; each may differ in
  * shape, radius, footprint and weights) with their own step counts into one batch.
- * Grids that fit a workgroup's LDS together with their halo and a ping-pong copy stay
- * resident in LDS for all their steps (one workgroup per grid).  The others are tiled
- * (128 x 64 tiles) with their plan's temporal depth (lowered if the batch tile would not fit
- * the LDS budget); pass p of all tiled grids is one multi-grid kernel, and the passes follow
+ * Small grids (a field of about 100 x 100 cells: it fits half a compute unit's LDS together with
+ * its halo and a ping-pong copy) stay resident for all their steps, one workgroup per grid, in
+ * registers or, when a side is longer than about 120 cells, in LDS.  The others run in passes of
+ * their plan's temporal depth (lowered to 16, or 13 at r = 3) on register tiles; a pass of all
+ * grids of a stencil class is one multi-grid kernel, and the passes follow
  * each other, so each tile's dependency on its neighbours' previous pass (the tiles' halo
  * swap, paper Sec. IV-B/C) is carried by the kernel boundary.  Steps == 0 is a copy.  The
  * plans must outlive the batch.  flags: ST_FLAG_GRAPH captures the whole run (resident
- * grids on a parallel branch) in one hipGraph replayed by every run.
+ * grids and each class on a parallel branch) in one hipGraph replayed by every run.
  * Errors: ST_EINVAL, ST_EUNSUPPORTED, ST_ENOMEM. */
 int stencil_batch_create(st_batch** out, int n, st_plan* const* plans, const int64_t* steps, uint32_t flags);
 
@@ -373,10 +374,10 @@ int stencil_batch_workspace_bytes(const st_batch* batch, size_t* bytes);
 int stencil_run_batched(st_batch* batch, const void* const* ins, void* const* outs, void* workspace,
                         size_t ws_bytes, void* stream);
 
-/* stencil_batch_set_class -- set the engine (0 = LDS tiles, 1 = marching) and pass depth of one
+/* stencil_batch_set_class -- set the engine (0 = tiles, 1 = marching) and pass depth of one
  * stencil class (shape 0 = star, 1 = box; radius 1..3) of the batch by hand; results are bitwise
- * the same for every choice.  Tiles: depth 1..16, further capped per grid by what its tile fits
- * in LDS.  Marching: depth up to 8 / 6 / 4 (star, r = 1 / 2 / 3) or 6 / 3 / 2 (box).  Errors: ST_EINVAL,
+ * the same for every choice.  Tiles: depth 1..16, capped at 13 for r = 3.  Marching (grids of less
+ * than 256 columns stay on tiles): depth up to 8 / 6 / 4 (star, r = 1 / 2 / 3) or 6 / 3 / 2 (box).  Errors: ST_EINVAL,
  * ST_EUNSUPPORTED (depth out of range). */
 int stencil_batch_set_class(st_batch* batch, int shape, int radius, int engine, int depth);
 
@@ -391,13 +392,13 @@ int stencil_batch_set_segment(st_batch* batch, int shape, int radius, int64_t mi
 int stencil_batch_get_segment(const st_batch* batch, int shape, int radius, int64_t* rows);
 
 /* stencil_batch_autotune -- pick, for each stencil class (shape, radius) of the grids that are
- * not LDS-resident, the engine and the depth of its passes: LDS tiles of 128 x 64 (one multi-grid
- * launch per pass for all tiled classes) with the depth capped at 1, 2, 3, 4, 6, 8, 12 or 16
- * (and by what each grid's tile fits in LDS), or marching (one wavefront per column band, four
- * columns per lane, any width and alignment; one chain of launches per class, the classes on
- * parallel branches of the graph) with every depth it offers (up to 8 / 6 / 4 levels for star
- * r = 1 / 2 / 3, 6 / 3 / 2 for box), each with the default segments and with segments 2, 4 and 8
- * times as long (stencil_batch_set_segment).  Coordinate descent: each
+ * not resident, the engine and the depth of its passes: register tiles (one multi-grid launch
+ * per pass) with the depth capped at 1, 2, 3, 4, 6, 8, 12 or 16, or marching (one wavefront per
+ * column band, four columns per lane, any width and alignment; grids of less than 256 columns
+ * stay on tiles) with every depth it offers (up to 8 / 6 / 4 levels for star r = 1 / 2 / 3,
+ * 6 / 3 / 2 for box), each with the default segments and with those that make one, two, three
+ * or four tasks per SIMD (stencil_batch_set_segment).  Each class is a chain of launches, the
+ * classes on parallel branches of the graph.  Coordinate descent: each
  * class in turn, every candidate timed on the whole batch run twice on the caller's buffers (outs
  * are overwritten; results are bitwise those of any other choice).  Writes the chosen depth and
  * engine (0 = tiles, 1 = marching) per class to tb_out[6] / engine_out[6] when non-NULL (star

@@ -1,20 +1,23 @@
 // Batched sweep: many independent grids of uneven size and mixed stencil shape, run by one
 // hipGraph launch.
 //
-// Small grids that fit a workgroup's LDS (with their halo and a ping-pong copy) are resident:
-// one workgroup keeps the grid in LDS for all of its steps, so it never round-trips through HBM.
-// The other grids are tiled; pass p of every tiled grid (tb steps each, as in the single-grid
-// sweep) is one multi-grid kernel whose workgroups each take one (grid, tile) of that pass, so a
-// pass of all grids costs one launch instead of one per grid.  Passes follow each other inside
-// the graph, so the dependency of a tile on its neighbours' previous pass (the halo exchange of
-// the paper's tiles, Sec. IV-B/C) is carried by the kernel boundary; the resident grids run on a
-// parallel branch of the same graph.
+// Small grids are resident: one workgroup keeps the grid for all of its steps, in registers where it
+// fits a 128 x 128 tile with its halo (batched_block.hip), else in LDS, so it never round-trips through
+// HBM.  The other grids run in passes: pass p of every grid of a stencil class is one multi-grid kernel
+// whose workgroups each take one (grid, tile) of that pass on register tiles, or whose wavefronts each
+// take one (grid, band, segment), so a pass of a class costs one launch instead of one per grid.  Passes
+// follow each other inside the graph, so the dependency of a tile on its neighbours' previous pass (the
+// halo exchange of the paper's tiles, Sec. IV-B/C) is carried by the kernel boundary; the classes and the
+// resident grids run on parallel branches of the same graph.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <mutex>
 #include <new>
 #include <vector>
 
+#include "batched.h"
+#include "block_body.h"
 #include "internal.h"
 #include "march_body.h"
 #include "sweep_body.h"
@@ -23,53 +26,8 @@ namespace st {
 
 namespace {
 
-struct BatchDesc {
-    const float* in;
-    float* out;
-    float* ws;
-    int64_t rows, cols;
-    int64_t tiles_x, tiles_y;  // tiled engine: tiles; marching engine: bands and segments
-    int64_t seg;               // marching engine: output rows per task
-    int r, shape, tb, steps, passes, resident;
-    int vec;  // marching engine: rows 16-byte aligned in every buffer (cols % 4 == 0): vector accesses
-    float b;
-    float w[MAXK];
-};
-
-struct PassArgs {
-    const BatchDesc* desc;
-    const int* order;            // tiled grids by pass count, descending
-    const int64_t* tile_prefix;  // [n_tiled + 1] tile offsets in that order
-    int n_active;                // grids with more than p passes (a prefix of the order)
-    int p;                       // pass index
-};
-
-// One tile shape for every tiled grid of a batch keeps the kernel's register use at the level of a
-// single sweep body (each extra shape multiplies the inlined code).
-constexpr int kTX = 128, kTY = 64, kRS = 8;
-
-template <int R, int SH>
-__device__ __forceinline__ void run_tile(const BatchDesc& d, const float* src, float* dst, int levels, int64_t y0,
-                                         int64_t x0, float* lds) {
-    tile_body<ST_F32, R, SH, kTX, kTY, kRS>(src, dst, d.rows, d.cols, d.b, levels, y0, x0, d.w, lds);
-}
-
-__device__ __forceinline__ void dispatch_tile(const BatchDesc& d, const float* src, float* dst, int levels, int64_t y0,
-                                              int64_t x0, float* lds) {
-    if (d.shape == SHAPE_BOX) {
-        switch (d.r) {
-            case 1: run_tile<1, SHAPE_BOX>(d, src, dst, levels, y0, x0, lds); break;
-            case 2: run_tile<2, SHAPE_BOX>(d, src, dst, levels, y0, x0, lds); break;
-            default: run_tile<3, SHAPE_BOX>(d, src, dst, levels, y0, x0, lds); break;
-        }
-    } else {
-        switch (d.r) {
-            case 1: run_tile<1, SHAPE_STAR>(d, src, dst, levels, y0, x0, lds); break;
-            case 2: run_tile<2, SHAPE_STAR>(d, src, dst, levels, y0, x0, lds); break;
-            default: run_tile<3, SHAPE_STAR>(d, src, dst, levels, y0, x0, lds); break;
-        }
-    }
-}
+constexpr int SIMDS = 1024;  // 256 compute units of four
+constexpr int kRS = 8;  // rows per thread of the LDS-resident kernel
 
 __device__ __forceinline__ void dispatch_resident(const BatchDesc& d, float* lds) {
     const int rows = int(d.rows), cols = int(d.cols);
@@ -88,33 +46,6 @@ __device__ __forceinline__ void dispatch_resident(const BatchDesc& d, float* lds
     }
 }
 
-// largest index i in [0, n) with a[i] <= x (a ascending, a[0] <= x)
-__device__ __forceinline__ int upper_index(const int64_t* a, int n, int64_t x) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (a[mid] <= x) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// One pass level of all tiled grids: workgroup o -> (grid, tile) through the tile prefix sums of
-// the grids still active at this pass (a prefix of the queue order).
-__global__ __launch_bounds__(NT) void batched_pass(PassArgs a) {
-    extern __shared__ float4 lds4[];
-    float* lds = reinterpret_cast<float*>(lds4);
-    const int64_t o = blockIdx.x;
-    const int k = upper_index(a.tile_prefix, a.n_active + 1, o);
-    const BatchDesc& d = a.desc[a.order[k]];
-    const int64_t t = o - a.tile_prefix[k];
-    const int64_t ty = t / d.tiles_x, tx = t - ty * d.tiles_x;
-    const int p = a.p, P = d.passes;
-    const float* src = p == 0 ? d.in : (((P - p) % 2 == 0) ? d.out : d.ws);  // written by pass p-1
-    float* dst = ((P - 1 - p) % 2 == 0) ? d.out : d.ws;
-    const int levels = min(d.tb, d.steps - p * d.tb);
-    dispatch_tile(d, src, dst, levels, ty * kTY, tx * kTX, lds);
-}
-
 // The LDS-resident grids: one workgroup per grid for all of its steps.
 __global__ __launch_bounds__(NT) void batched_resident(const BatchDesc* desc, const int* res) {
     extern __shared__ float4 lds4[];
@@ -123,8 +54,8 @@ __global__ __launch_bounds__(NT) void batched_resident(const BatchDesc* desc, co
 
 // Marching engine: one launch runs `levels` (the template TB) levels of pass p for the grids
 // order[s0 .. s0+n) of one stencil class; wavefront task -> (grid, band, segment) through the class's
-// task prefix sums.  Four columns per lane: one vector access per lane and row for grids whose rows
-// are 16-byte aligned in every buffer, four element accesses otherwise (any width and alignment).
+// task prefix sums.  Four columns per lane, one vector access per lane and row at any alignment; grids
+// narrower than a band run on register tiles.
 struct MarchPassArgs {
     const BatchDesc* desc;
     const int* order;            // the class's grids, ordered by passes then last-pass depth, descending
@@ -134,14 +65,15 @@ struct MarchPassArgs {
 };
 
 constexpr int MW = 4;  // wavefronts per workgroup of the marching engine
-constexpr int MV = 4;  // columns per lane of the marching engine (vector or element accesses per grid)
+constexpr int MV = 4;  // columns per lane of the marching engine
 
 // LDS of a batched marching workgroup: the input rows that the two wavefronts of a pair share (2 r tb
 // rows of 64 lanes x 16 bytes per pair).
 constexpr size_t march_share_bytes(int r, int tb) { return size_t(MW / 2) * 2 * r * tb * 64 * sizeof(float4); }
 
+// (r = 3 at its deepest is held to the 168 registers that let three wavefronts share a SIMD)
 template <int R, int SH, int TB>
-__global__ __launch_bounds__(64 * MW) void batched_march(MarchPassArgs a) {
+__global__ __launch_bounds__(64 * MW) __attribute__((amdgpu_waves_per_eu(R == 3 ? 3 : 1))) void batched_march(MarchPassArgs a) {
     extern __shared__ float4 shared_rows[];
     const int lane = int(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -176,19 +108,18 @@ __global__ __launch_bounds__(64 * MW) void batched_march(MarchPassArgs a) {
     const float* src = p == 0 ? d.in : (((P - p) % 2 == 0) ? d.out : d.ws);  // written by pass p-1
     float* dst = ((P - 1 - p) % 2 == 0) ? d.out : d.ws;
     const march::MarchView v{src, dst, d.rows, d.cols, d.b, march::BC_CONST, nullptr};
-    const int64_t X0 = band * (MV * (64 - 2 * H)) - MV * H;
+    const march::BandCols bc = march::band_cols(d.cols, d.tiles_x, d.zero_sides, band, MV, H);
+    const int64_t X0 = bc.x0;
     float4* mine = shared_rows + (wave >> 1) * (2 * RT * 64);
     if (paired) {  // each stages the rows on its own side of the boundary
-        if (d.vec) march::stage_rows<ST_F32, R, MV, TB, true>(v, lane, y0, y1, X0, up ? yb - RT : yb, yb - RT, mine);
-        else march::stage_rows<ST_F32, R, MV, TB, false>(v, lane, y0, y1, X0, up ? yb - RT : yb, yb - RT, mine);
+        march::stage_rows<ST_F32, R, MV, TB>(v, lane, y0, y1, X0, up ? yb - RT : yb, yb - RT, mine);
     }
     __syncthreads();  // every wavefront of the workgroup reaches it once
     if (!active) return;
     const march::SharedRows sh{paired ? mine : nullptr, yb - RT, yb + RT};
     // input rows in flight: one ring length, except box r >= 3 with several levels (registers)
     constexpr int D = SH == SHAPE_STAR || R <= 2 || TB == 1 ? 2 * R + 1 : 0;
-    if (d.vec) march::march_task_dir<ST_F32, R, MV, SH, TB, D, true>(v, d.w, lane, y0, y1, X0, up, sh);
-    else march::march_task_dir<ST_F32, R, MV, SH, TB, D, false>(v, d.w, lane, y0, y1, X0, up, sh);
+    march::march_task_dir<ST_F32, R, MV, SH, TB, D>(v, d.w, lane, y0, y1, X0, up, sh, bc.lo, bc.hi);
 }
 
 using MarchPassFn = void (*)(MarchPassArgs);
@@ -228,30 +159,29 @@ struct st_batch {
     int n;
     uint32_t flags;
     std::vector<BatchDesc> desc;
-    std::vector<int64_t> tile_prefix;  // over `order`
-    std::vector<int> order;            // tiled grids by pass count, descending
-    std::vector<int> res;              // LDS-resident grids
+    std::vector<int> res;              // one-workgroup grids: LDS-resident, then each class's on register tiles
+    int n_lds;                         // the LDS-resident ones
+    int whole_first[6], whole_n[6];    // per class: its grids on register tiles in `res`
     std::vector<int> zero_steps;       // grids with steps == 0 (copied, not computed)
-    std::vector<int> active;           // active[p]: tiled grids with more than p passes
     std::vector<int> tiled;            // grids that are neither resident nor zero-step, in input order
-    std::vector<int> tb_max;           // per grid: deepest pass the batch tile's LDS budget allows
-    int max_passes;
-    // per stencil class (slot = shape * 3 + r - 1): engine (0 = LDS tiles, 1 = marching) and depth
+    std::vector<int> tb_max, plan_tb;  // per grid: deepest pass on register tiles, and its plan's
+    // per stencil class (slot = shape * 3 + r - 1): engine (0 = register tiles, 1 = marching) and depth
     int engine[6], depth[6];
     int64_t seg_min[6];  // marching: least output rows per task (0: the tasks about fill the device once)
     struct MLaunch {
         int s0, n, p, levels;
         int64_t tasks;
     };
-    struct MClass {
-        int64_t seg = 0;               // output rows per task (the longest a grid's segment may be)
-        std::vector<int> order;        // the class's marching grids by passes, then last-pass depth
-        std::vector<int64_t> prefix;   // task prefix sums over `order`
+    struct Passes {
+        int64_t seg = 0;               // marching: output rows per task (the longest a grid's segment may be)
+        int def = 0;                   // register tiles: which of block::kDefs
+        std::vector<int> order;        // the class's grids by passes, then last-pass depth
+        std::vector<int64_t> prefix;   // task (tile) prefix sums over `order`
         std::vector<MLaunch> launches; // in pass order
-    } mclass[6];
-    size_t off_desc, off_tprefix, off_order, off_res, off_morder[6], off_mprefix[6], off_fields, ws_bytes;
+    } march[6], tile[6];               // per class, its grids on either engine
+    size_t off_desc, off_res, off_order[12], off_prefix[12], off_fields, ws_bytes;  // tables: march, then tile
     std::vector<size_t> field_off;     // per grid: workspace offset of its ping-pong field (0 = none)
-    size_t lds_pass, lds_res;
+    size_t lds_res;
     // staging + graph
     void* pinned;
     size_t pinned_bytes;
@@ -274,6 +204,12 @@ size_t batch_lds_budget() { return std::min<size_t>(80 * 1024, lds_limit()); }
 
 static int class_slot(const BatchDesc& d) { return d.shape * 3 + d.r - 1; }
 
+// Whether a grid and the halo around it fit the tile of batched_whole.
+static bool fits_tile(const BatchDesc& d) {
+    const block::Def& t = block::kDefs[block::kTall];
+    return d.rows + 2 * d.r <= t.nw * t.rw && d.cols + block::margin_cols(d.r, 1, t.v) + d.r <= 64 * t.v;
+}
+
 // Marching engine: output rows per task for a class, so that its tasks about fill the device once
 // (`waves`: the wavefronts of the class's kernel the device holds at once).
 static int64_t march_segment(int64_t band_rows, int64_t waves) {
@@ -293,48 +229,82 @@ static int64_t march_waves(int shape, int r, int tb) {
     return int64_t(blocks) * MW;
 }
 
-// Pass structure from each class's engine and depth.  Tiled engine: passes per grid, the queue
-// order (by pass count, descending, so that the grids still active at pass p are a prefix), the tile
-// prefix sums over that order and the LDS of the deepest pass.  Marching engine, per class: bands
-// and segments per grid, the order by (passes, depth of the last pass) descending, the task prefix
-// sums, and the launches -- at pass p the full-depth grids are a prefix of the order and the grids
-// finishing with a shallower pass follow in groups of equal depth.
+// Depth of a grid's deepest pass on register tiles: its steps spread evenly over the passes.
+static int even_depth(const BatchDesc& d) { return (d.steps + d.passes - 1) / d.passes; }
+
+// Register tile of a class: the least estimated time, from the instructions that a wavefront issues per level
+// (its cells' taps, a few per row, and the exchange), over the SIMDs the device has, plus one workgroup's own
+// time, which is what small batches wait for.  A tile must keep a quarter of its sides as block::cover asks.
+static int class_tile(const st_batch* B, const std::vector<int>& grids) {
+    int best = block::kTall;
+    double best_t = HUGE_VAL;
+    for (int def = 0; def <= block::kTall; ++def) {
+        const block::Def& t = block::kDefs[def];
+        double work = 0.0;
+        int steps = 0;
+        bool fits = true;
+        double level = 0.0;
+        for (int g : grids) {
+            const BatchDesc& d = B->desc[g];
+            const block::Cover c = block::cover(def, d.r, even_depth(d), d.rows, d.cols);
+            fits = fits && c.def == def;
+            const int taps = d.shape == SHAPE_BOX ? (2 * d.r + 1) * (2 * d.r + 1) : 4 * d.r + 1;
+            level = t.rw * t.v * (taps + 1.0) + 6.0 * t.rw + 40.0;
+            work += double(c.tiles) * t.nw * level * d.steps;
+            steps = std::max(steps, d.steps);
+        }
+        const double time = work / SIMDS + level * steps * t.nw / 4.0;
+        if (fits && time < best_t) {
+            best_t = time;
+            best = def;
+        }
+    }
+    return best;
+}
+
+// Pass structure from each class's engine and depth: the order by (passes, depth of the last pass)
+// descending, the task or tile prefix sums, and the launches.  Register tiles: at pass p the grids with
+// more than p passes are a prefix of the order, one launch.  Marching: bands and segments per grid; at pass
+// p the full-depth grids are a prefix of the order and the grids finishing with a shallower pass follow in
+// groups of equal depth.
+// On the marching engine, grids narrower than a band stay on register tiles: a band would leave lanes idle.
 static void build_passes(st_batch* B) {
-    std::vector<int> order;
-    size_t lds = 0;
-    for (int c = 0; c < 6; ++c) B->mclass[c] = st_batch::MClass();
+    for (int c = 0; c < 6; ++c) B->march[c] = B->tile[c] = st_batch::Passes();
     for (int g : B->tiled) {
         BatchDesc& d = B->desc[g];
         const int c = class_slot(d);
-        if (B->engine[c] == 0) {
-            d.tb = std::min(B->depth[c] > 0 ? B->depth[c] : d.tb, B->tb_max[g]);
-            d.tiles_x = (d.cols + kTX - 1) / kTX;
-            d.tiles_y = (d.rows + kTY - 1) / kTY;
-            d.passes = (d.steps + d.tb - 1) / d.tb;
-            lds = std::max(lds, tiled_lds_bytes(d.r, d.tb, kTX, kTY));
-            order.push_back(g);
-        } else {
-            d.tb = B->depth[c];
-            d.passes = (d.steps + d.tb - 1) / d.tb;
-            const int64_t band_w = MV * (64 - 2 * march::halo_lanes(d.r, d.tb, MV));
-            d.tiles_x = (d.cols + band_w - 1) / band_w;  // bands
-            B->mclass[c].order.push_back(g);
+        const bool marches = B->engine[c] == 1 && d.cols >= 64 * MV;
+        d.tb = marches ? B->depth[c]
+                       : std::min(B->engine[c] == 1 ? 12 / d.r : B->depth[c] > 0 ? B->depth[c] : B->plan_tb[g], B->tb_max[g]);
+        d.passes = (d.steps + d.tb - 1) / d.tb;
+        if (marches) {
+            const float zero = 0.0f;
+            d.zero_sides = std::memcmp(&d.b, &zero, sizeof zero) == 0 && d.cols >= 2 * 64 * MV;
+            d.tiles_x = march::band_count(d.cols, MV, march::halo_lanes(d.r, d.tb, MV), d.zero_sides);
+        }
+        (marches ? B->march : B->tile)[c].order.push_back(g);
+    }
+    for (int c = 0; c < 6; ++c) {
+        st_batch::Passes& M = B->tile[c];
+        if (M.order.empty()) continue;
+        std::stable_sort(M.order.begin(), M.order.end(), [&](int a, int b) { return B->desc[a].passes > B->desc[b].passes; });
+        M.def = class_tile(B, M.order);
+        M.prefix.assign(1, 0);
+        for (int g : M.order) {
+            BatchDesc& d = B->desc[g];
+            const block::Cover t = block::cover(M.def, d.r, even_depth(d), d.rows, d.cols);
+            d.tiles_x = t.tiles_x;
+            d.tiles_y = t.tiles / t.tiles_x;
+            M.prefix.push_back(M.prefix.back() + t.tiles);
+        }
+        int n = int(M.order.size());
+        for (int p = 0; p < B->desc[M.order[0]].passes; ++p) {
+            while (B->desc[M.order[n - 1]].passes <= p) --n;
+            M.launches.push_back({0, n, p, 0, M.prefix[n]});
         }
     }
-    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B->desc[a].passes > B->desc[b].passes; });
-    B->order = order;
-    B->tile_prefix.assign(1, 0);
-    for (int g : order) B->tile_prefix.push_back(B->tile_prefix.back() + B->desc[g].tiles_x * B->desc[g].tiles_y);
-    B->max_passes = order.empty() ? 0 : B->desc[order[0]].passes;
-    B->active.clear();
-    for (int p = 0; p < B->max_passes; ++p) {
-        int a = 0;
-        while (a < int(order.size()) && B->desc[order[a]].passes > p) ++a;
-        B->active.push_back(a);
-    }
-    B->lds_pass = lds;
     for (int c = 0; c < 6; ++c) {
-        st_batch::MClass& M = B->mclass[c];
+        st_batch::Passes& M = B->march[c];
         if (M.order.empty()) continue;
         const int tb = B->depth[c];
         auto last_depth = [&](int g) { return B->desc[g].steps - (B->desc[g].passes - 1) * tb; };
@@ -390,7 +360,8 @@ extern "C" int stencil_batch_create(st_batch** out, int n, st_plan* const* plans
     B->desc.resize(n);
     B->field_off.assign(n, 0);
     B->tb_max.assign(n, 0);
-    std::vector<int> tiled;
+    B->plan_tb.assign(n, 0);
+    std::vector<int> tiled, whole[6];
     size_t lds_res = 0;
     for (int g = 0; g < n; ++g) {
         const st_plan* p = plans[g];
@@ -420,23 +391,30 @@ extern "C" int stencil_batch_create(st_batch** out, int n, st_plan* const* plans
             d.resident = 1;
             d.passes = 1;
             d.tb = d.steps;
-            lds_res = std::max(lds_res, rl);
-            B->res.push_back(g);
+            if (fits_tile(d)) {
+                whole[class_slot(d)].push_back(g);
+            } else {
+                lds_res = std::max(lds_res, rl);
+                B->res.push_back(g);
+            }
             continue;
         }
-        // deepest pass the batch tile allows; the plan's depth, capped by it, is the starting point
-        int tbm = 16;
-        while (tbm > 1 && tiled_lds_bytes(p->radius, tbm, kTX, kTY) > batch_lds_budget()) --tbm;
-        B->tb_max[g] = tbm;
-        d.tb = std::min(std::max(1, p->tb), tbm);
-        d.tiles_x = (p->cols + kTX - 1) / kTX;
-        d.tiles_y = (p->rows + kTY - 1) / kTY;
+        // deepest pass that leaves a third of the tallest tile; the plan's depth, capped by it, is the
+        // starting point
+        B->tb_max[g] = std::min(16, 39 / p->radius);
+        B->plan_tb[g] = std::max(1, p->tb);
         tiled.push_back(g);
     }
     B->tiled = tiled;
+    B->n_lds = int(B->res.size());
+    for (int c = 0; c < 6; ++c) {
+        B->whole_first[c] = int(B->res.size());
+        B->whole_n[c] = int(whole[c].size());
+        B->res.insert(B->res.end(), whole[c].begin(), whole[c].end());
+    }
     for (int c = 0; c < 6; ++c) {
         B->engine[c] = 0;
-        B->depth[c] = 0;  // 0: each grid keeps its plan's depth (capped by the tile's LDS)
+        B->depth[c] = 0;  // 0: each grid keeps its plan's depth (capped)
         B->seg_min[c] = 0;
     }
     build_passes(B);
@@ -445,17 +423,14 @@ extern "C" int stencil_batch_create(st_batch** out, int n, st_plan* const* plans
     size_t off = 0;
     B->off_desc = off;
     off = align256(off + size_t(n) * sizeof(BatchDesc));
-    B->off_tprefix = off;
-    off = align256(off + (tiled.size() + 1) * sizeof(int64_t));
-    B->off_order = off;
-    off = align256(off + std::max<size_t>(tiled.size(), 1) * sizeof(int));
     B->off_res = off;
     off = align256(off + std::max<size_t>(B->res.size(), 1) * sizeof(int));
-    for (int c = 0; c < 6; ++c) {  // room for every tiled grid in any class's marching tables
-        B->off_morder[c] = off;
-        off = align256(off + std::max<size_t>(tiled.size(), 1) * sizeof(int));
-        B->off_mprefix[c] = off;
-        off = align256(off + (tiled.size() + 1) * sizeof(int64_t));
+    for (int t = 0; t < 12; ++t) {  // room for every grid of the class on either engine
+        const size_t m = size_t(std::count_if(tiled.begin(), tiled.end(), [&](int g) { return class_slot(B->desc[g]) == t % 6; }));
+        B->off_order[t] = off;
+        off = align256(off + std::max<size_t>(m, 1) * sizeof(int));
+        B->off_prefix[t] = off;
+        off = align256(off + (m + 1) * sizeof(int64_t));
     }
     B->off_fields = off;
     for (int g : tiled) {
@@ -483,6 +458,11 @@ extern "C" int stencil_batch_workspace_bytes(const st_batch* batch, size_t* byte
     return ST_OK;
 }
 
+static void drop_exec(st_batch* B) {
+    if (B->exec) (void)hipGraphExecDestroy(B->exec);
+    B->exec = nullptr;
+}
+
 extern "C" int stencil_batch_destroy(st_batch* batch) {
     if (!batch) return ST_OK;
     if (batch->staged) {
@@ -490,89 +470,118 @@ extern "C" int stencil_batch_destroy(st_batch* batch) {
         (void)hipEventDestroy(batch->staged);
     }
     if (batch->pinned) (void)hipHostFree(batch->pinned);
-    if (batch->exec) (void)hipGraphExecDestroy(batch->exec);
+    drop_exec(batch);
     delete batch;
     return ST_OK;
 }
 
-// The marching launches of class c, in pass order, on stream `s`.
-static int enqueue_march_class(st_batch* B, int c, char* ws, hipStream_t s) {
-    const st_batch::MClass& M = B->mclass[c];
+// The launches of table t (march[0 .. 5], then tile[0 .. 5]), in pass order, on stream `s`.
+static const st_batch::Passes& passes_of(const st_batch* B, int t) { return t < 6 ? B->march[t] : B->tile[t - 6]; }
+static int enqueue_passes(st_batch* B, int t, char* ws, hipStream_t s) {
+    const st_batch::Passes& M = passes_of(B, t);
     const BatchDesc& d0 = B->desc[M.order[0]];
+    const BatchDesc* desc = reinterpret_cast<const BatchDesc*>(ws + B->off_desc);
+    const int* order = reinterpret_cast<const int*>(ws + B->off_order[t]);
+    const int64_t* prefix = reinterpret_cast<const int64_t*>(ws + B->off_prefix[t]);
     for (const st_batch::MLaunch& L : M.launches) {
+        clear_stale_error();
+        if (t >= 6) {
+            if (L.tasks >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
+            const block::Def& tile = block::kDefs[M.def];
+            BlockPassFn fn = batched_block_lookup(d0.shape, d0.r, M.def);
+            const size_t lds = block::lds_floats(d0.r, tile.v, tile.rw, tile.nw) * sizeof(float);
+            if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
+            hipLaunchKernelGGL(fn, dim3(unsigned(L.tasks)), dim3(64 * tile.nw), lds, s, BlockPassArgs{desc, order, prefix, L.n, L.p});
+            ST_LAUNCH_CHECK("batched_block");
+            continue;
+        }
         MarchPassFn fn = batched_march_lookup(d0.shape, d0.r, L.levels);
         if (!fn) return fail(ST_EUNSUPPORTED, "no batched marching kernel for this class/depth");
         MarchPassArgs a;
-        a.desc = reinterpret_cast<const BatchDesc*>(ws + B->off_desc);
-        a.order = reinterpret_cast<const int*>(ws + B->off_morder[c]);
-        a.task_prefix = reinterpret_cast<const int64_t*>(ws + B->off_mprefix[c]);
+        a.desc = desc;
+        a.order = order;
+        a.task_prefix = prefix;
         a.s0 = L.s0;
         a.n = L.n;
         a.p = L.p;
         const int64_t blocks = (L.tasks + MW - 1) / MW;
-        clear_stale_error();
         hipLaunchKernelGGL(fn, dim3(unsigned(blocks)), dim3(64 * MW), march_share_bytes(d0.r, L.levels), s, a);
         ST_LAUNCH_CHECK("batched_march");
     }
     return ST_OK;
 }
 
-// Enqueue the batch's kernels: the resident grids on `side`, the marching classes on `mside[c]`
-// (each joined back into `s` at the end when it differs from s), the pass levels of the tiled grids
-// on `s`.
-static int enqueue_batch(st_batch* B, char* ws, hipStream_t s, hipStream_t side, hipEvent_t fork, hipEvent_t join,
-                         const hipStream_t* mside, const hipEvent_t* mjoin) {
-    const BatchDesc* desc = reinterpret_cast<const BatchDesc*>(ws + B->off_desc);
-    const bool branch = side != s;
-    if (branch) {
-        ST_HIP_CHECK(hipEventRecord(fork, s));
-        for (int c = 0; c < 6; ++c)
-            if (!B->mclass[c].order.empty()) ST_HIP_CHECK(hipStreamWaitEvent(mside[c], fork, 0));
-    }
-    for (int c = 0; c < 6; ++c) {
-        if (B->mclass[c].order.empty()) continue;
-        if (int rc = enqueue_march_class(B, c, ws, branch ? mside[c] : s)) return rc;
-        if (branch) {
-            ST_HIP_CHECK(hipEventRecord(mjoin[c], mside[c]));
-        }
-    }
-    if (!B->res.empty()) {
-        if (int rc = prepare_lds(reinterpret_cast<const void*>(batched_resident), B->lds_res)) return rc;
-        if (branch) {
-            ST_HIP_CHECK(hipStreamWaitEvent(side, fork, 0));
-        }
-        clear_stale_error();
-        hipLaunchKernelGGL(batched_resident, dim3(unsigned(B->res.size())), dim3(NT), B->lds_res, side, desc,
-                           reinterpret_cast<const int*>(ws + B->off_res));
-        ST_LAUNCH_CHECK("batched_resident");
-    }
-    if (B->max_passes > 0) {
-        if (int rc = prepare_lds(reinterpret_cast<const void*>(batched_pass), B->lds_pass)) return rc;
-        for (int p = 0; p < B->max_passes; ++p) {
-            PassArgs a;
-            a.desc = desc;
-            a.order = reinterpret_cast<const int*>(ws + B->off_order);
-            a.tile_prefix = reinterpret_cast<const int64_t*>(ws + B->off_tprefix);
-            a.n_active = B->active[p];
-            a.p = p;
-            const int64_t blocks = B->tile_prefix[B->active[p]];
-            clear_stale_error();
-            hipLaunchKernelGGL(batched_pass, dim3(unsigned(blocks)), dim3(NT), B->lds_pass, s, a);
-            ST_LAUNCH_CHECK("batched_pass");
-        }
-    }
-    if (branch && !B->res.empty()) {
-        ST_HIP_CHECK(hipEventRecord(join, side));
-        ST_HIP_CHECK(hipStreamWaitEvent(s, join, 0));
-    }
-    if (branch)
-        for (int c = 0; c < 6; ++c)
-            if (!B->mclass[c].order.empty()) ST_HIP_CHECK(hipStreamWaitEvent(s, mjoin[c], 0));
+// Class c's grids that one workgroup each keeps in registers.
+static int enqueue_whole(st_batch* B, int c, char* ws, hipStream_t s) {
+    const BatchDesc& d0 = B->desc[B->res[size_t(B->whole_first[c])]];
+    const block::Def& t = block::kDefs[block::kTall];
+    BlockPassFn fn = batched_whole_lookup(d0.shape, d0.r);
+    const size_t lds = block::lds_floats(d0.r, t.v, t.rw, t.nw) * sizeof(float);
+    if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
+    clear_stale_error();
+    hipLaunchKernelGGL(fn, dim3(unsigned(B->whole_n[c])), dim3(64 * t.nw), lds, s,
+                       BlockPassArgs{reinterpret_cast<const BatchDesc*>(ws + B->off_desc),
+                                     reinterpret_cast<const int*>(ws + B->off_res) + B->whole_first[c], nullptr, B->whole_n[c], -1});
+    ST_LAUNCH_CHECK("batched_whole");
     return ST_OK;
 }
 
-extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* const* outs, void* workspace,
-                                   size_t ws_bytes, void* stream) {
+// The branches of a captured batch: the LDS-resident grids, each class's one-workgroup grids, and each
+// class's passes on either engine.  Each has a stream and an event that joins it.
+constexpr int BRANCHES = 19;
+static bool branch_used(const st_batch* B, int i) {
+    if (i == 0) return B->n_lds > 0;
+    return i <= 6 ? B->whole_n[i - 1] > 0 : !passes_of(B, i - 7).order.empty();
+}
+static int enqueue_branch(st_batch* B, int i, char* ws, hipStream_t s) {
+    if (i > 6) return enqueue_passes(B, i - 7, ws, s);
+    if (i > 0) return enqueue_whole(B, i - 1, ws, s);
+    if (int rc = prepare_lds(reinterpret_cast<const void*>(batched_resident), B->lds_res)) return rc;
+    clear_stale_error();
+    hipLaunchKernelGGL(batched_resident, dim3(unsigned(B->n_lds)), dim3(NT), B->lds_res, s,
+                       reinterpret_cast<const BatchDesc*>(ws + B->off_desc), reinterpret_cast<const int*>(ws + B->off_res));
+    ST_LAUNCH_CHECK("batched_resident");
+    return ST_OK;
+}
+
+// The branches' streams and events.
+struct Branches {
+    hipStream_t side[BRANCHES] = {};
+    hipEvent_t fork = nullptr, join[BRANCHES] = {};
+    bool create(const st_batch* B, bool all) {
+        bool ok = hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
+        for (int i = 0; i < BRANCHES && ok; ++i)
+            ok = (!all && !branch_used(B, i)) || (hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking) == hipSuccess &&
+                                                  hipEventCreateWithFlags(&join[i], hipEventDisableTiming) == hipSuccess);
+        return ok;
+    }
+    ~Branches() {
+        if (fork) (void)hipEventDestroy(fork);
+        for (int i = 0; i < BRANCHES; ++i) {
+            if (join[i]) (void)hipEventDestroy(join[i]);
+            if (side[i]) (void)hipStreamDestroy(side[i]);
+        }
+    }
+};
+
+// Enqueue the batch's kernels on `s`, or each branch on its own stream forked from and joined into `s`.
+static int enqueue_batch(st_batch* B, char* ws, hipStream_t s, const Branches* br) {
+    if (br) ST_HIP_CHECK(hipEventRecord(br->fork, s));
+    for (int i = 0; i < BRANCHES; ++i) {
+        if (!branch_used(B, i)) continue;
+        if (br) ST_HIP_CHECK(hipStreamWaitEvent(br->side[i], br->fork, 0));
+        if (int rc = enqueue_branch(B, i, ws, br ? br->side[i] : s)) return rc;
+        if (br) ST_HIP_CHECK(hipEventRecord(br->join[i], br->side[i]));
+    }
+    if (br)
+        for (int i = 0; i < BRANCHES; ++i)
+            if (branch_used(B, i)) ST_HIP_CHECK(hipStreamWaitEvent(s, br->join[i], 0));
+    return ST_OK;
+}
+
+// stencil_run_batched; `br`: on these streams, whatever the batch's flags say (the autotuner).
+static int run_batched(st_batch* B, const void* const* ins, void* const* outs, void* workspace, size_t ws_bytes,
+                       void* stream, const Branches* br) {
     if (!B || !ins || !outs) return fail(ST_EINVAL, "NULL argument");
     if (!workspace || ws_bytes < B->ws_bytes) return fail(ST_ENOWS, "workspace too small");
     for (int g = 0; g < B->n; ++g) {
@@ -600,19 +609,14 @@ extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* co
             d.in = static_cast<const float*>(ins[g]);
             d.out = static_cast<float*>(outs[g]);
             d.ws = B->field_off[g] ? reinterpret_cast<float*>(ws + B->field_off[g]) : nullptr;
-            auto a16 = [](const void* q) { return reinterpret_cast<uintptr_t>(q) % 16 == 0; };
-            d.vec = d.cols % MV == 0 && a16(d.in) && a16(d.out) && (!d.ws || a16(d.ws));
             std::memcpy(h + g * sizeof(BatchDesc), &d, sizeof(d));
         }
-        std::memcpy(h + (B->off_tprefix - B->off_desc), B->tile_prefix.data(), B->tile_prefix.size() * sizeof(int64_t));
-        if (!B->order.empty())
-            std::memcpy(h + (B->off_order - B->off_desc), B->order.data(), B->order.size() * sizeof(int));
         if (!B->res.empty()) std::memcpy(h + (B->off_res - B->off_desc), B->res.data(), B->res.size() * sizeof(int));
-        for (int c = 0; c < 6; ++c) {
-            const st_batch::MClass& M = B->mclass[c];
+        for (int t = 0; t < 12; ++t) {
+            const st_batch::Passes& M = passes_of(B, t);
             if (M.order.empty()) continue;
-            std::memcpy(h + (B->off_morder[c] - B->off_desc), M.order.data(), M.order.size() * sizeof(int));
-            std::memcpy(h + (B->off_mprefix[c] - B->off_desc), M.prefix.data(), M.prefix.size() * sizeof(int64_t));
+            std::memcpy(h + (B->off_order[t] - B->off_desc), M.order.data(), M.order.size() * sizeof(int));
+            std::memcpy(h + (B->off_prefix[t] - B->off_desc), M.prefix.data(), M.prefix.size() * sizeof(int64_t));
         }
         ST_HIP_CHECK(hipMemcpyAsync(ws + B->off_desc, h, B->pinned_bytes, hipMemcpyHostToDevice, s));
         ST_HIP_CHECK(hipEventRecord(B->staged, s));
@@ -624,35 +628,24 @@ extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* co
     for (int g : B->zero_steps)
         ST_HIP_CHECK(hipMemcpyAsync(outs[g], ins[g], size_t(B->desc[g].rows * B->desc[g].cols) * sizeof(float),
                                     hipMemcpyDeviceToDevice, s));
-    bool any_march = false;
-    for (int c = 0; c < 6; ++c) any_march = any_march || !B->mclass[c].order.empty();
-    if (B->res.empty() && B->max_passes == 0 && !any_march) return ST_OK;
-    if (!(B->flags & ST_FLAG_GRAPH)) return enqueue_batch(B, ws, s, s, nullptr, nullptr, nullptr, nullptr);
+    bool any = false;
+    for (int i = 0; i < BRANCHES; ++i) any = any || branch_used(B, i);
+    if (!any) return ST_OK;
+    if (br || !(B->flags & ST_FLAG_GRAPH)) return enqueue_batch(B, ws, s, br);
     if (!(B->exec && B->g_ws == workspace)) {
-        if (B->exec) {
-            (void)hipGraphExecDestroy(B->exec);
-            B->exec = nullptr;
-        }
-        // capture: the resident grids on a side branch forked from and joined back into the main one
-        hipStream_t cap = nullptr, side = nullptr;
-        hipEvent_t fork = nullptr, join = nullptr;
-        hipStream_t mside[6] = {};
-        hipEvent_t mjoin[6] = {};
+        drop_exec(B);
+        // capture: every branch forked from and joined back into the main stream
+        hipStream_t cap = nullptr;
+        Branches branches;
         int rc = ST_OK;
         hipGraph_t graph = nullptr;
-        bool made = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) == hipSuccess &&
-                    hipStreamCreateWithFlags(&side, hipStreamNonBlocking) == hipSuccess &&
-                    hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
-                    hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess;
-        for (int c = 0; c < 6 && made; ++c)
-            made = hipStreamCreateWithFlags(&mside[c], hipStreamNonBlocking) == hipSuccess &&
-                   hipEventCreateWithFlags(&mjoin[c], hipEventDisableTiming) == hipSuccess;
+        const bool made = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) == hipSuccess && branches.create(B, false);
         if (!made) {
             rc = fail(ST_EHIP, "stream/event creation for graph capture failed");
         } else if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
             rc = fail(ST_EHIP, "hipStreamBeginCapture failed");
         } else {
-            rc = enqueue_batch(B, ws, cap, side, fork, join, mside, mjoin);
+            rc = enqueue_batch(B, ws, cap, &branches);
             const hipError_t e = hipStreamEndCapture(cap, &graph);
             if (!rc && e != hipSuccess) rc = fail(ST_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
         }
@@ -661,13 +654,6 @@ extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* co
             if (e2 != hipSuccess) rc = fail(ST_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e2));
         }
         if (graph) (void)hipGraphDestroy(graph);
-        if (fork) (void)hipEventDestroy(fork);
-        if (join) (void)hipEventDestroy(join);
-        if (side) (void)hipStreamDestroy(side);
-        for (int c = 0; c < 6; ++c) {
-            if (mjoin[c]) (void)hipEventDestroy(mjoin[c]);
-            if (mside[c]) (void)hipStreamDestroy(mside[c]);
-        }
         if (cap) (void)hipStreamDestroy(cap);
         (void)hipGetLastError();
         if (rc) return rc;
@@ -675,6 +661,11 @@ extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* co
     }
     ST_HIP_CHECK(hipGraphLaunch(B->exec, s));
     return ST_OK;
+}
+
+extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* const* outs, void* workspace,
+                                   size_t ws_bytes, void* stream) {
+    return run_batched(B, ins, outs, workspace, ws_bytes, stream, nullptr);
 }
 
 extern "C" int stencil_batch_set_class(st_batch* B, int shape, int radius, int engine, int depth) {
@@ -688,10 +679,7 @@ extern "C" int stencil_batch_set_class(st_batch* B, int shape, int radius, int e
     B->depth[c] = depth;
     build_passes(B);
     B->staged_valid = false;
-    if (B->exec) {
-        (void)hipGraphExecDestroy(B->exec);
-        B->exec = nullptr;
-    }
+    drop_exec(B);
     return ST_OK;
 }
 
@@ -703,10 +691,7 @@ extern "C" int stencil_batch_set_segment(st_batch* B, int shape, int radius, int
     B->seg_min[c] = min_rows;
     build_passes(B);
     B->staged_valid = false;
-    if (B->exec) {
-        (void)hipGraphExecDestroy(B->exec);
-        B->exec = nullptr;
-    }
+    drop_exec(B);
     return ST_OK;
 }
 
@@ -715,15 +700,16 @@ extern "C" int stencil_batch_get_segment(const st_batch* B, int shape, int radiu
     if ((shape != SHAPE_STAR && shape != SHAPE_BOX) || radius < 1 || radius > 3)
         return fail(ST_EINVAL, "bad class");
     const int c = shape * 3 + radius - 1;
-    *rows = B->engine[c] == 1 && !B->mclass[c].order.empty() ? B->mclass[c].seg : 0;
+    *rows = B->march[c].order.empty() ? 0 : B->march[c].seg;
     return ST_OK;
 }
 
 // Coordinate descent over the stencil classes (shape, radius) of the non-resident grids: for each
-// class in turn, time the whole batch (direct launches) with every candidate engine and depth -- LDS
+// class in turn, time the whole batch (for a graph on the streams of its branches: they share the
+// device, so what is fastest alone need not be) with every candidate engine and depth -- register
 // tiles with the class's depth capped at 1, 2, 3, 4, 6, 8, 12 or 16, or marching with 1 .. the
-// deepest its radius allows, each marching depth with the default segments and with segments 2, 4
-// and 8 times as long -- keep the fastest, then move to the next class.
+// deepest its radius allows, each marching depth with the default segments and with those that make
+// at most one, two, three or four tasks per SIMD (a pass waits for its busiest SIMD) -- keep the fastest, then move to the next class.
 extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void* const* outs, void* workspace,
                                       size_t ws_bytes, int* tb_out, int* engine_out, void* stream) {
     if (!B || !ins || !outs) return fail(ST_EINVAL, "NULL argument");
@@ -731,8 +717,6 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (tb_out) std::fill(tb_out, tb_out + 6, 0);
     if (engine_out) std::fill(engine_out, engine_out + 6, 0);
-    const uint32_t flags = B->flags;
-    B->flags &= ~ST_FLAG_GRAPH;
     bool present[6] = {};
     int deepest[6] = {};
     for (int g : B->tiled) {
@@ -741,23 +725,38 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
         deepest[c] = std::max(deepest[c], B->tb_max[g]);
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
+    Branches branches;
     int rc = ST_OK;
-    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = fail(ST_EHIP, "hipEventCreate");
-    auto apply = [&](int c, int engine, int depth, int seg_mult) {
+    if ((B->flags & ST_FLAG_GRAPH) && !branches.create(B, true)) rc = fail(ST_EHIP, "stream/event creation failed");
+    else if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = fail(ST_EHIP, "hipEventCreate");
+    // fill: marching segments such that the class's tasks are at most that many wavefronts a SIMD
+    auto apply = [&](int c, int engine, int depth, int fill) {
         B->engine[c] = engine;
         B->depth[c] = depth;
         B->seg_min[c] = 0;
         build_passes(B);
-        if (engine == 1 && seg_mult > 1) {  // longer than the default segment of this depth
-            B->seg_min[c] = seg_mult * B->mclass[c].seg;
-            build_passes(B);
+        if (engine == 1 && fill && !B->march[c].order.empty()) {
+            auto tasks = [&](int64_t seg) {
+                int64_t n = 0;
+                for (int g : B->march[c].order) n += B->desc[g].tiles_x * ((B->desc[g].rows + seg - 1) / seg);
+                return n;
+            };
+            int64_t lo = 1, hi = int64_t(1) << 31;  // the shortest segment that fits
+            while (lo < hi) {
+                const int64_t mid = lo + (hi - lo) / 2;
+                if (tasks(mid) <= int64_t(SIMDS) * fill) hi = mid; else lo = mid + 1;
+            }
+            if (lo < int64_t(1) << 31) {
+                B->seg_min[c] = lo;
+                build_passes(B);
+            }
         }
         B->staged_valid = false;  // descriptor tables changed
     };
     auto timed = [&](float* ms) -> int {
         for (int rep = 0; rep < 2; ++rep) {  // the first run warms up and stages the tables
             if (rep == 1 && hipEventRecord(e0, s) != hipSuccess) return fail(ST_EHIP, "hipEventRecord");
-            if (int r = stencil_run_batched(B, ins, outs, workspace, ws_bytes, stream)) return r;
+            if (int r = run_batched(B, ins, outs, workspace, ws_bytes, stream, B->flags & ST_FLAG_GRAPH ? &branches : nullptr)) return r;
         }
         if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
             return fail(ST_EHIP, "hipEventRecord/Synchronize");
@@ -768,17 +767,17 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
         if (!present[c]) continue;
         const int r = c % 3 + 1;
         struct Cand {
-            int engine, depth, seg_mult;
+            int engine, depth, fill;
         };
         std::vector<Cand> cands;
         for (int cap : kCaps)
-            if (cap <= deepest[c]) cands.push_back({0, cap, 1});
+            if (cap <= deepest[c]) cands.push_back({0, cap, 0});
         for (int t = 1; t <= march_max_tb(c / 3, r, 1); ++t)
-            for (int m : {1, 2, 4, 8}) cands.push_back({1, t, m});
+            for (int m : {0, 1, 2, 3, 4}) cands.push_back({1, t, m});
         Cand best = cands[0];
         float best_ms = 1e30f;
         for (const Cand& cd : cands) {
-            apply(c, cd.engine, cd.depth, cd.seg_mult);
+            apply(c, cd.engine, cd.depth, cd.fill);
             float ms = 0.0f;
             if ((rc = timed(&ms))) break;
             if (ms < best_ms) {
@@ -787,16 +786,12 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
             }
         }
         if (rc) break;
-        apply(c, best.engine, best.depth, best.seg_mult);
+        apply(c, best.engine, best.depth, best.fill);
         if (tb_out) tb_out[c] = best.depth;
         if (engine_out) engine_out[c] = best.engine;
     }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    B->flags = flags;
-    if (B->exec) {  // the captured graph holds the old pass structure
-        (void)hipGraphExecDestroy(B->exec);
-        B->exec = nullptr;
-    }
+    drop_exec(B);  // it holds the old pass structure
     return rc;
 }

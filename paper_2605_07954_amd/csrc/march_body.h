@@ -692,36 +692,39 @@ __device__ __forceinline__ void march_task(const MarchView& a, const float* w, i
     else march_levels<S, R, V, SHAPE, TB, D, false, VEC, XBC_CONST>(a, wv, lane, y0, y1, X0, none, lo, hi);
 }
 
-// The same task marched upwards when `up` is set (constant halo), taking the input rows `sh` from LDS.
-// Upward tasks take the general (edge) form only, which keeps the kernel's code to one more copy of
-// the loop.
-template <int S, int R, int V, int SHAPE, int TB, int D, bool VEC = true>
+// The same task (constant halo, whole lanes) marched upwards when `up` is set, taking the input rows `sh`
+// from LDS.
+template <int S, int R, int V, int SHAPE, int TB, int D>
 __device__ __forceinline__ void march_task_dir(const MarchView& a, const float* w, int lane, int64_t y0, int64_t y1,
-                                               int64_t X0, bool up, const SharedRows& sh) {
+                                               int64_t X0, bool up, const SharedRows& sh, int lo, int hi) {
     float wv[(2 * R + 1) * (2 * R + 1)];
     load_weights<R, V, SHAPE>(w, wv);
-    if (up) march_levels<S, R, V, SHAPE, TB, D, true, VEC, XBC_CONST, true, true>(a, wv, lane, y0, y1, X0, sh);
-    else if (task_edge<R, TB>(a, y0, y1, X0, V))
-        march_levels<S, R, V, SHAPE, TB, D, true, VEC, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh);
-    else march_levels<S, R, V, SHAPE, TB, D, false, VEC, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh);
+    if (task_edge<R, TB>(a, y0, y1, X0, V)) {
+        if (up) march_levels<S, R, V, SHAPE, TB, D, true, true, XBC_CONST, true, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
+        else march_levels<S, R, V, SHAPE, TB, D, true, true, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
+    } else if (up) {
+        march_levels<S, R, V, SHAPE, TB, D, false, true, XBC_CONST, true, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
+    } else {
+        march_levels<S, R, V, SHAPE, TB, D, false, true, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
+    }
 }
 
 // Stage input rows r0 .. r0 + R TB - 1 of the task (y0, y1, X0) in LDS (`dst[(row - o0) * 64 + lane]`) as
 // the task's own fetches would return them, for the neighbouring task that shares them.  All loads are
 // issued before the first LDS write, so staging costs one memory latency.
-template <int S, int R, int V, int TB, bool VEC = true>
+template <int S, int R, int V, int TB>
 __device__ __forceinline__ void stage_rows(const MarchView& a, int lane, int64_t y0, int64_t y1, int64_t X0,
                                            int64_t r0, int64_t o0, float4* dst) {
     constexpr int RT = R * TB;
     const int64_t gx = X0 + V * lane;
-    const ColMask<V> cm = col_mask<V, VEC>(gx, a.cols);
+    const ColMask<V> cm = col_mask<V, true>(gx, a.cols);
     const int64_t need_lo = y0 - R * TB, need_hi = y1 - 1 + R * TB;
     float4 raw[RT];
     if (task_edge<R, TB>(a, y0, y1, X0, V)) {
         const RowSpan sp{need_lo < 0 ? 0 : need_lo, need_hi > a.rows - 1 ? a.rows - 1 : need_hi};
 #pragma unroll
         for (int t = 0; t < RT; ++t)
-            raw[t] = __builtin_bit_cast(float4, fetch_raw<S, V, VEC, true, XBC_CONST>(a, r0 + t, gx, cm, X0, sp));
+            raw[t] = __builtin_bit_cast(float4, fetch_raw<S, V, true, true, XBC_CONST>(a, r0 + t, gx, cm, X0, sp));
     } else {
         const RowSpan sp{need_lo, need_hi};
 #pragma unroll

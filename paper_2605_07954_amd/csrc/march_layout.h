@@ -99,26 +99,37 @@ struct BandCols {
 // Columns of band `band` with V columns per lane and H halo lanes.  With zero sides the bands
 // between the first and the last follow the first at V (64 - 2H) columns each, the last of them
 // moved left where it would pass the last band's end (the overlap stores the same values).
-__host__ __device__ inline BandCols band_cols(const TaskMap& m, int64_t band, int V, int H) {
+__host__ __device__ inline BandCols band_cols(int64_t cols, int64_t bands, bool zero_sides, int64_t band, int V, int H) {
     const int64_t outw = int64_t(V) * (64 - 2 * H);
     BandCols c{band * outw - int64_t(V) * H, -1, -1};
-    if (m.zero_sides) {
-        const int64_t last = m.cols - 64 * int64_t(V);
+    if (zero_sides) {
+        const int64_t last = cols - 64 * int64_t(V);
         if (band == 0) {
             c.x0 = 0;
             c.lo = 0;
-        } else if (band == m.bands - 1) {
+        } else if (band == bands - 1) {
             c.x0 = last;
             c.hi = 64;
         } else {
             c.x0 = (band - 1) * outw + int64_t(V) * (64 - 2 * H);
             if (c.x0 > last) c.x0 = last;
         }
-    } else if (m.cols % V && m.cols >= 64 * int64_t(V)) {
-        const int64_t last = band == m.bands - 1 ? m.cols - int64_t(V) * (64 - H) : m.cols - 64 * int64_t(V);
+    } else if (cols % V && cols >= 64 * int64_t(V)) {
+        const int64_t last = band == bands - 1 ? cols - int64_t(V) * (64 - H) : cols - 64 * int64_t(V);
         if (c.x0 > last) c.x0 = last;  // (the overlap stores the same values)
     }
     return c;
+}
+__host__ __device__ inline BandCols band_cols(const TaskMap& m, int64_t band, int V, int H) {
+    return band_cols(m.cols, m.bands, m.zero_sides, band, V, H);
+}
+
+// Bands of a grid (more are harmless: they store what others do).
+inline int64_t band_count(int64_t cols, int V, int H, bool zero_sides) {
+    const int64_t outw = int64_t(V) * (64 - 2 * H);
+    if (!zero_sides) return (cols + outw - 1) / outw;
+    const int64_t sides = 2 * int64_t(V) * (64 - H);
+    return 2 + (cols > sides ? (cols - sides + outw - 1) / outw : 0);
 }
 
 // ---- host side: choosing a layout
@@ -177,16 +188,10 @@ inline bool zoned_map(TaskMap& m, int64_t seg, int64_t cut, int64_t reach, bool 
 inline bool plan_march_tasks(TaskMap& m, int64_t rows, int64_t cols, int V, int r, int levels, int taps,
                              int64_t waves, int64_t seg_min, bool zero_sides) {
     constexpr double edge_cost = 1.5;  // extra instructions per cell and level of an edge task
-    const int H = halo_lanes(r, levels, V);
-    const int64_t outw = int64_t(V) * (64 - 2 * H);
     m.rows = rows;
     m.cols = cols;
     m.zero_sides = zero_sides;
-    int64_t bands = (cols + outw - 1) / outw;
-    if (zero_sides) {
-        const int64_t sides = 2 * int64_t(V) * (64 - H);
-        bands = 2 + (cols > sides ? (cols - sides + outw - 1) / outw : 0);
-    }
+    const int64_t bands = band_count(cols, V, halo_lanes(r, levels, V), zero_sides);
     if (bands >= (int64_t(1) << 31)) return false;
     m.bands = int(bands);
     const int64_t per_band = std::max<int64_t>(1, waves / bands);  // segments per band
