@@ -389,7 +389,7 @@ __device__ __forceinline__ void input_store(float* lds, const float2 (&r)[SPT1],
 
 // scale: per field (inv, gain); the u0 channel enters as u0 * inv
 template <bool ZOUT>
-__global__ __launch_bounds__(256) void l1_fwd(const float* params, const float* u0, const float* kappa,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void l1_fwd(const float* params, const float* u0, const float* kappa,
                                               const float* scale, int nb, int H, int W, float* Z, uint16_t* A) {
     __shared__ float patch[2][2 * SPT1 * 256];
     const int64_t ntiles = tile_count(nb, H, W);
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void l1_fwd(const float* params, const float* 
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt) wa[s5][mt] = k < 18 ? params[k * C + 16 * mt + lane_px] : 0.0f;
     }
-    float bias[2][4];
+    f32x4_t bias[2];
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
@@ -427,16 +427,9 @@ __global__ __launch_bounds__(256) void l1_fwd(const float* params, const float* 
         const float inv = scale[2 * next.b];
         input_fetch(u0, kappa, next, H, W, pre, ok);
         __builtin_amdgcn_sched_barrier(0);  // (ahead of this tile's stores)
-        // accumulators start from the bias; K steps outermost so that consecutive MFMAs feed
-        // independent accumulators
+        // the first MFMAs start from the bias, read straight from `bias`; K steps outermost so that
+        // consecutive MFMAs feed independent accumulators
         f32x4_t acc[ROWS][MT][2];
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r)
-#pragma unroll
-            for (int m = 0; m < MT; ++m)
-#pragma unroll
-                for (int mt = 0; mt < 2; ++mt)
-                    acc[r][m][mt] = f32x4_t{bias[mt][0], bias[mt][1], bias[mt][2], bias[mt][3]};
         const float* opnd = lds + 2 * ((wave * ROWS) * (TW + 2) + lane_px);
 #pragma unroll
         for (int s5 = 0; s5 < 5; ++s5)
@@ -445,8 +438,9 @@ __global__ __launch_bounds__(256) void l1_fwd(const float* params, const float* 
 #pragma unroll
                 for (int m = 0; m < MT; ++m) {
                     const float bv = koff[s5] >= 0 ? opnd[2 * (r * (TW + 2) + m * 16) + koff[s5]] : 0.0f;
-                    acc[r][m][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[s5][0], bv, acc[r][m][0], 0, 0, 0);
-                    acc[r][m][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[s5][1], bv, acc[r][m][1], 0, 0, 0);
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt)
+                        acc[r][m][mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(wa[s5][mt], bv, s5 == 0 ? bias[mt] : acc[r][m][mt], 0, 0, 0);
                 }
         const int64_t row0 = (int64_t(tc.b) * H + tc.y0) * W * C;
         const __amdgpu_buffer_rsrc_t as = rows_at(A + row0);
