@@ -119,7 +119,64 @@ constexpr int FRAG = 9 * 2 * 64 * 8;  // bf16 per layer and direction
 constexpr int FRAG6 = 9 * 64 * 8;
 constexpr int NFRAG = 4 * 2 * FRAG + FRAG6;  // bf16 in the fragment area
 
-__global__ void prep_frags(const float* params, uint16_t* frags) {
+// Scale constants of each field: s = RMS of the field's cells (FP64, fixed-order two-stage sum;
+// s = 1 for an all-zero field), scale[2b] = fp32(1 / s), scale[2b + 1] = fp32(2^-11 s).
+constexpr int SCB = 256;  // stage-1 blocks per field
+constexpr int SCU = 8;    // cells a thread has in flight (a load at a time, 1024^2 took 6.4 us)
+__global__ __launch_bounds__(256) void field_scale_partial(const float* u, int64_t n, double* partial) {
+    __shared__ double red[256];
+    const int b = blockIdx.y;
+    const float* f = u + int64_t(b) * n;
+    double acc = 0.0;
+    constexpr int64_t STEP = int64_t(SCB) * 256;
+    int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    for (; k + (SCU - 1) * STEP < n; k += SCU * STEP) {
+        float x[SCU];
+#pragma unroll
+        for (int i = 0; i < SCU; ++i) x[i] = f[k + i * STEP];
+#pragma unroll
+        for (int i = 0; i < SCU; ++i) acc += double(x[i]) * double(x[i]);
+    }
+    for (; k < n; k += STEP) {
+        const double x = double(f[k]);
+        acc += x * x;
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) partial[int64_t(b) * SCB + blockIdx.x] = red[0];
+}
+
+// Field b's constants from its partial sums, by one workgroup of SCB threads: the sums are loaded at once
+// and added in order from LDS (a thread that loaded them one by one took 7.6 us).
+__device__ __forceinline__ void scale_finish(const double* partial, int b, int64_t n, float* scale) {
+    __shared__ double part[SCB];
+    part[threadIdx.x] = partial[int64_t(b) * SCB + threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x) return;
+    double acc = 0.0;
+#pragma unroll 16
+    for (int k = 0; k < SCB; ++k) acc += part[k];
+    double s = sqrt(acc / double(n));
+    if (!(s > 0.0)) s = 1.0;
+    scale[2 * b] = float(1.0 / s);
+    scale[2 * b + 1] = float(UPDATE_SCALE * s);
+}
+__global__ __launch_bounds__(SCB) void field_scale_finish(const double* partial, int64_t n, float* scale) {
+    scale_finish(partial, int(blockIdx.x), n, scale);
+}
+
+// The weight fragments; the workgroups past them finish the scale constants of one field each.
+constexpr int FRAG_BLOCKS = (NFRAG + SCB - 1) / SCB;
+__global__ __launch_bounds__(SCB) void prep_frags(const float* params, uint16_t* frags, const double* partial, int64_t cells,
+                                                  float* scale) {
+    if (blockIdx.x >= FRAG_BLOCKS) {
+        scale_finish(partial, int(blockIdx.x) - FRAG_BLOCKS, cells, scale);
+        return;
+    }
     // frags: [4 layers][2 directions][FRAG], then [FRAG6]
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= NFRAG) return;
@@ -1052,38 +1109,6 @@ __global__ void diff_norms_finish(const double* partial, int nblk, double* out2)
     out2[1] = s1;
 }
 
-// Scale constants of each field: s = RMS of the field's cells (FP64, fixed-order two-stage sum;
-// s = 1 for an all-zero field), scale[2b] = fp32(1 / s), scale[2b + 1] = fp32(2^-11 s).
-constexpr int SCB = 256;  // stage-1 blocks per field
-__global__ __launch_bounds__(256) void field_scale_partial(const float* u, int64_t n, double* partial) {
-    __shared__ double red[256];
-    const int b = blockIdx.y;
-    const float* f = u + int64_t(b) * n;
-    double acc = 0.0;
-    for (int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x; k < n; k += int64_t(SCB) * 256) {
-        const double x = double(f[k]);
-        acc += x * x;
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partial[int64_t(b) * SCB + blockIdx.x] = red[0];
-}
-
-__global__ void field_scale_finish(const double* partial, int nb, int64_t n, float* scale) {
-    const int b = int(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b >= nb) return;
-    double acc = 0.0;
-    for (int k = 0; k < SCB; ++k) acc += partial[int64_t(b) * SCB + k];
-    double s = sqrt(acc / double(n));
-    if (!(s > 0.0)) s = 1.0;
-    scale[2 * b] = float(1.0 / s);
-    scale[2 * b + 1] = float(UPDATE_SCALE * s);
-}
-
 // ---- the light-cone patch judge -------------------------------------------------------------
 // An n x n lattice of patches; window (a, c) = patch (a, c) dilated by K cells and clipped to the
 // grid.  The windows are packed edge to edge into a "mosaic" field in lattice order, so that the
@@ -1301,22 +1326,30 @@ int launch_conv(const ConvArgs& a, hipStream_t s) {
     return ST_OK;
 }
 
-// The scale constants of nb fields of H x W (see field_scale_finish) into `scale`.
-int compute_scale(const float* u0, int nb, int H, int W, double* partial, float* scale, hipStream_t s) {
+// The partial sums of the scale constants of nb fields of H x W.
+int sum_scale(const float* u0, int nb, int H, int W, double* partial, hipStream_t s) {
     clear_stale_error();
     hipLaunchKernelGGL(field_scale_partial, dim3(SCB, nb), dim3(256), 0, s, u0, int64_t(H) * W, partial);
     ST_LAUNCH_CHECK("field_scale_partial");
-    hipLaunchKernelGGL(field_scale_finish, dim3((nb + 63) / 64), dim3(64), 0, s, partial, nb, int64_t(H) * W, scale);
+    return ST_OK;
+}
+
+// The scale constants of nb fields of H x W (see scale_finish) into `scale`.
+int compute_scale(const float* u0, int nb, int H, int W, double* partial, float* scale, hipStream_t s) {
+    if (int rc = sum_scale(u0, nb, H, W, partial, s)) return rc;
+    hipLaunchKernelGGL(field_scale_finish, dim3(nb), dim3(SCB), 0, s, partial, int64_t(H) * W, scale);
     ST_LAUNCH_CHECK("field_scale_finish");
     return ST_OK;
 }
 
-// Forward pass; `scale` holds the (inv, gain) pair of each field (device).
-int forward_impl(const float* params, const float* u0, const float* kappa, const float* scale, float* uhat, int nb,
-                 int H, int W, char* ws, const WsLayout& L, bool train, hipStream_t s) {
+// Forward pass; `scale` holds the (inv, gain) pair of each field (device), or with `partial` (sum_scale)
+// receives it.
+int forward_impl(const float* params, const float* u0, const float* kappa, const float* scale, const double* partial, float* uhat,
+                 int nb, int H, int W, char* ws, const WsLayout& L, bool train, hipStream_t s) {
     uint16_t* frags = reinterpret_cast<uint16_t*>(ws + L.frags);
     clear_stale_error();
-    hipLaunchKernelGGL(prep_frags, dim3((NFRAG + 255) / 256), dim3(256), 0, s, params, frags);
+    hipLaunchKernelGGL(prep_frags, dim3(FRAG_BLOCKS + (partial ? nb : 0)), dim3(SCB), 0, s, params, frags, partial,
+                       int64_t(H) * W, const_cast<float*>(scale));  // (written with `partial` only)
     ST_LAUNCH_CHECK("prep_frags");
     auto act = [&](int l) { return reinterpret_cast<uint16_t*>(ws + L.act[l]); };
     auto zz = [&](int l) { return train ? reinterpret_cast<float*>(ws + L.z[l]) : nullptr; };
@@ -1405,10 +1438,10 @@ int surrogate_infer(sg_model* m, const float* params, const float* u0, const flo
     if (!workspace || ws_bytes < L.total) return fail(ST_ENOWS, "workspace too small");
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    float* scale = reinterpret_cast<float*>(ws + L.scale);
-    if (int rc = compute_scale(u0, batch, int(rows), int(cols), reinterpret_cast<double*>(ws + L.scalep), scale, s))
-        return rc;
-    return forward_impl(params, u0, kappa, scale, u_hat, batch, int(rows), int(cols), ws, L, false, s);
+    double* partial = reinterpret_cast<double*>(ws + L.scalep);
+    if (int rc = sum_scale(u0, batch, int(rows), int(cols), partial, s)) return rc;
+    return forward_impl(params, u0, kappa, reinterpret_cast<float*>(ws + L.scale), partial, u_hat, batch, int(rows), int(cols),
+                        ws, L, false, s);
 }
 
 // Loss and gradient; `scale_in` = the (inv, gain) pair of each field (device), or NULL to take them
@@ -1436,14 +1469,12 @@ static int loss_grad_impl(const float* params, const float* u0, const float* kap
     char* ws = static_cast<char*>(workspace);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int H = int(rows), W = int(cols), nb = batch;
-    const float* scale = scale_in;
-    if (!scale) {
-        float* sc = reinterpret_cast<float*>(ws + L.scale);
-        if (int rc = compute_scale(u0, nb, H, W, reinterpret_cast<double*>(ws + L.scalep), sc, s)) return rc;
-        scale = sc;
-    }
+    const float* scale = scale_in ? scale_in : reinterpret_cast<float*>(ws + L.scale);
+    double* squares = scale_in ? nullptr : reinterpret_cast<double*>(ws + L.scalep);
+    if (squares)
+        if (int rc = sum_scale(u0, nb, H, W, squares, s)) return rc;
     float* uhat = reinterpret_cast<float*>(ws + L.dz1);  // scratch: dz1 is not needed until layer-2 backward
-    if (int rc = forward_impl(params, u0, kappa, scale, uhat, nb, H, W, ws, L, true, s)) return rc;
+    if (int rc = forward_impl(params, u0, kappa, scale, squares, uhat, nb, H, W, ws, L, true, s)) return rc;
     float* dF = reinterpret_cast<float*>(ws + L.dF);
     double* lossp = reinterpret_cast<double*>(ws + L.lossp);
     const unsigned gpx = unsigned(L.nblk_px);
@@ -1707,10 +1738,10 @@ int surrogate_infer_checked(sg_model* m, const float* params, const float* u0, c
     float* b2 = reinterpret_cast<float*>(ws + L.total + 2 * field);
     double* part = reinterpret_cast<double*>(ws + L.total + 3 * field);
     double* sums = reinterpret_cast<double*>(ws + L.total + 3 * field + a256(1024 * 16));
-    float* scale = reinterpret_cast<float*>(ws + L.scale);
-    if (int rc = compute_scale(u0, 1, int(rows), int(cols), reinterpret_cast<double*>(ws + L.scalep), scale, s))
-        return rc;
-    if (int rc = forward_impl(params, u0, kappa, scale, uhat, 1, int(rows), int(cols), ws, L, false, s)) return rc;
+    const float* scale = reinterpret_cast<float*>(ws + L.scale);
+    double* partial = reinterpret_cast<double*>(ws + L.scalep);
+    if (int rc = sum_scale(u0, 1, int(rows), int(cols), partial, s)) return rc;
+    if (int rc = forward_impl(params, u0, kappa, scale, partial, uhat, 1, int(rows), int(cols), ws, L, false, s)) return rc;
     const int64_t n = rows * cols;
     // the patch judge needs its four mosaic fields in the two spare fields (else judge the whole field)
     const MosaicArgs g = mosaic_layout(rows, cols, K);
