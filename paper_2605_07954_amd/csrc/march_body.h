@@ -693,20 +693,17 @@ __device__ __forceinline__ void march_task(const MarchView& a, const float* w, i
 }
 
 // The same task (constant halo, whole lanes) marched upwards when `up` is set, taking the input rows `sh`
-// from LDS.
+// from LDS.  Upward tasks take the general (edge) form only, which keeps the kernel's code to one more copy
+// of the loop.
 template <int S, int R, int V, int SHAPE, int TB, int D>
 __device__ __forceinline__ void march_task_dir(const MarchView& a, const float* w, int lane, int64_t y0, int64_t y1,
                                                int64_t X0, bool up, const SharedRows& sh, int lo, int hi) {
     float wv[(2 * R + 1) * (2 * R + 1)];
     load_weights<R, V, SHAPE>(w, wv);
-    if (task_edge<R, TB>(a, y0, y1, X0, V)) {
-        if (up) march_levels<S, R, V, SHAPE, TB, D, true, true, XBC_CONST, true, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
-        else march_levels<S, R, V, SHAPE, TB, D, true, true, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
-    } else if (up) {
-        march_levels<S, R, V, SHAPE, TB, D, false, true, XBC_CONST, true, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
-    } else {
-        march_levels<S, R, V, SHAPE, TB, D, false, true, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
-    }
+    if (up) march_levels<S, R, V, SHAPE, TB, D, true, true, XBC_CONST, true, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
+    else if (task_edge<R, TB>(a, y0, y1, X0, V))
+        march_levels<S, R, V, SHAPE, TB, D, true, true, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
+    else march_levels<S, R, V, SHAPE, TB, D, false, true, XBC_CONST, false, true>(a, wv, lane, y0, y1, X0, sh, lo, hi);
 }
 
 // Stage input rows r0 .. r0 + R TB - 1 of the task (y0, y1, X0) in LDS (`dst[(row - o0) * 64 + lane]`) as
