@@ -398,8 +398,9 @@ int stencil_batch_get_segment(const st_batch* batch, int shape, int radius, int6
  * stay on tiles) with every depth it offers (up to 8 / 6 / 4 levels for star r = 1 / 2 / 3,
  * 6 / 3 / 2 for box), each with the default segments and with those that make one, two, three
  * or four tasks per SIMD (stencil_batch_set_segment).  Each class is a chain of launches, the
- * classes on parallel branches of the graph.  Coordinate descent: each
- * class in turn, every candidate timed on the whole batch run twice on the caller's buffers (outs
+ * classes on parallel branches of the graph.  Coordinate descent: each class in turn, every
+ * candidate timed on the whole batch, then each class's best six once more with the others
+ * chosen (the batch runs on the caller's buffers: outs
  * are overwritten; results are bitwise those of any other choice).  Writes the chosen depth and
  * engine (0 = tiles, 1 = marching) per class to tb_out[6] / engine_out[6] when non-NULL (star
  * r = 1, 2, 3, then box r = 1, 2, 3; 0 = class absent).  Synchronises the stream.  Errors: as

@@ -709,7 +709,8 @@ extern "C" int stencil_batch_get_segment(const st_batch* B, int shape, int radiu
 // device, so what is fastest alone need not be) with every candidate engine and depth -- register
 // tiles with the class's depth capped at 1, 2, 3, 4, 6, 8, 12 or 16, or marching with 1 .. the
 // deepest its radius allows, each marching depth with the default segments and with those that make
-// at most one, two, three or four tasks per SIMD (a pass waits for its busiest SIMD) -- keep the fastest, then move to the next class.
+// at most one, two, three or four tasks per SIMD (a pass waits for its busiest SIMD) --
+// keep the fastest, then move to the next class; then each class's best six once more.
 extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void* const* outs, void* workspace,
                                       size_t ws_bytes, int* tb_out, int* engine_out, void* stream) {
     if (!B || !ins || !outs) return fail(ST_EINVAL, "NULL argument");
@@ -753,43 +754,50 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
         }
         B->staged_valid = false;  // descriptor tables changed
     };
-    auto timed = [&](float* ms) -> int {
-        for (int rep = 0; rep < 2; ++rep) {  // the first run warms up and stages the tables
-            if (rep == 1 && hipEventRecord(e0, s) != hipSuccess) return fail(ST_EHIP, "hipEventRecord");
-            if (int r = run_batched(B, ins, outs, workspace, ws_bytes, stream, B->flags & ST_FLAG_GRAPH ? &branches : nullptr)) return r;
+    // the fastest of `runs` runs after one that warms up and stages the tables
+    auto timed = [&](int runs, float* ms) -> int {
+        const Branches* br = B->flags & ST_FLAG_GRAPH ? &branches : nullptr;
+        if (int r = run_batched(B, ins, outs, workspace, ws_bytes, stream, br)) return r;
+        *ms = 1e30f;
+        for (int i = 0; i < runs; ++i) {
+            if (hipEventRecord(e0, s) != hipSuccess) return fail(ST_EHIP, "hipEventRecord");
+            if (int r = run_batched(B, ins, outs, workspace, ws_bytes, stream, br)) return r;
+            float t = 0.0f;
+            if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                hipEventElapsedTime(&t, e0, e1) != hipSuccess)
+                return fail(ST_EHIP, "hipEventRecord/Synchronize/ElapsedTime");
+            *ms = std::min(*ms, t);
         }
-        if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess)
-            return fail(ST_EHIP, "hipEventRecord/Synchronize");
-        return hipEventElapsedTime(ms, e0, e1) == hipSuccess ? ST_OK : fail(ST_EHIP, "hipEventElapsedTime");
+        return ST_OK;
     };
     static const int kCaps[] = {1, 2, 3, 4, 6, 8, 12, 16};
-    for (int c = 0; c < 6 && rc == ST_OK; ++c) {
-        if (!present[c]) continue;
-        const int r = c % 3 + 1;
-        struct Cand {
-            int engine, depth, fill;
-        };
-        std::vector<Cand> cands;
-        for (int cap : kCaps)
-            if (cap <= deepest[c]) cands.push_back({0, cap, 0});
-        for (int t = 1; t <= march_max_tb(c / 3, r, 1); ++t)
-            for (int m : {0, 1, 2, 3, 4}) cands.push_back({1, t, m});
-        Cand best = cands[0];
-        float best_ms = 1e30f;
-        for (const Cand& cd : cands) {
-            apply(c, cd.engine, cd.depth, cd.fill);
-            float ms = 0.0f;
-            if ((rc = timed(&ms))) break;
-            if (ms < best_ms) {
-                best_ms = ms;
-                best = cd;
+    struct Cand {
+        int engine, depth, fill;
+        float ms;
+    };
+    std::vector<Cand> cands[6];
+    // every candidate once, the other classes as they are; then each class's best few again, the others tuned
+    for (int sweep = 0; sweep < 2; ++sweep)
+        for (int c = 0; c < 6 && rc == ST_OK; ++c) {
+            if (!present[c]) continue;
+            std::vector<Cand>& cs = cands[c];
+            if (sweep == 0) {
+                for (int cap : kCaps)
+                    if (cap <= deepest[c]) cs.push_back({0, cap, 0, 0.0f});
+                for (int t = 1; t <= march_max_tb(c / 3, c % 3 + 1, 1); ++t)
+                    for (int m : {0, 1, 2, 3, 4}) cs.push_back({1, t, m, 0.0f});
             }
+            for (Cand& cd : cs) {
+                apply(c, cd.engine, cd.depth, cd.fill);
+                if ((rc = timed(1 + 2 * sweep, &cd.ms))) break;
+            }
+            if (rc) break;
+            std::stable_sort(cs.begin(), cs.end(), [](const Cand& x, const Cand& y) { return x.ms < y.ms; });
+            cs.resize(std::min<size_t>(cs.size(), 6));
+            apply(c, cs[0].engine, cs[0].depth, cs[0].fill);
+            if (tb_out) tb_out[c] = cs[0].depth;
+            if (engine_out) engine_out[c] = cs[0].engine;
         }
-        if (rc) break;
-        apply(c, best.engine, best.depth, best.fill);
-        if (tb_out) tb_out[c] = best.depth;
-        if (engine_out) engine_out[c] = best.engine;
-    }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
     drop_exec(B);  // it holds the old pass structure
