@@ -590,8 +590,8 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
             if (plan->kind == KIND_CONST && tb > max_tb(plan, tx, ty)) continue;
             if (plan->kind == KIND_VARCOEF && varcoef_lds_bytes(tb, tx, ty) > lds_limit()) continue;
             if (tb > sample_steps) continue;
-            // a pass that marches anyway has no tile: one candidate of the four
-            if (var == VARIANT_TILED && ti > 0 && tiled_march_columns(plan, tb)) continue;
+            // (a pass that marches anyway is a candidate of that marching variant)
+            if (var == VARIANT_TILED && tiled_march_columns(plan, tb)) continue;
             plan->tb = tb;
             plan->tile_x = tx;
             plan->tile_y = ty;
