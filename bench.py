@@ -53,7 +53,7 @@ def gstencil_s(steps: int, rows: int, cols: int, seconds: float) -> float:
     return steps * rows * cols / (seconds * 1e9)
 
 
-KERNEL_NAMES = {0: "sweep_tiled", 1: "sweep_stream", 2: "sweep_march", 3: "sweep_march", 4: "sweep_march",
+KERNEL_NAMES = {0: "sweep_block", 1: "sweep_stream", 2: "sweep_march", 3: "sweep_march", 4: "sweep_march",
                 5: "sweep_resident", 6: "sweep_mfma"}
 VARIANT_NAMES = {0: "tiled", 1: "stream", 2: "march", 3: "march8", 4: "march1", 5: "resident", 6: "mfma"}
 
