@@ -71,9 +71,10 @@ constexpr int MV = 4;  // columns per lane of the marching engine
 // rows of 64 lanes x 16 bytes per pair).
 constexpr size_t march_share_bytes(int r, int tb) { return size_t(MW / 2) * 2 * r * tb * 64 * sizeof(float4); }
 
-// (r = 3 at its deepest is held to the 168 registers that let three wavefronts share a SIMD)
+// (Star r = 3 at four levels takes 175 registers, two wavefronts per SIMD.  Held to 168 for three it keeps 13
+// values in scratch, and 256 mixed grids with that class at this depth took 2.9-3.1 ms instead of 2.0.)
 template <int R, int SH, int TB>
-__global__ __launch_bounds__(64 * MW) __attribute__((amdgpu_waves_per_eu(R == 3 ? 3 : 1))) void batched_march(MarchPassArgs a) {
+__global__ __launch_bounds__(64 * MW) void batched_march(MarchPassArgs a) {
     extern __shared__ float4 shared_rows[];
     const int lane = int(threadIdx.x & 63);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
