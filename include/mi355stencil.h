@@ -11,8 +11,8 @@
  *     (for example torch tensors' data_ptr()).  The library never allocates
  *     device memory behind the caller's back: scratch space is a caller-owned
  *     "workspace" whose minimum size is queried first.  Plans, batches and
- *     models own host memory only (the batched entry point also owns one
- *     pinned host staging table and one hipGraph).
+ *     models own host memory only (a batch also owns one pinned host staging
+ *     table and, with ST_FLAG_GRAPH, the streams and events of its branches).
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *     All device work is enqueued on it, asynchronously.  Only the entry
  *     points marked "synchronises" wait for the device.
@@ -343,7 +343,7 @@ int stencil_solve_ws_bytes(const st_plan* plan, int64_t check_every, size_t* byt
 int stencil_solve(st_plan* plan, const void* in, void* out, int64_t max_steps, int64_t check_every, double tol,
                   int64_t* steps_done, double* rel_residual, void* workspace, size_t ws_bytes, void* stream);
 
-/* ---- batched: many independent grids, one graph launch ------------------ */
+/* ---- batched: many independent grids, one call -------------------------- */
 
 /* stencil_batch_create -- group n plans (FP32, constant weights, r <= 3; each may differ in
  * shape, radius, footprint and weights) with their own step counts into one batch.
@@ -354,8 +354,9 @@ int stencil_solve(st_plan* plan, const void* in, void* out, int64_t max_steps, i
  * grids of a stencil class is one multi-grid kernel, and the passes follow
  * each other, so each tile's dependency on its neighbours' previous pass (the tiles' halo
  * swap, paper Sec. IV-B/C) is carried by the kernel boundary.  Steps == 0 is a copy.  The
- * plans must outlive the batch.  flags: ST_FLAG_GRAPH captures the whole run (resident
- * grids and each class on a parallel branch) in one hipGraph replayed by every run.
+ * plans must outlive the batch.  flags: ST_FLAG_GRAPH runs the resident grids and each class on
+ * parallel branches: streams that the batch makes at first use and keeps, forked from and joined
+ * into the caller's stream (while that is being captured, all of it stays on that stream).
  * Errors: ST_EINVAL, ST_EUNSUPPORTED, ST_ENOMEM. */
 int stencil_batch_create(st_batch** out, int n, st_plan* const* plans, const int64_t* steps, uint32_t flags);
 
@@ -398,7 +399,7 @@ int stencil_batch_get_segment(const st_batch* batch, int shape, int radius, int6
  * stay on tiles) with every depth it offers (up to 8 / 6 / 4 levels for star r = 1 / 2 / 3,
  * 6 / 3 / 2 for box), each with the default segments and with those that make one, two, three
  * or four tasks per SIMD (stencil_batch_set_segment).  Each class is a chain of launches, the
- * classes on parallel branches of the graph.  Coordinate descent: each class in turn, every
+ * classes on parallel branches.  Coordinate descent: each class in turn, every
  * candidate timed on the whole batch, then each class's best six once more with the others
  * chosen (the batch runs on the caller's buffers: outs
  * are overwritten; results are bitwise those of any other choice).  Writes the chosen depth and
@@ -408,7 +409,8 @@ int stencil_batch_get_segment(const st_batch* batch, int shape, int radius, int6
 int stencil_batch_autotune(st_batch* batch, const void* const* ins, void* const* outs, void* workspace,
                            size_t ws_bytes, int* tb_out, int* engine_out, void* stream);
 
-/* stencil_batch_destroy -- free the batch (graph, pinned table).  NULL is a no-op. */
+/* stencil_batch_destroy -- free the batch (pinned table; its branches, once their work is done).  NULL
+ * is a no-op. */
 int stencil_batch_destroy(st_batch* batch);
 
 /* ---- CNN surrogate ------------------------------------------------------ */

@@ -1,14 +1,14 @@
-// Batched sweep: many independent grids of uneven size and mixed stencil shape, run by one
-// hipGraph launch.
+// Batched sweep: many independent grids of uneven size and mixed stencil shape, run by one call.
 //
 // Small grids are resident: one workgroup keeps the grid for all of its steps, in registers where it
 // fits a 128 x 128 tile with its halo (batched_block.hip), else in LDS, so it never round-trips through
 // HBM.  The other grids run in passes: pass p of every grid of a stencil class is one multi-grid kernel
 // whose workgroups each take one (grid, tile) of that pass on register tiles, or whose wavefronts each
 // take one (grid, band, segment), so a pass of a class costs one launch instead of one per grid.  Passes
-// follow each other inside the graph, so the dependency of a tile on its neighbours' previous pass (the
-// halo exchange of the paper's tiles, Sec. IV-B/C) is carried by the kernel boundary; the classes and the
-// resident grids run on parallel branches of the same graph.
+// follow each other on a stream, so the dependency of a tile on its neighbours' previous pass (the
+// halo exchange of the paper's tiles, Sec. IV-B/C) is carried by the kernel boundary; with ST_FLAG_GRAPH
+// the classes and the resident grids run on parallel branches, forked from and joined into the caller's
+// stream.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -149,6 +149,32 @@ MarchPassFn batched_march_lookup(int shape, int r, int levels) {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// The branches of a batch: the LDS-resident grids, each class's one-workgroup grids, and each class's
+// passes on either engine.
+constexpr int BRANCHES = 19;
+
+// Each branch's stream and the event that joins it, made when the branch is first used and kept as long as
+// the batch.  (A hipGraph per batch, captured from such streams and made again whenever a class changed,
+// ended the process in a host segmentation fault now and then, three times on record, each in a run that
+// captured, instantiated and destroyed many of them; the cause was not found, so nothing is captured.)
+struct Branches {
+    hipStream_t side[BRANCHES] = {};
+    hipEvent_t fork = nullptr, join[BRANCHES] = {};
+    bool make(int i) {
+        return (fork || hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess) &&
+               (side[i] || hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking) == hipSuccess) &&
+               (join[i] || hipEventCreateWithFlags(&join[i], hipEventDisableTiming) == hipSuccess);
+    }
+    ~Branches() {
+        for (int i = 0; i < BRANCHES; ++i)
+            if (side[i]) (void)hipStreamSynchronize(side[i]);
+        for (int i = 0; i < BRANCHES; ++i) {
+            if (join[i]) (void)hipEventDestroy(join[i]);
+            if (side[i]) (void)hipStreamDestroy(side[i]);
+        }
+        if (fork) (void)hipEventDestroy(fork);
+    }
+};
 
 }  // namespace
 
@@ -183,7 +209,8 @@ struct st_batch {
     size_t off_desc, off_res, off_order[12], off_prefix[12], off_fields, ws_bytes;  // tables: march, then tile
     std::vector<size_t> field_off;     // per grid: workspace offset of its ping-pong field (0 = none)
     size_t lds_res;
-    // staging + graph
+    Branches branches;  // ST_FLAG_GRAPH only
+    // staging
     void* pinned;
     size_t pinned_bytes;
     hipEvent_t staged;
@@ -191,8 +218,6 @@ struct st_batch {
     std::vector<const void*> last_in;
     std::vector<void*> last_out;
     void* last_ws;
-    hipGraphExec_t exec;
-    void* g_ws;
 };
 
 namespace {
@@ -447,8 +472,6 @@ extern "C" int stencil_batch_create(st_batch** out, int n, st_plan* const* plans
     B->staged = nullptr;
     B->staged_valid = false;
     B->last_ws = nullptr;
-    B->exec = nullptr;
-    B->g_ws = nullptr;
     *out = B;
     return ST_OK;
 }
@@ -459,11 +482,6 @@ extern "C" int stencil_batch_workspace_bytes(const st_batch* batch, size_t* byte
     return ST_OK;
 }
 
-static void drop_exec(st_batch* B) {
-    if (B->exec) (void)hipGraphExecDestroy(B->exec);
-    B->exec = nullptr;
-}
-
 extern "C" int stencil_batch_destroy(st_batch* batch) {
     if (!batch) return ST_OK;
     if (batch->staged) {
@@ -471,7 +489,6 @@ extern "C" int stencil_batch_destroy(st_batch* batch) {
         (void)hipEventDestroy(batch->staged);
     }
     if (batch->pinned) (void)hipHostFree(batch->pinned);
-    drop_exec(batch);
     delete batch;
     return ST_OK;
 }
@@ -527,9 +544,6 @@ static int enqueue_whole(st_batch* B, int c, char* ws, hipStream_t s) {
     return ST_OK;
 }
 
-// The branches of a captured batch: the LDS-resident grids, each class's one-workgroup grids, and each
-// class's passes on either engine.  Each has a stream and an event that joins it.
-constexpr int BRANCHES = 19;
 static bool branch_used(const st_batch* B, int i) {
     if (i == 0) return B->n_lds > 0;
     return i <= 6 ? B->whole_n[i - 1] > 0 : !passes_of(B, i - 7).order.empty();
@@ -545,44 +559,45 @@ static int enqueue_branch(st_batch* B, int i, char* ws, hipStream_t s) {
     return ST_OK;
 }
 
-// The branches' streams and events.
-struct Branches {
-    hipStream_t side[BRANCHES] = {};
-    hipEvent_t fork = nullptr, join[BRANCHES] = {};
-    bool create(const st_batch* B, bool all) {
-        bool ok = hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess;
-        for (int i = 0; i < BRANCHES && ok; ++i)
-            ok = (!all && !branch_used(B, i)) || (hipStreamCreateWithFlags(&side[i], hipStreamNonBlocking) == hipSuccess &&
-                                                  hipEventCreateWithFlags(&join[i], hipEventDisableTiming) == hipSuccess);
-        return ok;
+// Enqueue the batch's kernels: with ST_FLAG_GRAPH, where there is more than one branch, each on its own
+// stream forked from and joined into `s`.  A caller that captures `s` gets them one after another.
+static int enqueue_batch(st_batch* B, char* ws, hipStream_t s) {
+    int used = 0;
+    for (int i = 0; i < BRANCHES; ++i) used += branch_used(B, i);
+    bool fork = (B->flags & ST_FLAG_GRAPH) && used > 1;
+    if (fork) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &st) != hipSuccess) clear_stale_error();
+        fork = st == hipStreamCaptureStatusNone;
     }
-    ~Branches() {
-        if (fork) (void)hipEventDestroy(fork);
-        for (int i = 0; i < BRANCHES; ++i) {
-            if (join[i]) (void)hipEventDestroy(join[i]);
-            if (side[i]) (void)hipStreamDestroy(side[i]);
-        }
-    }
-};
-
-// Enqueue the batch's kernels on `s`, or each branch on its own stream forked from and joined into `s`.
-static int enqueue_batch(st_batch* B, char* ws, hipStream_t s, const Branches* br) {
-    if (br) ST_HIP_CHECK(hipEventRecord(br->fork, s));
-    for (int i = 0; i < BRANCHES; ++i) {
-        if (!branch_used(B, i)) continue;
-        if (br) ST_HIP_CHECK(hipStreamWaitEvent(br->side[i], br->fork, 0));
-        if (int rc = enqueue_branch(B, i, ws, br ? br->side[i] : s)) return rc;
-        if (br) ST_HIP_CHECK(hipEventRecord(br->join[i], br->side[i]));
-    }
-    if (br)
+    Branches& br = B->branches;
+    if (fork) {
         for (int i = 0; i < BRANCHES; ++i)
-            if (branch_used(B, i)) ST_HIP_CHECK(hipStreamWaitEvent(s, br->join[i], 0));
-    return ST_OK;
+            if (branch_used(B, i) && !br.make(i)) return fail(ST_EHIP, "stream/event creation failed");
+        ST_HIP_CHECK(hipEventRecord(br.fork, s));
+    }
+    // A failed branch ends the loop, but what was enqueued before it is joined all the same: the caller's
+    // stream is the only one that the caller can wait for.
+    int rc = ST_OK;
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < BRANCHES && !rc && e == hipSuccess; ++i) {
+        if (!branch_used(B, i)) continue;
+        if (fork && (e = hipStreamWaitEvent(br.side[i], br.fork, 0)) != hipSuccess) break;
+        rc = enqueue_branch(B, i, ws, fork ? br.side[i] : s);
+        if (!fork) continue;
+        e = hipEventRecord(br.join[i], br.side[i]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(s, br.join[i], 0);
+        if (e != hipSuccess) (void)hipStreamSynchronize(br.side[i]);
+    }
+    if (!rc && e != hipSuccess) {
+        clear_stale_error();
+        rc = fail(ST_EHIP, std::string("fork/join of the batch's streams: ") + hipGetErrorString(e));
+    }
+    return rc;
 }
 
-// stencil_run_batched; `br`: on these streams, whatever the batch's flags say (the autotuner).
-static int run_batched(st_batch* B, const void* const* ins, void* const* outs, void* workspace, size_t ws_bytes,
-                       void* stream, const Branches* br) {
+extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* const* outs, void* workspace,
+                                   size_t ws_bytes, void* stream) {
     if (!B || !ins || !outs) return fail(ST_EINVAL, "NULL argument");
     if (!workspace || ws_bytes < B->ws_bytes) return fail(ST_ENOWS, "workspace too small");
     for (int g = 0; g < B->n; ++g) {
@@ -629,44 +644,7 @@ static int run_batched(st_batch* B, const void* const* ins, void* const* outs, v
     for (int g : B->zero_steps)
         ST_HIP_CHECK(hipMemcpyAsync(outs[g], ins[g], size_t(B->desc[g].rows * B->desc[g].cols) * sizeof(float),
                                     hipMemcpyDeviceToDevice, s));
-    bool any = false;
-    for (int i = 0; i < BRANCHES; ++i) any = any || branch_used(B, i);
-    if (!any) return ST_OK;
-    if (br || !(B->flags & ST_FLAG_GRAPH)) return enqueue_batch(B, ws, s, br);
-    if (!(B->exec && B->g_ws == workspace)) {
-        drop_exec(B);
-        // capture: every branch forked from and joined back into the main stream
-        hipStream_t cap = nullptr;
-        Branches branches;
-        int rc = ST_OK;
-        hipGraph_t graph = nullptr;
-        const bool made = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) == hipSuccess && branches.create(B, false);
-        if (!made) {
-            rc = fail(ST_EHIP, "stream/event creation for graph capture failed");
-        } else if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-            rc = fail(ST_EHIP, "hipStreamBeginCapture failed");
-        } else {
-            rc = enqueue_batch(B, ws, cap, &branches);
-            const hipError_t e = hipStreamEndCapture(cap, &graph);
-            if (!rc && e != hipSuccess) rc = fail(ST_EHIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e));
-        }
-        if (!rc) {
-            const hipError_t e2 = hipGraphInstantiate(&B->exec, graph, nullptr, nullptr, 0);
-            if (e2 != hipSuccess) rc = fail(ST_EHIP, std::string("hipGraphInstantiate: ") + hipGetErrorString(e2));
-        }
-        if (graph) (void)hipGraphDestroy(graph);
-        if (cap) (void)hipStreamDestroy(cap);
-        (void)hipGetLastError();
-        if (rc) return rc;
-        B->g_ws = workspace;
-    }
-    ST_HIP_CHECK(hipGraphLaunch(B->exec, s));
-    return ST_OK;
-}
-
-extern "C" int stencil_run_batched(st_batch* B, const void* const* ins, void* const* outs, void* workspace,
-                                   size_t ws_bytes, void* stream) {
-    return run_batched(B, ins, outs, workspace, ws_bytes, stream, nullptr);
+    return enqueue_batch(B, ws, s);
 }
 
 extern "C" int stencil_batch_set_class(st_batch* B, int shape, int radius, int engine, int depth) {
@@ -680,7 +658,6 @@ extern "C" int stencil_batch_set_class(st_batch* B, int shape, int radius, int e
     B->depth[c] = depth;
     build_passes(B);
     B->staged_valid = false;
-    drop_exec(B);
     return ST_OK;
 }
 
@@ -692,7 +669,6 @@ extern "C" int stencil_batch_set_segment(st_batch* B, int shape, int radius, int
     B->seg_min[c] = min_rows;
     build_passes(B);
     B->staged_valid = false;
-    drop_exec(B);
     return ST_OK;
 }
 
@@ -706,8 +682,8 @@ extern "C" int stencil_batch_get_segment(const st_batch* B, int shape, int radiu
 }
 
 // Coordinate descent over the stencil classes (shape, radius) of the non-resident grids: for each
-// class in turn, time the whole batch (for a graph on the streams of its branches: they share the
-// device, so what is fastest alone need not be) with every candidate engine and depth -- register
+// class in turn, time the whole batch (branches that run beside each other share the device, so what is
+// fastest alone need not be) with every candidate engine and depth -- register
 // tiles with the class's depth capped at 1, 2, 3, 4, 6, 8, 12 or 16, or marching with 1 .. the
 // deepest its radius allows, each marching depth with the default segments and with those that make
 // at most one, two, three or four tasks per SIMD (a pass waits for its busiest SIMD) --
@@ -727,10 +703,8 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
         deepest[c] = std::max(deepest[c], B->tb_max[g]);
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    Branches branches;
     int rc = ST_OK;
-    if ((B->flags & ST_FLAG_GRAPH) && !branches.create(B, true)) rc = fail(ST_EHIP, "stream/event creation failed");
-    else if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = fail(ST_EHIP, "hipEventCreate");
+    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) rc = fail(ST_EHIP, "hipEventCreate");
     // fill: marching segments such that the class's tasks are at most that many wavefronts a SIMD
     auto apply = [&](int c, int engine, int depth, int fill) {
         B->engine[c] = engine;
@@ -757,12 +731,11 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
     };
     // the fastest of `runs` runs after one that warms up and stages the tables
     auto timed = [&](int runs, float* ms) -> int {
-        const Branches* br = B->flags & ST_FLAG_GRAPH ? &branches : nullptr;
-        if (int r = run_batched(B, ins, outs, workspace, ws_bytes, stream, br)) return r;
+        if (int r = stencil_run_batched(B, ins, outs, workspace, ws_bytes, stream)) return r;
         *ms = 1e30f;
         for (int i = 0; i < runs; ++i) {
             if (hipEventRecord(e0, s) != hipSuccess) return fail(ST_EHIP, "hipEventRecord");
-            if (int r = run_batched(B, ins, outs, workspace, ws_bytes, stream, br)) return r;
+            if (int r = stencil_run_batched(B, ins, outs, workspace, ws_bytes, stream)) return r;
             float t = 0.0f;
             if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&t, e0, e1) != hipSuccess)
@@ -801,6 +774,5 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
         }
     if (e0) (void)hipEventDestroy(e0);
     if (e1) (void)hipEventDestroy(e1);
-    drop_exec(B);  // it holds the old pass structure
     return rc;
 }

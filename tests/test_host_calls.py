@@ -1,0 +1,151 @@
+"""What the library asks of the HIP runtime, on a host without a GPU: each test runs the library's host side
+in a process of its own on a runtime that only writes the calls down (hip_stub.cpp).  Run as a script, this
+file is that process; the tests read its log."""
+import ctypes
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = "/opt/rocm/include"
+CALLER = 1000001  # the caller's stream
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(ROCM), reason="needs g++ and HIP headers")
+
+
+# ---- in the process of its own ----------------------------------------------------------------------------
+class Host:
+    """The library on the stub, with its log."""
+
+    def __init__(self, stub):
+        self.stub = ctypes.CDLL(stub, mode=ctypes.RTLD_GLOBAL)
+        self.stub.stub_log.restype = ctypes.c_char_p
+        sys.modules["torch"] = None  # its own runtime stays out of this process
+        sys.path.insert(0, os.path.dirname(HERE))
+        import paper_2605_07954_amd as st
+        self.st, self.lib = st, st.lib()
+
+    def log(self):
+        text = self.stub.stub_log().decode()
+        self.stub.stub_clear()
+        return [line.split(" ") for line in text.splitlines()]
+
+    def weights(self, shape, r):
+        k = 2 * r + 1
+        w = np.full((k, k), 1.0 / (k * k), np.float32)
+        if shape == "star":
+            m = np.zeros((k, k), bool)
+            m[r, :] = m[:, r] = True
+            w[~m] = 0.0
+        return w
+
+    def fail(self, what, after):
+        self.stub.stub_fail(what.encode(), after)
+
+
+def case_batch(h, flags, fail=None, capturing=False):
+    """Two runs of a batch of every kind of branch, a class changed by hand, a third run; its end."""
+    grids = [(300, 700, "star", 1), (300, 700, "box", 2), (200, 90, "star", 1), (40, 50, "star", 3), (30, 40, "box", 1),
+             (5, 900, "star", 2)]
+    plans = [h.st.stencil_plan(a, c, r, h.weights(s, r), 0.0, "f32", 0) for a, c, s, r in grids]
+    batch = h.st.stencil_batch_create(plans, [9] * len(grids), flags)
+    fields = [[np.zeros((a, c), np.float32) for a, c, _, _ in grids] for _ in range(2)]
+    ins, outs = ((ctypes.c_void_p * len(grids))(*[f.ctypes.data for f in fs]) for fs in fields)
+    ws = np.zeros(h.st.stencil_batch_workspace_bytes(batch), np.uint8)
+
+    def run():
+        rc = h.lib.stencil_run_batched(batch, ins, outs, ws.ctypes.data, ws.nbytes, CALLER)
+        return rc, h.log()
+
+    if capturing:
+        h.stub.stub_capturing(ctypes.c_void_p(CALLER))
+    out = {"runs": [run(), run()]}
+    h.st.stencil_batch_set_class(batch, "star", 1, "march", 4)
+    if fail:
+        h.fail(*fail)
+    out["runs"].append(run())
+    h.st.stencil_batch_destroy(batch)
+    out["end"] = h.log()
+    return out
+
+
+CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
+
+
+# ---- the tests --------------------------------------------------------------------------------------------
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    r = subprocess.run(["g++", "-shared", "-fPIC", "-O1", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I", ROCM,
+                        os.path.join(HERE, "hip_stub.cpp"), "-o", so], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    return so
+
+
+def ask(stub, case, **kw):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), stub, case, json.dumps(kw)], capture_output=True,
+                       text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return json.loads(r.stdout)
+
+
+def unjoined(log):
+    """Streams that hold a launch which the caller's stream does not wait for by the end of the log."""
+    dirty, at = set(), {}
+    for c in log:
+        if c[0] == "launch" and c[-1] != str(CALLER):
+            dirty.add(c[-1])
+        elif c[0] == "record":
+            at[c[1]] = c[2]
+        elif c[0] == "wait" and c[1] == str(CALLER):
+            dirty.discard(at.get(c[2]))
+        elif c[0] == "sync":
+            dirty.discard(c[1])
+    return dirty
+
+
+def made(log, what):
+    return [c for c in log if c[0] == what]
+
+
+@pytest.mark.parametrize("flags", [0, 2])
+def test_batch_captures_nothing(stub, flags):
+    res = ask(stub, "batch", flags=flags)
+    whole = [c for _, log in res["runs"] for c in log] + res["end"]
+    assert all(rc == 0 for rc, _ in res["runs"])
+    for what in ("capture", "captured", "exec", "replay"):
+        assert not made(whole, what)
+    streams = {c[-1] for c in made(whole, "launch")}
+    assert (len(streams) > 3) if flags else streams == {str(CALLER)}
+    for _, log in res["runs"]:
+        assert made(log, "launch") and not unjoined(log)
+        assert not made(log, "stream-") and not made(log, "event-")
+    assert not made(res["runs"][1][1], "stream") and not made(res["runs"][1][1], "event")  # made once
+    # the end waits for each stream before it goes
+    gone = {c[1] for c in made(res["end"], "stream-")}
+    assert gone == {c[1] for c in made(whole, "stream")}
+    for s in gone:
+        assert res["end"].index(["sync", s]) < res["end"].index(["stream-", s])
+
+
+@pytest.mark.parametrize("what,after", [("launch", 0), ("launch", 2), ("launch", 6), ("wait", 3), ("wait", 4), ("stream", 0)])
+def test_batch_joins_what_a_failed_run_enqueued(stub, what, after):
+    res = ask(stub, "batch", flags=2, fail=[what, after])
+    rc, log = res["runs"][2]
+    assert rc == -4 and not unjoined(log)
+
+
+def test_batch_under_capture_stays_on_the_stream(stub):
+    res = ask(stub, "batch", flags=2, capturing=True)
+    for rc, log in res["runs"]:
+        assert rc == 0 and {c[-1] for c in made(log, "launch")} == {str(CALLER)}
+        assert not made(log, "wait") and not made(log, "stream")
+
+
+if __name__ == "__main__":
+    print(json.dumps(CASES[sys.argv[2]](Host(sys.argv[1]), **json.loads(sys.argv[3]))))
