@@ -415,11 +415,13 @@ int stencil_workspace_bytes(const st_plan* plan, int64_t steps, size_t* bytes) {
     return ST_OK;
 }
 
-static bool overlap(const void* a, const void* b, size_t n) {
+// Whether a's n bytes and b's m bytes share one.
+static bool overlap(const void* a, size_t n, const void* b, size_t m) {
     const char* x = static_cast<const char*>(a);
     const char* y = static_cast<const char*>(b);
-    return x < y + n && y < x + n;
+    return x < y + m && y < x + n;
 }
+static bool overlap(const void* a, const void* b, size_t n) { return overlap(a, n, b, n); }
 
 // Enqueue all passes of a run on `s`.
 static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa, int64_t steps, void* ws,
@@ -848,7 +850,7 @@ int stencil_solve(st_plan* plan, const void* in, void* out, int64_t max_steps, i
         ST_LAUNCH_CHECK("solve_reset");
         plan->stop = &rec->stop;
         // (where in or out lies in the workspace, stencil_run decides)
-        const bool apart = !overlap(workspace, in, need) && !overlap(workspace, out, need);
+        const bool apart = !overlap(workspace, need, in, bytes) && !overlap(workspace, need, out, bytes);
         // (a marching plan's tile was never chosen: its last passes take the one that is fastest on large
         // grids; star r = 1 at 4096^2, tb 7, per check of 20 steps: 64 x 64 123 us, 128 x 64 109 us)
         if (is_march(plan->variant)) {

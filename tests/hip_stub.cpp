@@ -64,7 +64,13 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
     char* d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
     std::string n = d ? d : name;
     std::free(d);
-    n = n.substr(0, n.rfind('('));  // arguments
+    size_t open = n.size();  // of the argument list
+    for (int depth = 0; open > 0;) {
+        --open;
+        depth += (n[open] == ')') - (n[open] == '(');
+        if (depth <= 0) break;
+    }
+    n.resize(open);
     if (n.compare(0, 5, "void ") == 0) n = n.substr(5);
     for (const char* ns : {"st::", "(anonymous namespace)::"})
         for (size_t p; (p = n.find(ns)) != std::string::npos;) n.erase(p, std::strlen(ns));

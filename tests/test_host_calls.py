@@ -74,6 +74,19 @@ def case_batch(h, flags, fail=None, capturing=False):
     return out
 
 
+def case_solve(h, first, gap=0):
+    """A solve whose workspace lies right above its fields or right below them (or over the end of `out`)."""
+    rows, cols = 200, 256
+    plan = h.st.stencil_plan(rows, cols, 1, h.weights("star", 1), 0.0, "f32", 0)
+    field, need = rows * cols * 4, h.st.stencil_solve_ws_bytes(plan, 8)
+    mem = np.zeros(2 * field + need + 256, np.uint8)
+    base = mem.ctypes.data + -mem.ctypes.data % 256
+    ws, x = (base, base + (need + 255) // 256 * 256) if first == "workspace" else (base + 2 * field - gap, base)
+    steps, rel = ctypes.c_int64(), ctypes.c_double()
+    rc = h.lib.stencil_solve(plan, x, x + field, 16, 8, 0.0, ctypes.byref(steps), ctypes.byref(rel), ws, need, CALLER)
+    return {"rc": rc, "kernels": [c[1].split("<")[0] for c in made(h.log(), "launch")]}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -145,6 +158,14 @@ def test_batch_under_capture_stays_on_the_stream(stub):
     for rc, log in res["runs"]:
         assert rc == 0 and {c[-1] for c in made(log, "launch")} == {str(CALLER)}
         assert not made(log, "wait") and not made(log, "stream")
+
+
+def test_solve_does_not_depend_on_where_its_buffers_lie(stub):
+    above, below = ask(stub, "solve", first="fields"), ask(stub, "solve", first="workspace")
+    assert above["kernels"].count("sweep_block_sums") == 2  # the residual comes from each interval's last pass
+    assert above == below
+    # a workspace that overlaps `out` is refused, as stencil_run refuses it
+    assert ask(stub, "solve", first="fields", gap=256)["rc"] == -2
 
 
 if __name__ == "__main__":
