@@ -6,14 +6,14 @@
 //
 // Stars, and boxes of radius 1, run several levels per pass on register tiles (sweep3d_block.h).
 //
-// Boxes of radius 2 (125 taps: their weights alone fill the scalar registers) run one level per pass on
-// LDS tiles.  One workgroup owns a TY x TX column of the grid and marches along z over a segment of planes:
+// Boxes of radius 2 (125 taps: their weights alone fill the scalar registers), and single levels of large
+// FP32 stars (ring_pass), run on LDS tiles, one level per pass.  One workgroup owns a TY x TX column of the grid and marches along z over a segment of planes:
 // the 2r + 1 input planes of the current output plane sit in an LDS ring, each with its r-deep
 // (y, x) halo; every iteration stores a plane fetched earlier into the slot the oldest plane leaves,
 // starts fetching the plane after next into registers (two register sets, so two planes are in
 // flight), and computes its cells of the output plane from the ring meanwhile.  A wavefront covers one row of the
 // tile (64 consecutive columns), so loads and stores are coalesced and LDS reads of one tap hit 64
-// consecutive words.  Bound by LDS: one read per tap and cell.
+// consecutive words.  Boxes are bound by LDS (one read per tap and cell), stars by HBM.
 #include <algorithm>
 
 #include "internal.h"
@@ -72,7 +72,7 @@ __device__ __forceinline__ void store_plane(float* slot, const PlaneRegs<R>& p) 
     }
 }
 
-template <int S, int R>
+template <int S, int R, int SHAPE>
 __global__ __launch_bounds__(NT3) void sweep3d(Args3 a) {
     constexpr int K = 2 * R + 1;
     using P = PlaneRegs<R>;
@@ -110,7 +110,8 @@ __global__ __launch_bounds__(NT3) void sweep3d(Args3 a) {
                 for (int dy = -R; dy <= R; ++dy)
 #pragma unroll
                     for (int dx = -R; dx <= R; ++dx) {
-                        if (dz == 0 && dy == 0 && dx == 0) continue;
+                        const int nz = (dz != 0) + (dy != 0) + (dx != 0);
+                        if (nz == 0 || (SHAPE == SHAPE_STAR && nz > 1)) continue;
                         acc = __builtin_fmaf(a.w[((dz + R) * K + dy + R) * K + dx + R], pl[o + dy * PW + dx], acc);
                     }
             }
@@ -133,13 +134,26 @@ __global__ __launch_bounds__(NT3) void sweep3d(Args3 a) {
     }
 }
 
-// The kernel of boxes of radius 2 by storage type.
+// The kernels on LDS tiles: boxes of radius 2, FP32 stars.
 using Fn3 = void (*)(Args3);
-Fn3 box2_lookup(int storage) {
-    if (storage == ST_F32) return sweep3d<ST_F32, 2>;
-    if (storage == ST_BF16) return sweep3d<ST_BF16, 2>;
-    if (storage == ST_F16) return sweep3d<ST_F16, 2>;
+Fn3 ring_lookup(int shape, int r, int storage) {
+    if (shape == SHAPE_STAR) return storage != ST_F32 ? nullptr : r == 1 ? sweep3d<ST_F32, 1, SHAPE_STAR> : sweep3d<ST_F32, 2, SHAPE_STAR>;
+    if (r != 2) return nullptr;
+    if (storage == ST_F32) return sweep3d<ST_F32, 2, SHAPE_BOX>;
+    if (storage == ST_BF16) return sweep3d<ST_BF16, 2, SHAPE_BOX>;
+    if (storage == ST_F16) return sweep3d<ST_F16, 2, SHAPE_BOX>;
     return nullptr;
+}
+
+// Single levels of an FP32 star that run on LDS tiles: their 64 columns start on cache lines where the rows
+// do, while a register tile stores 64 - 2r columns and so parts of lines at every tile's sides.  The widths
+// (a multiple of 16) and sizes where that is faster; us a step, LDS tiles / register tiles.  r = 1: 256^3
+// 35 / 36, 400^3 145 / 154, 512^3 241 / 331, 4 x 8192^2 502 / 611; at other widths 300^3 56 / 52, 450^3
+// 236 / 210.  r = 2, larger halos to load, from fields beyond the 256 MB cache on: 400^3 197 / 163; 512^3
+// 266 / 348, 640^3 680 / 645, 64 x 2048^2 516 / 658.  16-bit fields: 512^3 391 / 208.
+bool ring_pass(const st_plan* p) {
+    return p->shape == SHAPE_STAR && p->storage == ST_F32 && p->cols % 16 == 0 &&
+           field_cells(p) >= (p->radius == 1 ? int64_t(1) << 24 : int64_t(1) << 26);
 }
 
 // Stars and boxes of radius 1 on register tiles (sweep3d_block.h): one column per lane, four rows per
@@ -203,7 +217,8 @@ int cover3(const st_plan* p, int levels, Cover3* c) {
         }
     }
     const double bytes = 2.0 * double(field_cells(p)) * double(elem_size(p->storage));
-    c->cost = std::max(best, bytes / 4.4e6 / 0.235 * (bytes > 2e8 ? 1.0 : 1.0 / 3.0)) + 15.0;
+    const double rate = levels == 1 && ring_pass(p) ? 4.4e6 : 3.5e6;  // bytes per us
+    c->cost = std::max(best, bytes / rate / 0.235 * (bytes > 2e8 ? 1.0 : 1.0 / 3.0)) + 15.0;
     return ST_OK;
 }
 
@@ -272,8 +287,8 @@ int max_levels_3d(st_plan* p) {
 }
 
 int launch_3d(const st_plan* p, const void* src, void* dst, int levels, hipStream_t s) {
-    if (on_tiles(p)) return launch_tiles(p, src, dst, levels, s);
-    Fn3 fn = box2_lookup(p->storage);
+    if (on_tiles(p) && !(levels == 1 && ring_pass(p))) return launch_tiles(p, src, dst, levels, s);
+    Fn3 fn = ring_lookup(p->shape, p->radius, p->storage);
     if (!fn) return fail(ST_EUNSUPPORTED, "no 3D kernel for this storage/shape/radius");
     Args3 a;
     a.src = src;

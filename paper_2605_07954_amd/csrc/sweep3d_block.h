@@ -10,11 +10,11 @@
 // plane is loaded, raw, while this one computes.  The pass stores the tile without its outer R T rows
 // and columns; a segment recomputes R T planes at either end.
 //
-// One level per pass is bound by HBM (8 bytes and 4.4 TB/s per update: 560 GStencil/s for the 7-point star
-// at 512^3, the kernel this replaced); T levels divide the bytes by T.  Measured there at T = 1 .. 7:
-// 424, 900, 1216, 1468, 1590, 1646, 1331 GStencil/s -- up to T = 2 bound by HBM, from T = 4 on by the vector
-// ALU, whose work grows with the tile's margin (64 x 64 cells for (64 - 2T)^2), and at T = 7 by spilled
-// registers.  Sixteen wavefronts of four rows beat eight of eight (1193 at T = 3) and 128-column tiles
+// One level per pass is bound by HBM (8 bytes per update; LDS tiles of whole cache lines reach 4.4 TB/s,
+// 560 GStencil/s for the 7-point star at 512^3, and run single levels of large FP32 stars); T levels divide
+// the bytes by T.  Measured there at T = 1 .. 7: 424, 900, 1216, 1468, 1590, 1646, 1331 GStencil/s -- 3.4 to
+// 3.6 TB/s up to T = 2; the work grows with the tile's margin (64 x 64 cells for (64 - 2T)^2), and T = 7
+// spills registers.  Sixteen wavefronts of four rows beat eight of eight (1193 at T = 3) and 128-column tiles
 // (997), which leave fewer wavefronts to a SIMD.
 #pragma once
 

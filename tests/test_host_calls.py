@@ -87,6 +87,17 @@ def case_solve(h, first, gap=0):
     return {"rc": rc, "kernels": [c[1].split("<")[0] for c in made(h.log(), "launch")]}
 
 
+def case_run3d(h, dims, shape, r, storage, steps):
+    """The kernels of a 3D run (on made-up device addresses)."""
+    k = 2 * r + 1
+    w = np.full((k, k, k), 0.01, np.float32)
+    if shape == "star":
+        w[(np.indices((k, k, k)) != r).sum(0) > 1] = 0.0
+    plan = h.st.stencil_plan3d(*dims, r, w, 0.0, storage, 0)
+    rc = h.lib.stencil_run(plan, 1 << 40, 2 << 40, steps, 3 << 40, h.st.stencil_workspace_bytes(plan, steps), CALLER)
+    return {"rc": rc, "launches": made(h.log(), "launch")}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -166,6 +177,19 @@ def test_solve_does_not_depend_on_where_its_buffers_lie(stub):
     assert above == below
     # a workspace that overlaps `out` is refused, as stencil_run refuses it
     assert ask(stub, "solve", first="fields", gap=256)["rc"] == -2
+
+
+@pytest.mark.parametrize("dims,shape,r,storage,ring", [
+    ((512, 512, 512), "star", 1, "f32", True), ((256, 256, 256), "star", 1, "f32", True), ((512, 512, 512), "star", 2, "f32", True),
+    ((300, 300, 300), "star", 1, "f32", False), ((128, 128, 128), "star", 1, "f32", False), ((400, 400, 400), "star", 2, "f32", False),
+    ((512, 512, 512), "star", 1, "bf16", False), ((512, 512, 512), "box", 1, "f32", False)])
+def test_3d_single_levels(stub, dims, shape, r, storage, ring):
+    """One level of a large FP32 star goes where it is fastest; runs of several levels stay on register tiles."""
+    one = ask(stub, "run3d", dims=dims, shape=shape, r=r, storage=storage, steps=1)
+    assert one["rc"] == 0 and len(one["launches"]) == 1
+    assert one["launches"][0][1].startswith("sweep3d<") == ring
+    for c in ask(stub, "run3d", dims=dims, shape=shape, r=r, storage=storage, steps=8)["launches"]:
+        assert c[1].startswith("sweep3d_block")
 
 
 if __name__ == "__main__":
