@@ -992,50 +992,79 @@ __global__ void adam_kernel(float* p, const float* g, float* m, float* v, int n,
 // training-data synthesis and crops
 // ---------------------------------------------------------------------------
 constexpr int NU = 16, NK = 8;
-constexpr int SY = 64, SX = 256;  // cells per synthesis block: a column of SY cells per thread
 
 // Both fields are separable per mode: sin(a i) sin(b j) for u0, and
-// cos(A_j + B_i) = cos A_j cos B_i - sin A_j sin B_i for kappa.  A thread keeps the factors of its column
-// in registers, a block those of its rows in LDS (FP64 trigonometry, rounded to FP32), and the cells are
-// combined with FMAs.  The trigonometry binds: 32 factors per column and 32 per row, 0.6 per cell of a
-// 64 x 256 tile (16 x 64 tiles: 2.5 per cell, and four LDS reads per mode and cell; 107 us for eight
-// 1024^2 pairs against 34).
-__global__ __launch_bounds__(SX) void synth_kernel(const float* coef, int n, int rows, int cols, float* u0,
-                                                   float* kappa) {
+// cos(A_j + B_i) = cos A_j cos B_i - sin A_j sin B_i for kappa.  A workgroup takes SY rows x 256 / G columns,
+// each thread every G-th row of one column: a thread keeps the factors of its column in registers, the
+// workgroup those of its rows in LDS (FP64 trigonometry, rounded to FP32), and the cells are combined with
+// FMAs.  The trigonometry binds: 32 factors per column and 32 per row.  G = 1 on 64 x 256 tiles computes 0.6
+// of them per cell, but a thread 40 one after another, which takes 20 us however small the field; G = 4 on
+// 16 x 64 tiles shares a column's among four threads, 10 each, 2.5 per cell.  us, G = 4 / G = 1: 100^2 5.7 / 21,
+// 1024^2 11 / 25, 8 x 512^2 19 / 25, 4 x 1024^2 32 / 26, 8 x 1024^2 58 / 31 (100 before either).
+template <int SY, int G>
+__global__ __launch_bounds__(256) void synth_kernel(const float* coef, int n, int rows, int cols, float* u0,
+                                                    float* kappa) {
+    constexpr int SX = 256 / G;
     __shared__ __align__(16) float rowf[SY][NU + 2 * NK];  // amp sin, then cos and sin of the kappa modes
     const int bx = (cols + SX - 1) / SX, by = (rows + SY - 1) / SY;
     const int t = blockIdx.x / (bx * by), r = blockIdx.x % (bx * by);
-    const int i0 = (r / bx) * SY, j = (r % bx) * SX + int(threadIdx.x);
+    const int i0 = (r / bx) * SY, jc = int(threadIdx.x) % SX, part = int(threadIdx.x) / SX, j = (r % bx) * SX + jc;
     const float* c = coef + int64_t(t) * 4 * (NU + NK);
     const double pi = 3.14159265358979323846;
-    for (int k = threadIdx.x; k < NU * SY; k += SX) {
+    for (int k = threadIdx.x; k < NU * SY; k += 256) {
         const int q = k / NU, m = k % NU;
         rowf[q][m] = c[4 * m + 2] * float(sin(double(c[4 * m]) * pi * (i0 + q + 1) / (rows + 1)));
     }
-    for (int k = threadIdx.x; k < NK * SY; k += SX) {
+    for (int k = threadIdx.x; k < NK * SY; k += 256) {
         const int q = k / NK, m = k % NK;
         const double B = 2.0 * pi * double(c[4 * (NU + m) + 1]) * double(i0 + q) / rows;
         rowf[q][NU + m] = float(cos(B));
         rowf[q][NU + NK + m] = float(sin(B));
     }
     float tu[NU], ca[NK], sa[NK], bamp[NK];
+    auto u_factor = [&](int m) { return float(sin(double(c[4 * m + 1]) * pi * (j + 1) / (cols + 1))); };
+    auto k_phase = [&](int m) { return 2.0 * pi * double(c[4 * (NU + m)]) * double(j) / cols + double(c[4 * (NU + m) + 3]); };
+    if constexpr (G == 1) {
 #pragma unroll
-    for (int m = 0; m < NU; ++m) tu[m] = float(sin(double(c[4 * m + 1]) * pi * (j + 1) / (cols + 1)));
+        for (int m = 0; m < NU; ++m) tu[m] = u_factor(m);
+#pragma unroll
+        for (int m = 0; m < NK; ++m) {
+            const double A = k_phase(m);
+            ca[m] = float(cos(A));
+            sa[m] = float(sin(A));
+        }
+        __syncthreads();
+    } else {
+        __shared__ float colf[NU + 2 * NK][SX];
+        static_assert(NU % G == 0 && NK % G == 0, "modes in equal parts");
+#pragma unroll
+        for (int m = 0; m < NU / G; ++m) colf[part * (NU / G) + m][jc] = u_factor(part * (NU / G) + m);
+#pragma unroll
+        for (int m = 0; m < NK / G; ++m) {
+            const int k = part * (NK / G) + m;
+            const double A = k_phase(k);
+            colf[NU + k][jc] = float(cos(A));
+            colf[NU + NK + k][jc] = float(sin(A));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < NU; ++m) tu[m] = colf[m][jc];
+#pragma unroll
+        for (int m = 0; m < NK; ++m) {
+            ca[m] = colf[NU + m][jc];
+            sa[m] = colf[NU + NK + m][jc];
+        }
+    }
     double nrm = 0.0;
 #pragma unroll
     for (int m = 0; m < NK; ++m) {
-        const float* cm = c + 4 * (NU + m);
-        const double A = 2.0 * pi * double(cm[0]) * double(j) / cols + double(cm[3]);
-        ca[m] = float(cos(A));
-        sa[m] = float(sin(A));
-        bamp[m] = cm[2];
-        nrm += fabs(double(cm[2]));
+        bamp[m] = c[4 * (NU + m) + 2];
+        nrm += fabs(double(bamp[m]));
     }
     const float binv = float(0.075 / fmax(nrm, 1e-30));
-    __syncthreads();
     if (j >= cols) return;
     const int nq = rows - i0 < SY ? rows - i0 : SY;
-    for (int q = 0; q < nq; ++q) {
+    for (int q = part; q < nq; q += G) {
         float u = 0.0f, g = 0.0f;
 #pragma unroll
         for (int m = 0; m < NU; ++m) u = __builtin_fmaf(rowf[q][m], tu[m], u);
@@ -1562,10 +1591,12 @@ int surrogate_synth_fields(const float* coef, int n, int64_t rows, int64_t cols,
                            void* stream) {
     if (!coef || !u0_out || !kappa_out) return fail(ST_EINVAL, "NULL argument");
     if (n < 1 || rows < 1 || cols < 1 || int64_t(n) * rows * cols > (int64_t(1) << 33)) return fail(ST_EINVAL, "bad sizes");
-    const int64_t blocks = int64_t(n) * ((rows + SY - 1) / SY) * ((cols + SX - 1) / SX);
+    auto blocks = [&](int64_t sy, int64_t sx) { return int64_t(n) * ((rows + sy - 1) / sy) * ((cols + sx - 1) / sx); };
+    const bool large = int64_t(n) * rows * cols >= 3000000;  // (see synth_kernel)
+    const int64_t grid = large ? blocks(64, 256) : blocks(16, 64);
     clear_stale_error();
-    hipLaunchKernelGGL(synth_kernel, dim3(unsigned(blocks)), dim3(SX), 0, static_cast<hipStream_t>(stream), coef, n,
-                       int(rows), int(cols), u0_out, kappa_out);
+    hipLaunchKernelGGL((large ? synth_kernel<64, 1> : synth_kernel<16, 4>), dim3(unsigned(grid)), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), coef, n, int(rows), int(cols), u0_out, kappa_out);
     ST_LAUNCH_CHECK("synth");
     return ST_OK;
 }

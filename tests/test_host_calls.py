@@ -98,6 +98,11 @@ def case_run3d(h, dims, shape, r, storage, steps):
     return {"rc": rc, "launches": made(h.log(), "launch")}
 
 
+def case_synth(h, n, rows, cols):
+    rc = h.lib.surrogate_synth_fields(1 << 40, n, rows, cols, 2 << 40, 3 << 40, CALLER)
+    return {"rc": rc, "launches": made(h.log(), "launch")}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -190,6 +195,14 @@ def test_3d_single_levels(stub, dims, shape, r, storage, ring):
     assert one["launches"][0][1].startswith("sweep3d<") == ring
     for c in ask(stub, "run3d", dims=dims, shape=shape, r=r, storage=storage, steps=8)["launches"]:
         assert c[1].startswith("sweep3d_block")
+
+
+@pytest.mark.parametrize("n,rows,cols,kernel,grid", [(1, 100, 100, "<16,4>", 14), (1, 1024, 1024, "<16,4>", 1024),
+                                                     (4, 1024, 1024, "<64,1>", 256)])
+def test_synthesis_tiles(stub, n, rows, cols, kernel, grid):
+    """Small fields share a column's factors among threads; a thread alone takes as long as a large field."""
+    res = ask(stub, "synth", n=n, rows=rows, cols=cols)
+    assert res["rc"] == 0 and res["launches"] == [["launch", "synth_kernel" + kernel, str(grid), "256", str(CALLER)]]
 
 
 if __name__ == "__main__":
