@@ -184,7 +184,7 @@ __device__ __forceinline__ TileAt tile_at(int64_t t, int64_t tiles_x, int64_t ro
 }
 
 // Register tiles: V columns per lane, RW rows per wavefront, NW wavefronts.  A plan's tile picks the one
-// of its size.  A pass whose margins would leave less than a quarter of that tile in either direction
+// of its size (pick).  A pass whose margins would leave less than a quarter of a tile in either direction
 // takes the last, whose 128 x 128 cells hold every depth a plan accepts (r tb <= 39).  Eight wavefronts of
 // eight rows beat sixteen of four on the same tile (star r = 1, 8192^2, tb 8: 3109 against 2756
 // GStencil/s): half the rows cross LDS, and two or three workgroups share a compute unit.
@@ -206,6 +206,35 @@ inline Cover cover(int def, int r, int levels, int64_t rows, int64_t cols) {
     if (out_rows(def) < 1 || out_cols(def) < 1) return Cover{-1, 0, 0};
     const int64_t tx = (cols + out_cols(def) - 1) / out_cols(def);
     return Cover{def, tx, tx * ((rows + out_rows(def) - 1) / out_rows(def))};
+}
+
+// The tile that a plan's pass runs on: the plan's own (`def`), unless its margins would leave less than
+// two fifths of its cells -- then the one of least estimated time, from the instructions that a wavefront
+// issues per level (`ops` a cell, a few per row, and the exchange) over the 1024 SIMDs, plus one workgroup's
+// own time.  Three passes at 2000^2, us, own tile / picked: box r = 4, 64 x 64, 6 levels (6 % kept)
+// 2193 / 555 (LDS tiles, whose halo lies around the tile, took 645); box r = 3, 64 x 64, 4 levels (39 %)
+// 206 / 173; star r = 4, 128 x 64, 4 levels (38 %) 94 / 88.  From two fifths up the own tile was never slower
+// than LDS tiles, and a plan's tile stays the plan's.
+inline Cover pick(int def, double ops, int r, int levels, int64_t rows, int64_t cols) {
+    const Cover own = cover(def, r, levels, rows, cols);
+    if (own.def == def) {
+        const Def& d = kDefs[def];
+        const double keep = double(d.nw * d.rw - 2 * r * levels) * (64 * d.v - 2 * margin_cols(r, levels, d.v));
+        if (keep >= 0.4 * d.nw * d.rw * 64 * d.v) return own;
+    }
+    Cover best = own;
+    double best_t = 0.0;
+    for (int i = 0; i <= kTall; ++i) {
+        const Cover c = cover(i, r, levels, rows, cols);
+        if (c.def != i) continue;
+        const Def& d = kDefs[i];
+        const double t = d.nw * (d.rw * d.v * ops + 6.0 * d.rw + 40.0) * (double(c.tiles) / 1024 + 0.25);
+        if (best_t == 0.0 || t < best_t) {
+            best_t = t;
+            best = c;
+        }
+    }
+    return best;
 }
 
 }  // namespace block

@@ -271,9 +271,15 @@ BlockFn block_lookup(int storage, int shape, int r, int def) {
     return nullptr;
 }
 
+// The register tiles of a pass.
+block::Cover plan_cover(const st_plan* p, int levels) {
+    const int k = 2 * p->radius + 1;
+    return block::pick(tile_index(p->tile_x, p->tile_y), p->shape == SHAPE_BOX ? k * k + 1 : 2 * k, p->radius, levels, p->rows, p->cols);
+}
+
 // A pass on register tiles; with `sums` its last level's sums per tile (sweep_block_sums), `tiles` of them.
 int launch_block(const st_plan* p, const void* src, void* dst, int levels, double* sums, int64_t* tiles, hipStream_t s) {
-    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    const block::Cover c = plan_cover(p, levels);
     if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
     if (c.tiles >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
     const block::Def& d = block::kDefs[c.def];
@@ -457,12 +463,12 @@ int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa
 
 int64_t sums_tiles(const st_plan* p, int levels) {
     if (p->kind != KIND_CONST || p->bc != ST_BC_CONST) return 0;
-    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    const block::Cover c = plan_cover(p, levels);
     return c.def < 0 || c.tiles >= int64_t(1) << 31 ? 0 : c.tiles;
 }
 
 double block_work(const st_plan* p, int levels) {
-    const block::Cover c = block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    const block::Cover c = plan_cover(p, levels);
     if (c.def < 0) return HUGE_VAL;
     const block::Def& d = block::kDefs[c.def];
     return double(c.tiles) * (64 * d.v * d.rw * d.nw) * levels;

@@ -103,6 +103,15 @@ def case_synth(h, n, rows, cols):
     return {"rc": rc, "launches": made(h.log(), "launch")}
 
 
+def case_run(h, rows, cols, shape, r, steps, storage="f32", tb=0, tile=(0, 0), shift=0):
+    """The kernels of an untuned 2D run (on made-up device addresses, `shift` bytes off a 256-byte boundary)."""
+    plan = h.st.stencil_plan(rows, cols, r, h.weights(shape, r), 0.5, storage, 0)
+    if tb:
+        h.st.stencil_set_blocking(plan, tb, *tile)
+    rc = h.lib.stencil_run(plan, (1 << 40) + shift, 2 << 40, steps, 3 << 40, h.st.stencil_workspace_bytes(plan, steps), CALLER)
+    return {"rc": rc, "launches": made(h.log(), "launch")}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -203,6 +212,16 @@ def test_synthesis_tiles(stub, n, rows, cols, kernel, grid):
     """Small fields share a column's factors among threads; a thread alone takes as long as a large field."""
     res = ask(stub, "synth", n=n, rows=rows, cols=cols)
     assert res["rc"] == 0 and res["launches"] == [["launch", "synth_kernel" + kernel, str(grid), "256", str(CALLER)]]
+
+
+@pytest.mark.parametrize("rows,shape,r,tb,tile,kernel", [
+    (2000, "box", 4, 6, (64, 64), "2,8,16"), (2000, "box", 3, 4, (64, 64), "2,8,8"), (300, "box", 4, 4, (128, 32), "1,8,8"),
+    (2000, "star", 1, 8, (64, 64), "1,8,8"), (2000, "star", 1, 6, (128, 64), "2,8,8"), (2000, "box", 2, 4, (256, 32), "4,4,8")])
+def test_tiles_that_margins_use_up(stub, rows, shape, r, tb, tile, kernel):
+    """A pass whose margins would leave little of the plan's tile takes another; the others keep it."""
+    res = ask(stub, "run", rows=rows, cols=rows, shape=shape, r=r, steps=3 * tb, tb=tb, tile=tile)
+    assert res["rc"] == 0
+    assert {c[1] for c in res["launches"]} == {f"sweep_block<0,{r},{int(shape == 'box')},{kernel}>"}
 
 
 if __name__ == "__main__":
