@@ -128,7 +128,8 @@ int stencil_set_blocking(st_plan* plan, int tb, int tile_x, int tile_y);
 /* kernel variants of the constant-weight sweep */
 #define ST_VARIANT_TILED   0  /* one launch per pass, one tile per workgroup, kept in registers
                                  (tile_x and tile_y choose among its tile sizes); passes over
-                                 grids large enough for it run on the marching kernels           */
+                                 grids large enough for it run on the marching kernels, most
+                                 single steps on LDS tiles                                       */
 #define ST_VARIANT_STREAM  1  /* persistent workgroups; the next tile is copied into LDS by DMA
                                  while the current one computes (FP32, cols % 4 == 0)          */
 #define ST_VARIANT_MARCH   2  /* each wavefront walks a column band down the grid, rows in a

@@ -423,6 +423,15 @@ static bool overlap(const void* a, size_t n, const void* b, size_t m) {
 }
 static bool overlap(const void* a, const void* b, size_t n) { return overlap(a, n, b, n); }
 
+// Large boxes whose arithmetic hides no HBM trip: runs of them take single steps where tiled_step lets them.
+// us a step, single / two at a time: r = 4 at 1000 x 2000 FP32 9.7 / 13, 4096^2 42 / 60; r = 3 BF16 at
+// 1400 x 1408 8.0 / 9.3, 4096^2 29 / 38, FP32 at 1400 x 1408 8.7 / 8.6, 15625 x 128 8 / 10.6, but 6000 x 8192
+// 93 / 78.  Smaller grids wait for launches: 300^2, r = 4, two at a time 53 / 49 us for six steps.
+static bool single_steps(const st_plan* p) {
+    if (p->shape != SHAPE_BOX || p->radius < 3 || field_cells(p) < 1500000) return false;
+    return p->radius == 4 || p->storage != ST_F32 || field_cells(p) < 6000000;
+}
+
 // Enqueue all passes of a run on `s`.
 static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa, int64_t steps, void* ws,
                        hipStream_t s) {
@@ -434,8 +443,12 @@ static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa
     if (resident_run(p)) return launch_resident(p, in, out, ws, steps, s);
     if (p->kind == KIND_3D) max_levels_3d(p);
     const bool naive = p->flags & ST_FLAG_NAIVE;
-    const int64_t tb = naive ? 1 : p->tb;
-    const int64_t P = n_passes(p, steps);
+    int64_t tb = naive ? 1 : p->tb;
+    int64_t P = n_passes(p, steps);
+    if (P > 1 && tb > 1 && single_steps(p) && tiled_step(p, in, ws) && tiled_step(p, ws, out)) {
+        tb = 1;
+        P = steps;
+    }
     const void* src = in;
     for (int64_t k = 0; k < P; ++k) {
         void* dst = ((P - 1 - k) % 2 == 0) ? out : ws;
@@ -592,8 +605,9 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
             if (plan->kind == KIND_CONST && tb > max_tb(plan, tx, ty)) continue;
             if (plan->kind == KIND_VARCOEF && varcoef_lds_bytes(tb, tx, ty) > lds_limit()) continue;
             if (tb > sample_steps) continue;
-            // (a pass that marches anyway is a candidate of that marching variant)
-            if (var == VARIANT_TILED && tiled_march_columns(plan, tb)) continue;
+            // (a pass that marches anyway is a candidate of that marching variant, and a single step has one tile)
+            const bool step = tb == 1 && tiled_step(plan, in, out);
+            if (step ? ti > 0 : var == VARIANT_TILED && tiled_march_columns(plan, tb)) continue;
             plan->tb = tb;
             plan->tile_x = tx;
             plan->tile_y = ty;

@@ -61,6 +61,7 @@ struct SweepArgs {
     int64_t tiles_x, tiles_y;  // tile grid of this launch
     float b;                   // halo value, already rounded to the storage type
     int tb;                    // levels (steps) in this pass
+    const int* stop;           // sweep_step; nullable: when it holds a nonzero value the pass does nothing
     float w[MAXK];             // dense (2r+1)^2 row-major weights
 };
 
@@ -110,6 +111,8 @@ int64_t sums_tiles(const st_plan* p, int levels);
 // Cells a pass of `levels` levels on register tiles computes, margins included.
 double block_work(const st_plan* p, int levels);
 int launch_naive(const st_plan* p, const void* src, void* dst, const float* kappa, hipStream_t s);
+// whether a pass of one level of the tiled variant between these buffers runs on LDS tiles (sweep.hip)
+bool tiled_step(const st_plan* p, const void* src, const void* dst);
 // columns per lane when the marching kernels run a pass of the tiled variant, else 0 (sweep.hip)
 int tiled_march_columns(const st_plan* p, int levels);
 bool tile_supported(int shape, int radius, int tx, int ty);

@@ -6,6 +6,7 @@
 //                 global memory with a bounds test.  The plain GPU reference path.
 //   sweep_block   tb steps per launch (temporal blocking) on register tiles, see block_body.h and
 //                 sweep_block.h.
+//   sweep_step    one step per launch on LDS tiles, for footprints and sizes where no step is to be saved.
 //   sweep_stream  tb steps per launch on LDS tiles, persistent workgroups, the next tile copied into
 //                 LDS by DMA while the current one computes.
 // All use the same per-cell FP32 order (centre product, then one FMA per footprint tap in
@@ -49,6 +50,96 @@ __global__ __launch_bounds__(256) void sweep_naive(SweepArgs a) {
                 acc = __builtin_fmaf(a.w[(dy + R) * K + dx + R], at(i + dy, j + dx), acc);
             }
         static_cast<T*>(a.dst)[idx] = F::st(acc);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// one step on LDS tiles
+// ---------------------------------------------------------------------------
+// A workgroup stages its 128 x 64 tile and an R-deep halo into LDS, 16-byte chunks (whole ones: tiled_step),
+// all in flight before the first is written, and each thread computes 4 columns x 8 rows from a register
+// ring of input rows, three 16-byte LDS reads per row.  Stars are bound by HBM (16384 x 8192 FP32, r = 1:
+// 195 us, 5.5 TB/s), the largest boxes by FP32 issue (r = 4 at 16384 x 8192: 328 us, 66 TFLOP/s).
+constexpr int STX = 128, STY = 64, SRS = 8;
+template <int S, int R>
+struct StepGeo {
+    static constexpr int VEC = Fmt<S>::VEC;
+    static constexpr int OFF = 8;  // buffer column of the tile's first
+    static constexpr int LO = (OFF - R) / VEC * VEC, HI = (OFF + STX + R + VEC - 1) / VEC * VEC;  // staged columns
+    static constexpr int BW = (OFF + STX + 8 + 7) / 8 * 8, BH = STY + 2 * R, NCH = (HI - LO) / VEC, TOTAL = BH * NCH;
+    static constexpr int PER = (TOTAL + NT - 1) / NT;  // chunks per thread
+};
+template <int S, int R, int SHAPE>
+__global__ __launch_bounds__(NT) void sweep_step(SweepArgs a) {
+    using F = Fmt<S>;
+    using T = typename F::T;
+    using G = StepGeo<S, R>;
+    constexpr int K = 2 * R + 1;
+    __shared__ float4 buf4[G::BH * G::BW / 4];
+    __shared__ float wsh[K * K];
+    float* buf = reinterpret_cast<float*>(buf4);
+    if (a.stop && __hip_atomic_load(a.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
+    const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
+    const int64_t y0 = t / a.tiles_x * STY, x0 = t % a.tiles_x * STX;
+    const T* src = static_cast<const T*>(a.src);
+    T* dst = static_cast<T*>(a.dst);
+    // (weights reach vector registers through LDS: 81 of them do not fit the scalar registers)
+    if (threadIdx.x < K * K) wsh[threadIdx.x] = a.w[threadIdx.x];
+    uint4 raw[G::PER];
+    bool in[G::PER];
+#pragma unroll
+    for (int u = 0; u < G::PER; ++u) {
+        const int k = int(threadIdx.x) + u * NT;
+        const int64_t gy = y0 - R + k / G::NCH, gx = x0 - G::OFF + G::LO + k % G::NCH * G::VEC;
+        in[u] = k < G::TOTAL && gy >= 0 && gy < a.rows && gx >= 0 && gx < a.cols;
+        if (in[u]) raw[u] = *reinterpret_cast<const uint4*>(src + gy * a.cols + gx);
+    }
+#pragma unroll
+    for (int u = 0; u < G::PER; ++u) {
+        const int k = int(threadIdx.x) + u * NT;
+        if (k >= G::TOTAL) break;
+        float v[G::VEC];
+        if (in[u]) {
+            widen_chunk<S>(raw[u], v);
+        } else {
+#pragma unroll
+            for (int e = 0; e < G::VEC; ++e) v[e] = a.b;
+        }
+        float4* p = reinterpret_cast<float4*>(buf + k / G::NCH * G::BW + G::LO + k % G::NCH * G::VEC);
+#pragma unroll
+        for (int e = 0; e < G::VEC; e += 4) p[e / 4] = make_float4(v[e], v[e + 1], v[e + 2], v[e + 3]);
+    }
+    __syncthreads();
+    float wreg[K * K];
+#pragma unroll
+    for (int q = 0; q < K * K; ++q) wreg[q] = wsh[q];
+    static_assert(STX / 4 * (STY / SRS) == NT, "a block of cells per thread");
+    const int seg = int(threadIdx.x) / (STX / 4), c4 = 4 * (int(threadIdx.x) % (STX / 4));
+    const float* rows = buf + seg * SRS * G::BW + G::OFF + c4 - 4;
+    const int64_t gx = x0 + c4;
+    float v[SRS + 2 * R][12];
+#pragma unroll
+    for (int j = 0; j < SRS + 2 * R; ++j) {
+        const float4* p = reinterpret_cast<const float4*>(rows + j * G::BW);
+        const float4 q0 = p[0], q1 = p[1], q2 = p[2];
+        v[j][0] = q0.x; v[j][1] = q0.y; v[j][2] = q0.z; v[j][3] = q0.w;
+        v[j][4] = q1.x; v[j][5] = q1.y; v[j][6] = q1.z; v[j][7] = q1.w;
+        v[j][8] = q2.x; v[j][9] = q2.y; v[j][10] = q2.z; v[j][11] = q2.w;
+        if (j < 2 * R) continue;
+        const int k = j - 2 * R;  // the output row that this input row completes
+        float o[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[c] = wreg[R * K + R] * v[k + R][4 + c];
+#pragma unroll
+        for (int dy = -R; dy <= R; ++dy)
+#pragma unroll
+            for (int dx = -R; dx <= R; ++dx) {
+                if ((dy == 0 && dx == 0) || !tap_in(SHAPE, dy, dx)) continue;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) o[c] = __builtin_fmaf(wreg[(dy + R) * K + dx + R], v[k + R + dy][4 + c + dx], o[c]);
+            }
+        const int64_t gy = y0 + seg * SRS + k;
+        if (gy < a.rows && gx < a.cols) store4<S>(dst + gy * a.cols + gx, o);
     }
 }
 
@@ -307,6 +398,24 @@ int launch_block(const st_plan* p, const void* src, void* dst, int levels, doubl
 }
 
 template <int S, int SH>
+KernelFn step_fn_r(int r) {
+    switch (r) {
+        case 1: return sweep_step<S, 1, SH>;
+        case 2: return sweep_step<S, 2, SH>;
+        case 3: return sweep_step<S, 3, SH>;
+        case 4: return sweep_step<S, 4, SH>;
+    }
+    return nullptr;
+}
+
+KernelFn step_lookup(int storage, int shape, int r) {
+    if (storage == ST_F32) return shape == SHAPE_BOX ? step_fn_r<ST_F32, SHAPE_BOX>(r) : step_fn_r<ST_F32, SHAPE_STAR>(r);
+    if (storage == ST_BF16) return shape == SHAPE_BOX ? step_fn_r<ST_BF16, SHAPE_BOX>(r) : step_fn_r<ST_BF16, SHAPE_STAR>(r);
+    if (storage == ST_F16) return shape == SHAPE_BOX ? step_fn_r<ST_F16, SHAPE_BOX>(r) : step_fn_r<ST_F16, SHAPE_STAR>(r);
+    return nullptr;
+}
+
+template <int S, int SH>
 KernelFn naive_fn_r(int r) {
     switch (r) {
         case 1: return sweep_naive<S, 1, SH>;
@@ -355,7 +464,19 @@ void fill_args(const st_plan* p, const void* src, void* dst, const float* kappa,
     a.rows = p->rows;
     a.cols = p->cols;
     a.b = p->bq;
+    a.stop = p->stop;
     std::memcpy(a.w, p->w, sizeof(a.w));
+}
+
+int launch_step(const st_plan* p, const void* src, void* dst, hipStream_t s) {
+    SweepArgs a;
+    fill_args(p, src, dst, nullptr, a);
+    a.tiles_x = (p->cols + STX - 1) / STX;
+    a.tiles_y = (p->rows + STY - 1) / STY;
+    clear_stale_error();
+    hipLaunchKernelGGL(step_lookup(p->storage, p->shape, p->radius), dim3(unsigned(a.tiles_x * a.tiles_y)), dim3(NT), 0, s, a);
+    ST_LAUNCH_CHECK("sweep_step");
+    return ST_OK;
 }
 
 }  // namespace
@@ -427,6 +548,27 @@ int tiled_march_columns(const st_plan* p, int levels) {
     return vmax && levels <= march_max_tb(p->shape, p->radius, vmax) ? vmax : 0;
 }
 
+// Passes of one level of the tiled variant that run on LDS tiles: no step is saved, so a register tile's
+// margins and a marching wavefront's warm-up only cost.  Rows and buffers must be whole 16-byte chunks.  us a
+// step, LDS tiles / what runs otherwise: star r = 1 FP32 512^2 4.7 / 4.9, 16384 x 8192 195 / 240; star r = 4
+// BF16 2000 x 3000 8.2 / 13.5; box r = 2 BF16 2000 x 3000 9.5 / 15.6; box r = 4 FP32 1024^2 9.1 / 11.7, 4096^2
+// 42 / 55, BF16 40 / 59.  The marching kernels keep what they run faster: 16-bit fields of r = 1 and 3 that
+// leave the caches little to do (star r = 1 3000 x 4000 11.7 / 9.9, star r = 3 8192^2 55 / 50, box r = 1 4096^2
+// 15.8 / 14.5), box r = 3 in FP32 (4096^2 34 / 32), and large boxes narrower than a tile (250000 x 40, r = 4
+// 74 / 47).
+bool tiled_step(const st_plan* p, const void* src, const void* dst) {
+    if (p->kind != KIND_CONST || p->bc != ST_BC_CONST || p->variant != VARIANT_TILED) return false;
+    const bool f32 = p->storage == ST_F32, box = p->shape == SHAPE_BOX;
+    if (p->cols % (f32 ? 4 : 8) || reinterpret_cast<uintptr_t>(src) % 16 || reinterpret_cast<uintptr_t>(dst) % 16) return false;
+    const int64_t cells = p->rows * p->cols;
+    if ((p->cols + STX - 1) / STX * ((p->rows + STY - 1) / STY) >= int64_t(1) << 24) return false;  // threads of a launch
+    if (box && p->radius >= 3 && p->cols < STX) return cells < 1500000;
+    if (p->cols < 512) return true;  // (marching bands would be half empty: box r = 1 100000 x 256 21 / 28)
+    if (box && p->radius == 3 && f32) return cells < 6000000 || cells >= int64_t(1) << 25;
+    if (!f32 && (box ? p->radius == 1 : p->radius % 2 == 1)) return cells < 8000000 || cells >= (!box && p->radius == 1 ? 20000000 : 100000000);
+    return true;
+}
+
 int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa, int levels, hipStream_t s) {
     if (p->flags & ST_FLAG_NAIVE) {
         // the reference path: one launch per step through the workspace is handled by the caller
@@ -456,6 +598,7 @@ int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa
         ST_LAUNCH_CHECK("sweep_stream");
         return ST_OK;
     }
+    if (levels == 1 && tiled_step(p, src, dst)) return launch_step(p, src, dst, s);
     if (p->variant == VARIANT_TILED)
         if (const int vmax = tiled_march_columns(p, levels)) return launch_march(p, src, dst, levels, vmax, s);
     return launch_block(p, src, dst, levels, nullptr, nullptr, s);

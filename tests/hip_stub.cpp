@@ -72,7 +72,7 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
     }
     n.resize(open);
     if (n.compare(0, 5, "void ") == 0) n = n.substr(5);
-    for (const char* ns : {"st::", "(anonymous namespace)::"})
+    for (const char* ns : {"st::", "march_k::", "(anonymous namespace)::"})
         for (size_t p; (p = n.find(ns)) != std::string::npos;) n.erase(p, std::strlen(ns));
     for (size_t p; (p = n.find(' ')) != std::string::npos;) n.erase(p, 1);
     g_kernels[host] = n;

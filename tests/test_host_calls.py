@@ -215,13 +215,38 @@ def test_synthesis_tiles(stub, n, rows, cols, kernel, grid):
 
 
 @pytest.mark.parametrize("rows,shape,r,tb,tile,kernel", [
-    (2000, "box", 4, 6, (64, 64), "2,8,16"), (2000, "box", 3, 4, (64, 64), "2,8,8"), (300, "box", 4, 4, (128, 32), "1,8,8"),
+    (2000, "star", 3, 8, (64, 64), "2,8,16"), (2000, "star", 4, 4, (64, 64), "2,8,16"), (300, "star", 4, 4, (128, 32), "1,8,8"),
     (2000, "star", 1, 8, (64, 64), "1,8,8"), (2000, "star", 1, 6, (128, 64), "2,8,8"), (2000, "box", 2, 4, (256, 32), "4,4,8")])
 def test_tiles_that_margins_use_up(stub, rows, shape, r, tb, tile, kernel):
     """A pass whose margins would leave little of the plan's tile takes another; the others keep it."""
     res = ask(stub, "run", rows=rows, cols=rows, shape=shape, r=r, steps=3 * tb, tb=tb, tile=tile)
     assert res["rc"] == 0
     assert {c[1] for c in res["launches"]} == {f"sweep_block<0,{r},{int(shape == 'box')},{kernel}>"}
+
+
+@pytest.mark.parametrize("rows,cols,shape,r,storage,kw,kernel", [
+    (1024, 1024, "star", 1, "f32", {}, "sweep_step"), (8192, 8192, "star", 1, "f32", {}, "sweep_step"),
+    (2000, 3000, "star", 4, "bf16", {}, "sweep_step"), (4096, 4096, "box", 4, "bf16", {}, "sweep_step"),
+    (4096, 4096, "star", 1, "bf16", {}, "sweep_march"), (4096, 4096, "star", 3, "f16", {}, "sweep_march"),
+    (8192, 8192, "star", 1, "f16", {}, "sweep_step"), (4096, 4096, "box", 3, "f32", {}, "sweep_march"),
+    (250000, 40, "box", 4, "f32", {}, "sweep_march"), (1024, 1023, "star", 1, "f32", {}, "sweep_block"),
+    (1024, 1020, "star", 1, "bf16", {}, "sweep_block"), (1024, 1024, "star", 1, "f32", {"shift": 4}, "sweep_block"),
+    (1024, 1024, "star", 1, "f32", {"shift": 16}, "sweep_step")])
+def test_single_steps(stub, rows, cols, shape, r, storage, kw, kernel):
+    """One step of an untuned plan runs where it is fastest; what LDS tiles cannot load whole goes elsewhere."""
+    res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=1, storage=storage, **kw)
+    assert res["rc"] == 0 and [c[1].split("<")[0] for c in res["launches"]] == [kernel]
+
+
+@pytest.mark.parametrize("rows,cols,r,storage,single", [
+    (1000, 2000, 4, "f32", True), (1000, 2000, 3, "bf16", True), (4096, 4096, 3, "f16", True), (15625, 128, 3, "f32", True),
+    (1000, 1000, 4, "f32", False), (4096, 4096, 3, "f32", False), (6000, 8192, 3, "f32", False)])
+def test_large_boxes_take_single_steps(stub, rows, cols, r, storage, single):
+    runs = {n: ask(stub, "run", rows=rows, cols=cols, shape="box", r=r, steps=n, storage=storage) for n in (2, 7)}
+    assert all(run["rc"] == 0 for run in runs.values())
+    assert len(runs[2]["launches"]) == 1  # no workspace was asked for
+    assert len(runs[7]["launches"]) == (7 if single else 4)
+    assert not single or {c[1].split("<")[0] for c in runs[7]["launches"]} == {"sweep_step"}
 
 
 if __name__ == "__main__":
