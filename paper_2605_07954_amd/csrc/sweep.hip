@@ -16,6 +16,7 @@
 #include <mutex>
 
 #include "internal.h"
+#include "march_layout.h"
 #include "storage.h"
 #include "sweep_block.h"
 #include "sweep_body.h"
@@ -540,11 +541,23 @@ int launch_naive(const st_plan* p, const void* src, void* dst, const float* kapp
 // 1450 / 1573, 4096^2 1588 / 2201; box r = 1 at tb 6, 2000 x 3000 1550 / 1310, 4096^2 1802 / 2155.  Boxes
 // of r >= 3 hold few rows in flight either way, and one-column marching wins from 1.5 10^6 cells on (box
 // r = 3 at tb 2, 1000^2 168 / 153, 1448^2 218 / 251, 4096^2 424 / 491; at 16384^2 eight columns reach 720).
+// Eight columns (four at widths that are no multiple of eight) pay where their bands hold grid in at least
+// 0.62 of their lanes (4 10^7 cells of box r = 3, 12 steps at tb 2, ms, eight columns / one column: 1200 wide
+// 0.95 / 1.20, 1000 wide 1.17 / 1.18, 520 wide 1.40 / 1.13, 64 wide 5.3 / 1.8), and on grids narrower than a tile register tiles beat a band of
+// 256 columns where they hold most of their rows (10^7 cells, 100 wide: star r = 2 118 / 85, box r = 1 124 / 88,
+// but star r = 1 70 / 59 to 219 / 222 and star r = 3 177 / 170, at 40 wide 327 / 401).
 int tiled_march_columns(const st_plan* p, int levels) {
     if (p->kind != KIND_CONST || p->bc != ST_BC_CONST) return 0;
     const int64_t cells = p->rows * p->cols;
     const bool big_box = p->shape == SHAPE_BOX && p->radius >= 3;
-    const int vmax = cells < (big_box ? int64_t(1500000) : int64_t(8000000)) ? 0 : !big_box ? 4 : cells < (int64_t(1) << 25) ? 1 : 8;
+    if (cells < (big_box ? 1500000 : 8000000)) return 0;
+    if (p->cols < 128 && ((p->shape == SHAPE_STAR && p->radius == 2) || (p->shape == SHAPE_BOX && p->radius == 1))) return 0;
+    int vmax = 4;
+    if (big_box) {
+        const int V = p->cols % 8 ? 4 : 8;  // (launch_march: rows of whole vectors of eight)
+        const int64_t bands = march::band_count(p->cols, V, march::halo_lanes(p->radius, levels, V), false);
+        vmax = cells >= int64_t(1) << 25 && double(p->cols) >= 0.62 * double(bands * 64 * V) ? 8 : 1;
+    }
     return vmax && levels <= march_max_tb(p->shape, p->radius, vmax) ? vmax : 0;
 }
 

@@ -249,5 +249,15 @@ def test_large_boxes_take_single_steps(stub, rows, cols, r, storage, single):
     assert not single or {c[1].split("<")[0] for c in runs[7]["launches"]} == {"sweep_step"}
 
 
+@pytest.mark.parametrize("rows,cols,shape,r,kernel", [
+    (625000, 64, "box", 3, "sweep_march<0,3,1,"), (40000, 1000, "box", 3, "sweep_march<0,3,8,"), (76923, 520, "box", 3, "sweep_march<0,3,1,"),
+    (57142, 700, "box", 3, "sweep_march_w3<0,3,4,"), (250000, 40, "star", 2, "sweep_block"), (250000, 40, "box", 1, "sweep_block"),
+    (250000, 40, "star", 3, "sweep_march"), (3000, 4000, "star", 2, "sweep_march<0,2,4,")])
+def test_marching_of_narrow_grids(stub, rows, cols, shape, r, kernel):
+    """Bands that a narrow grid would leave empty are not taken, however many rows it has."""
+    res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=8)
+    assert res["rc"] == 0 and all(c[1].startswith(kernel) for c in res["launches"])
+
+
 if __name__ == "__main__":
     print(json.dumps(CASES[sys.argv[2]](Host(sys.argv[1]), **json.loads(sys.argv[3]))))
