@@ -209,12 +209,13 @@ inline Cover cover(int def, int r, int levels, int64_t rows, int64_t cols) {
 }
 
 // The tile that a plan's pass runs on: the plan's own (`def`), unless its margins would leave less than
-// two fifths of its cells -- then the one of least estimated time, from the instructions that a wavefront
-// issues per level (`ops` a cell, a few per row, and the exchange) over the 1024 SIMDs, plus one workgroup's
-// own time.  Three passes at 2000^2, us, own tile / picked: box r = 4, 64 x 64, 6 levels (6 % kept)
-// 2193 / 555 (LDS tiles, whose halo lies around the tile, took 645); box r = 3, 64 x 64, 4 levels (39 %)
-// 206 / 173; star r = 4, 128 x 64, 4 levels (38 %) 94 / 88.  From two fifths up the own tile was never slower
-// than LDS tiles, and a plan's tile stays the plan's.
+// two fifths of its cells and another is estimated to take less than 0.85 of its time: the instructions that
+// a compute unit issues per level (`ops` a cell, a few per row, and the exchange) for its share of the 256.
+// Three passes at 2000^2, us, own tile / picked: star r = 4, 64 x 64, 6 levels (6 % kept) 592 / 157 (LDS tiles,
+// whose halo lies around the tile, took 295); box r = 2, 64 x 64, 12 levels 1429 / 351; star r = 4, 128 x 64, 4
+// levels (38 %) 94 / 88.  From two fifths up the own tile was never slower than LDS tiles.  Small grids are
+// often best on small tiles all the same: star r = 1 at 512^2, 64 x 64, 16 levels (25 %) 8.0 us a pass, on the
+// next tile 9.7.
 inline Cover pick(int def, double ops, int r, int levels, int64_t rows, int64_t cols) {
     const Cover own = cover(def, r, levels, rows, cols);
     if (own.def == def) {
@@ -222,15 +223,18 @@ inline Cover pick(int def, double ops, int r, int levels, int64_t rows, int64_t 
         const double keep = double(d.nw * d.rw - 2 * r * levels) * (64 * d.v - 2 * margin_cols(r, levels, d.v));
         if (keep >= 0.4 * d.nw * d.rw * 64 * d.v) return own;
     }
+    auto time = [&](const Cover& c) {
+        const Def& d = kDefs[c.def];
+        const double share = c.tiles <= 256 ? 1.0 : double(c.tiles) / 256 + 0.3;  // (a last round is partly hidden)
+        return share * d.nw * (d.rw * d.v * ops + 6.0 * d.rw + 40.0);
+    };
     Cover best = own;
-    double best_t = 0.0;
+    if (own.def < 0) return own;
+    double best_t = time(own) * (own.def == def ? 0.85 : 1.0);
     for (int i = 0; i <= kTall; ++i) {
         const Cover c = cover(i, r, levels, rows, cols);
-        if (c.def != i) continue;
-        const Def& d = kDefs[i];
-        const double t = d.nw * (d.rw * d.v * ops + 6.0 * d.rw + 40.0) * (double(c.tiles) / 1024 + 0.25);
-        if (best_t == 0.0 || t < best_t) {
-            best_t = t;
+        if (c.def == i && time(c) < best_t) {
+            best_t = time(c);
             best = c;
         }
     }
