@@ -27,6 +27,7 @@ struct BlockPassArgs {
     const int64_t* tile_prefix;  // prefix sums of tiles over `order` (n + 1 of them; p >= 0)
     int n;
     int p;
+    int64_t first;  // the first tile of this launch
 };
 using BlockPassFn = void (*)(BlockPassArgs);
 // The kernel of a class with tile `def` (block::kDefs), or of whole grids in one tile.

@@ -509,7 +509,9 @@ static int enqueue_passes(st_batch* B, int t, char* ws, hipStream_t s) {
             BlockPassFn fn = batched_block_lookup(d0.shape, d0.r, M.def);
             const size_t lds = block::lds_floats(d0.r, tile.v, tile.rw, tile.nw) * sizeof(float);
             if (int rc = prepare_lds(reinterpret_cast<const void*>(fn), lds)) return rc;
-            hipLaunchKernelGGL(fn, dim3(unsigned(L.tasks)), dim3(64 * tile.nw), lds, s, BlockPassArgs{desc, order, prefix, L.n, L.p});
+            launch_runs(L.tasks, 64 * tile.nw, [&](int64_t first, int64_t n) {
+                hipLaunchKernelGGL(fn, dim3(unsigned(n)), dim3(64 * tile.nw), lds, s, BlockPassArgs{desc, order, prefix, L.n, L.p, first});
+            });
             ST_LAUNCH_CHECK("batched_block");
             continue;
         }
@@ -539,7 +541,7 @@ static int enqueue_whole(st_batch* B, int c, char* ws, hipStream_t s) {
     clear_stale_error();
     hipLaunchKernelGGL(fn, dim3(unsigned(B->whole_n[c])), dim3(64 * t.nw), lds, s,
                        BlockPassArgs{reinterpret_cast<const BatchDesc*>(ws + B->off_desc),
-                                     reinterpret_cast<const int*>(ws + B->off_res) + B->whole_first[c], nullptr, B->whole_n[c], -1});
+                                     reinterpret_cast<const int*>(ws + B->off_res) + B->whole_first[c], nullptr, B->whole_n[c], -1, 0});
     ST_LAUNCH_CHECK("batched_whole");
     return ST_OK;
 }

@@ -33,7 +33,7 @@ __device__ __forceinline__ void load_w(const BatchDesc& d, BlockArgs& a) {
 template <int R, int SH, int V, int RW, int NW>
 __global__ __launch_bounds__(64 * NW) void batched_block(BlockPassArgs q) {
     extern __shared__ float4 lds4[];
-    const int64_t o = block::xcd_order(blockIdx.x, gridDim.x);
+    const int64_t o = q.first + block::xcd_order(blockIdx.x, gridDim.x);
     const int k = upper_index(q.tile_prefix, q.n + 1, o);
     const BatchDesc& d = q.desc[q.order[k]];
     const int P = d.passes, p = q.p;

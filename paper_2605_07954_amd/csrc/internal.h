@@ -51,6 +51,12 @@ constexpr int MAXK3 = (2 * ST_MAX_RADIUS_3D + 1) * (2 * ST_MAX_RADIUS_3D + 1) * 
 // Workgroups of a one-cell-per-thread reference launch; beyond it the kernels stride over the grid
 // (a launch may hold at most 2^32 threads).
 constexpr int64_t kNaiveMaxBlocks = int64_t(1) << 20;
+// Calls launch(first, n) for runs of blocks [first, first + n) of `threads` threads that together are [0, blocks).
+template <typename F>
+inline void launch_runs(int64_t blocks, int threads, F&& launch) {
+    const int64_t most = ((int64_t(1) << 32) - 1) / threads;
+    for (int64_t first = 0; first < blocks; first += most) launch(first, blocks - first < most ? blocks - first : most);
+}
 
 // Kernel argument block of one sweep pass (passed by value; weights live in kernargs).
 struct SweepArgs {

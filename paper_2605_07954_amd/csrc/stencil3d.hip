@@ -252,14 +252,20 @@ int launch_tiles(const st_plan* p, const void* src, void* dst, int levels, hipSt
             a.wy[i] = w[d * k];
             a.wx[i] = w[d];
         }
-        hipLaunchKernelGGL(reinterpret_cast<void (*)(Args3B)>(const_cast<void*>(block3(p, levels))), dim3(unsigned(grid)),
-                           dim3(64 * nw), lds, s, a);
+        launch_runs(grid, 64 * nw, [&](int64_t first, int64_t n) {
+            a.first = first;
+            hipLaunchKernelGGL(reinterpret_cast<void (*)(Args3B)>(const_cast<void*>(block3(p, levels))), dim3(unsigned(n)),
+                               dim3(64 * nw), lds, s, a);
+        });
     } else {
         Args3X a;
         fill(a);
         std::memcpy(a.w, p->w3, sizeof(a.w));
-        hipLaunchKernelGGL(reinterpret_cast<void (*)(Args3X)>(const_cast<void*>(block3(p, levels))), dim3(unsigned(grid)),
-                           dim3(64 * nw), lds, s, a);
+        launch_runs(grid, 64 * nw, [&](int64_t first, int64_t n) {
+            a.first = first;
+            hipLaunchKernelGGL(reinterpret_cast<void (*)(Args3X)>(const_cast<void*>(block3(p, levels))), dim3(unsigned(n)),
+                               dim3(64 * nw), lds, s, a);
+        });
     }
     ST_LAUNCH_CHECK("sweep3d_block");
     return ST_OK;

@@ -385,14 +385,16 @@ int launch_block(const st_plan* p, const void* src, void* dst, int levels, doubl
     a.rows = p->rows;
     a.cols = p->cols;
     a.tiles_x = c.tiles_x;
-    a.tiles = c.tiles;
     a.stop = p->stop;
     a.b = p->bq;
     a.tb = levels;
     a.sums = sums;
     std::memcpy(a.w, p->w, sizeof(a.w));
     clear_stale_error();
-    hipLaunchKernelGGL(fn, dim3(unsigned(a.tiles)), dim3(64 * d.nw), lds, s, a);
+    launch_runs(c.tiles, 64 * d.nw, [&](int64_t first, int64_t n) {
+        a.first = first;
+        hipLaunchKernelGGL(fn, dim3(unsigned(n)), dim3(64 * d.nw), lds, s, a);
+    });
     ST_LAUNCH_CHECK("sweep_block");
     if (tiles) *tiles = c.tiles;
     return ST_OK;

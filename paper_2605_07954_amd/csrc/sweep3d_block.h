@@ -27,6 +27,7 @@ struct Args3B {
     void* dst;
     int64_t planes, rows, cols;
     int64_t tiles_x, tiles, zseg;  // tiles of a plane; planes per segment
+    int64_t first;                 // the first (segment, tile) of this launch
     float b;
     float wc;                                     // the centre weight
     float wz[2 * ST_MAX_RADIUS_3D], wy[2 * ST_MAX_RADIUS_3D], wx[2 * ST_MAX_RADIUS_3D];  // offsets -R .. -1, 1 .. R
@@ -36,7 +37,7 @@ struct Args3X {
     const void* src;
     void* dst;
     int64_t planes, rows, cols;
-    int64_t tiles_x, tiles, zseg;
+    int64_t tiles_x, tiles, zseg, first;
     float b;
     float w[MAXK3];  // dense, row-major in (dz, dy, dx)
 };
@@ -345,7 +346,7 @@ __device__ __forceinline__ void march3d_box(const Args3X& a, const TileAt& at, i
 template <int S, int R, int T, int V, int RW, int NW>
 __global__ __launch_bounds__(64 * NW) void sweep3d_block(Args3B a) {
     extern __shared__ float4 lds4[];
-    const int64_t seg = blockIdx.x / a.tiles, tile = blockIdx.x - seg * a.tiles;
+    const int64_t at0 = a.first + blockIdx.x, seg = at0 / a.tiles, tile = at0 - seg * a.tiles;
     const block::TileAt at = block::tile_at<R, V, RW, NW>(tile, a.tiles_x, a.rows, a.cols, T);
     const int64_t z0 = seg * a.zseg, z1 = z0 + a.zseg < a.planes ? z0 + a.zseg : a.planes;
     float* lds = reinterpret_cast<float*>(lds4);
@@ -356,7 +357,7 @@ __global__ __launch_bounds__(64 * NW) void sweep3d_block(Args3B a) {
 template <int S, int R, int T, int V, int RW, int NW>
 __global__ __launch_bounds__(64 * NW) void sweep3d_block_box(Args3X a) {
     extern __shared__ float4 lds4[];
-    const int64_t seg = blockIdx.x / a.tiles, tile = blockIdx.x - seg * a.tiles;
+    const int64_t at0 = a.first + blockIdx.x, seg = at0 / a.tiles, tile = at0 - seg * a.tiles;
     const block::TileAt at = block::tile_at<R, V, RW, NW>(tile, a.tiles_x, a.rows, a.cols, T);
     const int64_t z0 = seg * a.zseg, z1 = z0 + a.zseg < a.planes ? z0 + a.zseg : a.planes;
     float* lds = reinterpret_cast<float*>(lds4);

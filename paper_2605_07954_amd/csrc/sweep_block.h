@@ -12,7 +12,7 @@ struct BlockArgs {
     const void* src;
     void* dst;
     int64_t rows, cols;
-    int64_t tiles_x, tiles;
+    int64_t tiles_x, first;  // tiles across; the first tile of this launch
     const int* stop;  // nullable: when it holds a nonzero value the pass does nothing
     float b;
     int tb;           // levels of this pass
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * NW) void sweep_block(BlockArgs a) {
     extern __shared__ float4 lds4[];
     if (a.stop && __hip_atomic_load(a.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
     const block::TileAt at =
-        block::tile_at<R, V, RW, NW>(block::xcd_order(blockIdx.x, a.tiles), a.tiles_x, a.rows, a.cols, a.tb);
+        block::tile_at<R, V, RW, NW>(a.first + block::xcd_order(blockIdx.x, gridDim.x), a.tiles_x, a.rows, a.cols, a.tb);
     float* lds = reinterpret_cast<float*>(lds4);
     double sum[2];
     if (at.edge) block::tile_levels<S, R, SHAPE, V, RW, NW, true, false>(a, at, lds, sum);
@@ -201,7 +201,7 @@ template <int S, int R, int SHAPE, int V, int RW, int NW>
 __global__ __launch_bounds__(64 * NW) void sweep_block_sums(BlockArgs a) {
     extern __shared__ float4 lds4[];
     if (a.stop && __hip_atomic_load(a.stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;
-    const int64_t t = block::xcd_order(blockIdx.x, a.tiles);
+    const int64_t t = a.first + block::xcd_order(blockIdx.x, gridDim.x);
     const block::TileAt at = block::tile_at<R, V, RW, NW>(t, a.tiles_x, a.rows, a.cols, a.tb);
     float* lds = reinterpret_cast<float*>(lds4);
     double sum[2] = {0.0, 0.0};

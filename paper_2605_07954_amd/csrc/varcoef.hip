@@ -57,6 +57,7 @@ struct VArgs {
     float* dst;
     int64_t rows, cols;
     int64_t tiles_x, tiles;  // of one field
+    int64_t first, blocks;   // the tiles of this launch, of all fields: `blocks` from `first` on
     int fields;              // fields one after another in src, kappa and dst
     float b;
     int tb;
@@ -195,7 +196,7 @@ template <int V, int RW, int NW>
 __global__ __launch_bounds__(64 * NW) void varcoef_block(VArgs a) {
     extern __shared__ float4 lds4[];
     float* lds = reinterpret_cast<float*>(lds4);
-    const int64_t t = block::xcd_order(blockIdx.x, a.tiles * a.fields), f = t / a.tiles;
+    const int64_t t = a.first + block::xcd_order(blockIdx.x, a.blocks), f = t / a.tiles;
     const block::TileAt at = block::tile_at<1, V, RW, NW>(t - f * a.tiles, a.tiles_x, a.rows, a.cols, a.tb);
     if (at.edge) vc_levels<V, RW, NW, true>(a, at, f, lds);
     else vc_levels<V, RW, NW, false>(a, at, f, lds);
@@ -230,7 +231,11 @@ static int launch_vc_block(int tile, VArgs a, hipStream_t s) {
     a.tiles_x = c.tiles_x;
     a.tiles = c.tiles;
     clear_stale_error();
-    hipLaunchKernelGGL(fn, dim3(unsigned(c.tiles * a.fields)), dim3(64 * d.nw), lds, s, a);
+    launch_runs(c.tiles * a.fields, 64 * d.nw, [&](int64_t first, int64_t n) {
+        a.first = first;
+        a.blocks = n;
+        hipLaunchKernelGGL(fn, dim3(unsigned(n)), dim3(64 * d.nw), lds, s, a);
+    });
     ST_LAUNCH_CHECK("varcoef_block");
     return ST_OK;
 }
@@ -253,7 +258,7 @@ int varcoef_launch(const st_plan* p, const float* src, float* dst, const float* 
         return ST_OK;
     }
     return launch_vc_block(tile_index(p->tile_x, p->tile_y),
-                           VArgs{src, kappa, dst, p->rows, p->cols, 0, 0, 1, p->bq, levels, VcWindows{}, 0}, s);
+                           VArgs{src, kappa, dst, p->rows, p->cols, 0, 0, 0, 0, 1, p->bq, levels, VcWindows{}, 0}, s);
 }
 
 int varcoef_windows(const float* u0, const float* kappa, const VcWindows& w, int64_t rows, int64_t cols, int fields,
@@ -264,7 +269,7 @@ int varcoef_windows(const float* u0, const float* kappa, const VcWindows& w, int
     for (int64_t k = 0; k < passes; ++k) {
         float* dst = (passes - 1 - k) % 2 == 0 ? out : scratch;
         const int levels = int(steps / passes + (k < steps % passes));
-        if (int rc = launch_vc_block(0, VArgs{src, kappa, dst, rows, cols, 0, 0, fields, 0.0f, levels, w, k == 0}, s)) return rc;
+        if (int rc = launch_vc_block(0, VArgs{src, kappa, dst, rows, cols, 0, 0, 0, 0, fields, 0.0f, levels, w, k == 0}, s)) return rc;
         src = dst;
     }
     return ST_OK;

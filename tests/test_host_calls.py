@@ -112,6 +112,13 @@ def case_run(h, rows, cols, shape, r, steps, storage="f32", tb=0, tile=(0, 0), s
     return {"rc": rc, "launches": made(h.log(), "launch")}
 
 
+def case_varcoef(h, rows, cols, steps, tb, tile):
+    plan = h.st.stencil_plan_varcoef(rows, cols, 0.0, 0)
+    h.st.stencil_set_blocking(plan, tb, *tile)
+    rc = h.lib.stencil_run_varcoef(plan, 1 << 40, 2 << 40, 3 << 40, steps, 4 << 40, h.st.stencil_workspace_bytes(plan, steps), CALLER)
+    return {"rc": rc, "launches": made(h.log(), "launch")}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -257,6 +264,20 @@ def test_marching_of_narrow_grids(stub, rows, cols, shape, r, kernel):
     """Bands that a narrow grid would leave empty are not taken, however many rows it has."""
     res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=8)
     assert res["rc"] == 0 and all(c[1].startswith(kernel) for c in res["launches"])
+
+
+@pytest.mark.parametrize("case,kw,blocks", [
+    ("varcoef", dict(rows=140000, cols=140000, steps=8, tb=8, tile=(64, 64)), 2917 ** 2),
+    ("run", dict(rows=140000, cols=140000, shape="box", r=4, storage="bf16", steps=2, tb=2, tile=(64, 64)), 2917 ** 2),
+    ("run3d", dict(dims=(1, 150000, 150001), shape="star", r=1, storage="f32", steps=1), 2420 ** 2),
+    ("run3d", dict(dims=(2, 150000, 150001), shape="box", r=1, storage="bf16", steps=1), None)])
+def test_more_threads_than_a_launch_holds(stub, case, kw, blocks):
+    """Fields that fit the device's memory with more tiles than one launch has threads for."""
+    res = ask(stub, case, **kw)
+    assert res["rc"] == 0
+    work = [int(c[2]) * int(c[3]) for c in res["launches"]]
+    assert len(work) > 1 and sum(work) >= 2 ** 32 > max(work)
+    assert blocks is None or blocks == sum(int(c[2]) for c in res["launches"])
 
 
 if __name__ == "__main__":
