@@ -423,15 +423,6 @@ static bool overlap(const void* a, size_t n, const void* b, size_t m) {
 }
 static bool overlap(const void* a, const void* b, size_t n) { return overlap(a, n, b, n); }
 
-// Large boxes whose arithmetic hides no HBM trip: runs of them take single steps where tiled_step lets them.
-// us a step, single / two at a time: r = 4 at 1000 x 2000 FP32 9.7 / 13, 4096^2 42 / 60; r = 3 BF16 at
-// 1400 x 1408 8.0 / 9.3, 4096^2 29 / 38, FP32 at 1400 x 1408 8.7 / 8.6, 15625 x 128 8 / 10.6, but 6000 x 8192
-// 93 / 78.  Smaller grids wait for launches: 300^2, r = 4, two at a time 53 / 49 us for six steps.
-static bool single_steps(const st_plan* p) {
-    if (p->shape != SHAPE_BOX || p->radius < 3 || field_cells(p) < 1500000) return false;
-    return p->radius == 4 || p->storage != ST_F32 || field_cells(p) < 6000000;
-}
-
 // Enqueue all passes of a run on `s`.
 static int enqueue_run(st_plan* p, const void* in, void* out, const float* kappa, int64_t steps, void* ws,
                        hipStream_t s) {

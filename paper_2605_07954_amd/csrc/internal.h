@@ -119,6 +119,8 @@ double block_work(const st_plan* p, int levels);
 int launch_naive(const st_plan* p, const void* src, void* dst, const float* kappa, hipStream_t s);
 // whether a pass of one level of the tiled variant between these buffers runs on LDS tiles (sweep.hip)
 bool tiled_step(const st_plan* p, const void* src, const void* dst);
+// whether runs of the tiled variant take single steps where tiled_step lets them (sweep.hip)
+bool single_steps(const st_plan* p);
 // columns per lane when the marching kernels run a pass of the tiled variant, else 0 (sweep.hip)
 int tiled_march_columns(const st_plan* p, int levels);
 bool tile_supported(int shape, int radius, int tx, int ty);

@@ -547,13 +547,14 @@ int launch_naive(const st_plan* p, const void* src, void* dst, const float* kapp
 // 0.62 of their lanes (4 10^7 cells of box r = 3, 12 steps at tb 2, ms, eight columns / one column: 1200 wide
 // 0.95 / 1.20, 1000 wide 1.17 / 1.18, 520 wide 1.40 / 1.13, 64 wide 5.3 / 1.8), and on grids narrower than a tile register tiles beat a band of
 // 256 columns where they hold most of their rows (10^7 cells, 100 wide: star r = 2 118 / 85, box r = 1 124 / 88,
-// but star r = 1 70 / 59 to 219 / 222 and star r = 3 177 / 170, at 40 wide 327 / 401).
+// but star r = 1 70 / 59 to 219 / 222 and star r = 3 177 / 170, at 40 wide 327 / 401; star r = 2 at two levels
+// 39 / 48).
 int tiled_march_columns(const st_plan* p, int levels) {
     if (p->kind != KIND_CONST || p->bc != ST_BC_CONST) return 0;
     const int64_t cells = p->rows * p->cols;
     const bool big_box = p->shape == SHAPE_BOX && p->radius >= 3;
     if (cells < (big_box ? 1500000 : 8000000)) return 0;
-    if (p->cols < 128 && ((p->shape == SHAPE_STAR && p->radius == 2) || (p->shape == SHAPE_BOX && p->radius == 1))) return 0;
+    if (levels >= 4 && p->cols < 128 && ((p->shape == SHAPE_STAR && p->radius == 2) || (p->shape == SHAPE_BOX && p->radius == 1))) return 0;
     int vmax = 4;
     if (big_box) {
         const int V = p->cols % 8 ? 4 : 8;  // (launch_march: rows of whole vectors of eight)
@@ -567,8 +568,8 @@ int tiled_march_columns(const st_plan* p, int levels) {
 // margins and a marching wavefront's warm-up only cost.  Rows and buffers must be whole 16-byte chunks.  us a
 // step, LDS tiles / what runs otherwise: star r = 1 FP32 512^2 4.7 / 4.9, 16384 x 8192 195 / 240; star r = 4
 // BF16 2000 x 3000 8.2 / 13.5; box r = 2 BF16 2000 x 3000 9.5 / 15.6; box r = 4 FP32 1024^2 9.1 / 11.7, 4096^2
-// 42 / 55, BF16 40 / 59.  The marching kernels keep what they run faster: 16-bit fields of r = 1 and 3 that
-// leave the caches little to do (star r = 1 3000 x 4000 11.7 / 9.9, star r = 3 8192^2 55 / 50, box r = 1 4096^2
+// 42 / 55, BF16 40 / 59.  The marching kernels keep what they run faster: 16-bit stars and boxes of r = 1 of some
+// sizes (star r = 1 3000 x 4000 11.7 / 9.9, r = 3 8192^2 55 / 50, r = 4 8192^2 55 / 51, box r = 1 4096^2
 // 15.8 / 14.5), box r = 3 in FP32 (4096^2 34 / 32), and large boxes narrower than a tile (250000 x 40, r = 4
 // 74 / 47).
 bool tiled_step(const st_plan* p, const void* src, const void* dst) {
@@ -576,12 +577,40 @@ bool tiled_step(const st_plan* p, const void* src, const void* dst) {
     const bool f32 = p->storage == ST_F32, box = p->shape == SHAPE_BOX;
     if (p->cols % (f32 ? 4 : 8) || reinterpret_cast<uintptr_t>(src) % 16 || reinterpret_cast<uintptr_t>(dst) % 16) return false;
     const int64_t cells = p->rows * p->cols;
-    if ((p->cols + STX - 1) / STX * ((p->rows + STY - 1) / STY) >= int64_t(1) << 24) return false;  // threads of a launch
-    if (box && p->radius >= 3 && p->cols < STX) return cells < 1500000;
-    if (p->cols < 512) return true;  // (marching bands would be half empty: box r = 1 100000 x 256 21 / 28)
+    const int64_t tiles = (p->cols + STX - 1) / STX * ((p->rows + STY - 1) / STY);
+    if (tiles >= int64_t(1) << 24) return false;  // threads of a launch
+    const bool big = box && p->radius == 4;
+    if (tiles < 256 && (p->tile_x != STX || p->tile_y != STY))  // a small grid: the plan's tile spreads it
+        return big && p->tile_x * p->tile_y == STX * STY;
+    if (big) return p->cols >= STX || cells < 1500000;
+    const int V = tiled_march_columns(p, 1);
+    if (!V) return true;  // (register tiles were never faster)
+    // lanes that hold grid: 60000 x 200 (0.78 of either) box r = 3 FP32 32 / 28, 100000 x 256 (1.0 of the tiles,
+    // 0.5 of the bands) box r = 1 BF16 21 / 28
+    const double fill = double(cells) / double(tiles * STX * STY);
+    const double bands = double(march::band_count(p->cols, V, march::halo_lanes(p->radius, 1, V), false));
+    const double march_fill = double(p->cols) / (bands * 64 * V);
+    if (fill < 0.8) return fill > 1.2 * march_fill && !(box && p->radius == 3);
+    if (p->cols < 512) return true;
     if (box && p->radius == 3 && f32) return cells < 6000000 || cells >= int64_t(1) << 25;
-    if (!f32 && (box ? p->radius == 1 : p->radius % 2 == 1)) return cells < 8000000 || cells >= (!box && p->radius == 1 ? 20000000 : 100000000);
-    return true;
+    if (f32 || box) return f32 || p->radius != 1 || cells >= 100000000;
+    const int64_t from[] = {8000000, 0, 8000000, 60000000}, to[] = {20000000, 0, 100000000, 100000000};
+    return cells < from[p->radius - 1] || cells >= to[p->radius - 1];
+}
+
+// Boxes whose arithmetic hides the HBM trip of every step, where the tiles of a step are whole and share out
+// evenly among the compute units.  us a step, single / two at a time: r = 4 1000 x 2000 FP32 (256 tiles) 9.8 /
+// 13, 4096^2 42 / 60, but 5000 x 400 (316 tiles) 16 / 13; r = 3 in 16 bits 4096^2 29 / 38, but 666 x 3000 (264
+// tiles) 10.4 / 9.2; FP32 r = 3 only on grids that marching bands fit worse: 15625 x 128 8.7 / 10.6, 6000 x 8192
+// 93 / 78.  Grids of few tiles wait for launches: 300^2, r = 4, two at a time 53 / 49 for six steps.
+bool single_steps(const st_plan* p) {
+    if (p->shape != SHAPE_BOX || p->radius < 3) return false;
+    const int64_t cells = p->rows * p->cols, tiles = (p->cols + STX - 1) / STX * ((p->rows + STY - 1) / STY);
+    if (cells < 1500000) return false;
+    const double fill = double(cells) / double((tiles + 255) / 256 * 256 * STX * STY);
+    if (p->radius == 4 || p->storage != ST_F32) return fill >= 0.75;
+    const double bands = double(march::band_count(p->cols, 1, march::halo_lanes(3, 2, 1), false));
+    return cells < 6000000 && fill >= 1.2 * double(p->cols) / (bands * 64);
 }
 
 int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa, int levels, hipStream_t s) {

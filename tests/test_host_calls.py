@@ -238,7 +238,10 @@ def test_tiles_that_margins_use_up(stub, rows, shape, r, tb, tile, kernel):
     (8192, 8192, "star", 1, "f16", {}, "sweep_step"), (4096, 4096, "box", 3, "f32", {}, "sweep_march"),
     (250000, 40, "box", 4, "f32", {}, "sweep_march"), (1024, 1023, "star", 1, "f32", {}, "sweep_block"),
     (1024, 1020, "star", 1, "bf16", {}, "sweep_block"), (1024, 1024, "star", 1, "f32", {"shift": 4}, "sweep_block"),
-    (1024, 1024, "star", 1, "f32", {"shift": 16}, "sweep_step")])
+    (1024, 1024, "star", 1, "f32", {"shift": 16}, "sweep_step"), (300, 300, "box", 3, "f32", {"tb": 1, "tile": (64, 64)}, "sweep_block"),
+    (2000, 3000, "box", 4, "f32", {"tb": 1, "tile": (64, 64)}, "sweep_step"),
+    (300, 300, "box", 4, "f32", {"tb": 1, "tile": (256, 32)}, "sweep_step"), (60000, 200, "box", 3, "f32", {}, "sweep_march"),
+    (40, 250000, "star", 3, "f32", {}, "sweep_march"), (100000, 256, "box", 1, "bf16", {}, "sweep_step")])
 def test_single_steps(stub, rows, cols, shape, r, storage, kw, kernel):
     """One step of an untuned plan runs where it is fastest; what LDS tiles cannot load whole goes elsewhere."""
     res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=1, storage=storage, **kw)
@@ -246,7 +249,7 @@ def test_single_steps(stub, rows, cols, shape, r, storage, kw, kernel):
 
 
 @pytest.mark.parametrize("rows,cols,r,storage,single", [
-    (1000, 2000, 4, "f32", True), (1000, 2000, 3, "bf16", True), (4096, 4096, 3, "f16", True), (15625, 128, 3, "f32", True),
+    (1000, 2000, 4, "f32", True), (1000, 2000, 3, "bf16", True), (4096, 4096, 3, "f16", True), (15625, 128, 3, "f32", True), (5000, 400, 4, "f32", False), (666, 3000, 3, "bf16", False),
     (1000, 1000, 4, "f32", False), (4096, 4096, 3, "f32", False), (6000, 8192, 3, "f32", False)])
 def test_large_boxes_take_single_steps(stub, rows, cols, r, storage, single):
     runs = {n: ask(stub, "run", rows=rows, cols=cols, shape="box", r=r, steps=n, storage=storage) for n in (2, 7)}
@@ -262,7 +265,7 @@ def test_large_boxes_take_single_steps(stub, rows, cols, r, storage, single):
     (250000, 40, "star", 3, "sweep_march"), (3000, 4000, "star", 2, "sweep_march<0,2,4,")])
 def test_marching_of_narrow_grids(stub, rows, cols, shape, r, kernel):
     """Bands that a narrow grid would leave empty are not taken, however many rows it has."""
-    res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=8)
+    res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=12)
     assert res["rc"] == 0 and all(c[1].startswith(kernel) for c in res["launches"])
 
 
