@@ -4,6 +4,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <tuple>
 #include <unordered_set>
 #include <vector>
 
@@ -40,15 +41,16 @@ size_t lds_limit() {
 
 int resident_blocks_of(const void* fn, size_t lds, int threads, int* blocks) {
     static std::mutex mu;
-    static std::map<std::pair<const void*, size_t>, int> cache;
+    static std::map<std::tuple<int, const void*, size_t, int>, int> cache;
     std::lock_guard<std::mutex> lk(mu);
-    auto it = cache.find({fn, lds});
+    int dev = 0;
+    ST_HIP_CHECK(hipGetDevice(&dev));
+    auto it = cache.find({dev, fn, lds, threads});
     if (it == cache.end()) {
-        int dev = 0, cus = 0, occ = 0;
-        ST_HIP_CHECK(hipGetDevice(&dev));
+        int cus = 0, occ = 0;
         ST_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         ST_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, lds));
-        it = cache.emplace(std::make_pair(fn, lds), std::max(1, cus * std::max(occ, 1))).first;
+        it = cache.emplace(std::make_tuple(dev, fn, lds, threads), std::max(1, cus * std::max(occ, 1))).first;
     }
     *blocks = it->second;
     return ST_OK;

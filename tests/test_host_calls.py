@@ -119,6 +119,17 @@ def case_varcoef(h, rows, cols, steps, tb, tile):
     return {"rc": rc, "launches": made(h.log(), "launch")}
 
 
+def case_occupancy(h):
+    """Workgroups at once of one kernel, asked for 256, 1024 and 256 threads a workgroup."""
+    fn = h.lib._ZN2st18resident_blocks_ofEPKvmiPi
+    out = []
+    for threads in (256, 1024, 256):
+        n = ctypes.c_int()
+        fn(ctypes.c_void_p(64), ctypes.c_size_t(0), ctypes.c_int(threads), ctypes.byref(n))
+        out.append(n.value)
+    return out
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -281,6 +292,10 @@ def test_more_threads_than_a_launch_holds(stub, case, kw, blocks):
     work = [int(c[2]) * int(c[3]) for c in res["launches"]]
     assert len(work) > 1 and sum(work) >= 2 ** 32 > max(work)
     assert blocks is None or blocks == sum(int(c[2]) for c in res["launches"])
+
+
+def test_occupancy_is_kept_by_workgroup_size(stub):
+    assert ask(stub, "occupancy") == [1024, 256, 1024]  # the stub's compute units hold 1024 threads
 
 
 if __name__ == "__main__":
