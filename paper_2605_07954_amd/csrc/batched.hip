@@ -228,6 +228,9 @@ size_t batch_lds_budget() { return std::min<size_t>(80 * 1024, lds_limit()); }
 
 }  // namespace
 
+// Whether grids of this width march when their class does: narrower than a band, they would leave lanes idle.
+static bool marches_at(int64_t cols) { return cols >= 64 * MV; }
+
 static int class_slot(const BatchDesc& d) { return d.shape * 3 + d.r - 1; }
 
 // Whether a grid and the halo around it fit the tile of batched_whole.
@@ -293,13 +296,12 @@ static int class_tile(const st_batch* B, const std::vector<int>& grids) {
 // more than p passes are a prefix of the order, one launch.  Marching: bands and segments per grid; at pass
 // p the full-depth grids are a prefix of the order and the grids finishing with a shallower pass follow in
 // groups of equal depth.
-// On the marching engine, grids narrower than a band stay on register tiles: a band would leave lanes idle.
 static void build_passes(st_batch* B) {
     for (int c = 0; c < 6; ++c) B->march[c] = B->tile[c] = st_batch::Passes();
     for (int g : B->tiled) {
         BatchDesc& d = B->desc[g];
         const int c = class_slot(d);
-        const bool marches = B->engine[c] == 1 && d.cols >= 64 * MV;
+        const bool marches = B->engine[c] == 1 && marches_at(d.cols);
         d.tb = marches ? B->depth[c]
                        : std::min(B->engine[c] == 1 ? 12 / d.r : B->depth[c] > 0 ? B->depth[c] : B->plan_tb[g], B->tb_max[g]);
         d.passes = (d.steps + d.tb - 1) / d.tb;
@@ -697,11 +699,12 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (tb_out) std::fill(tb_out, tb_out + 6, 0);
     if (engine_out) std::fill(engine_out, engine_out + 6, 0);
-    bool present[6] = {};
+    bool present[6] = {}, wide[6] = {};  // (wide: some grid of the class marches)
     int deepest[6] = {};
     for (int g : B->tiled) {
         const int c = class_slot(B->desc[g]);
         present[c] = true;
+        wide[c] = wide[c] || marches_at(B->desc[g].cols);
         deepest[c] = std::max(deepest[c], B->tb_max[g]);
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -760,7 +763,7 @@ extern "C" int stencil_batch_autotune(st_batch* B, const void* const* ins, void*
             if (sweep == 0) {
                 for (int cap : kCaps)
                     if (cap <= deepest[c]) cs.push_back({0, cap, 0, 0.0f});
-                for (int t = 1; t <= march_max_tb(c / 3, c % 3 + 1, 1); ++t)
+                for (int t = 1; wide[c] && t <= march_max_tb(c / 3, c % 3 + 1, 1); ++t)
                     for (int m : {0, 1, 2, 3, 4}) cs.push_back({1, t, m, 0.0f});
             }
             for (Cand& cd : cs) {

@@ -130,6 +130,20 @@ def case_occupancy(h):
     return out
 
 
+def case_batch_tuner(h, cols):
+    """What the tuner picks for a class of grids of these widths, and how many runs of the batch it times."""
+    plans = [h.st.stencil_plan(700, c, 2, h.weights("star", 2), 0.0, "f32", 0) for c in cols]
+    batch = h.st.stencil_batch_create(plans, [30] * len(cols), 0)
+    ptrs = [(ctypes.c_void_p * len(cols))(*[(f + 1 << 40) + (k << 32) for k in range(len(cols))]) for f in range(2)]
+    ws = np.zeros(h.st.stencil_batch_workspace_bytes(batch), np.uint8)
+    depth, engine = (ctypes.c_int * 6)(), (ctypes.c_int * 6)()
+    rc = h.lib.stencil_batch_autotune(batch, *ptrs, ws.ctypes.data, ws.nbytes, depth, engine, CALLER)
+    log = h.log()
+    last = max(i for i, c in enumerate(log) if c[0] == "record")
+    return {"rc": rc, "depth": depth[1], "engine": engine[1], "marched": any("march" in c[1] for c in log[:last] if c[0] == "launch"),
+            "runs": len(made(log, "record"))}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -296,6 +310,15 @@ def test_more_threads_than_a_launch_holds(stub, case, kw, blocks):
 
 def test_occupancy_is_kept_by_workgroup_size(stub):
     assert ask(stub, "occupancy") == [1024, 256, 1024]  # the stub's compute units hold 1024 threads
+
+
+def test_batch_tuner_of_narrow_grids(stub):
+    """A class that never marches (all its grids narrower than a band) is tuned over its tiles alone."""
+    narrow, wide = ask(stub, "batch_tuner", cols=[100, 200, 255]), ask(stub, "batch_tuner", cols=[100, 200, 256])
+    assert narrow["rc"] == wide["rc"] == 0
+    assert wide["engine"] == 1 and wide["marched"]
+    assert narrow["engine"] == 0 and not narrow["marched"] and narrow["depth"] in (1, 2, 3, 4, 6, 8, 12, 16)
+    assert narrow["runs"] < wide["runs"]
 
 
 if __name__ == "__main__":
