@@ -144,6 +144,25 @@ def case_batch_tuner(h, cols):
             "runs": len(made(log, "record"))}
 
 
+def case_graph(h, kind):
+    """Graphs made and replayed by runs of a plan, each call a change of one thing (or of none)."""
+    heat = kind == "varcoef"
+    plan = h.st.stencil_plan_varcoef(64, 64, 0.0, 2) if heat else h.st.stencil_plan(64, 64, 1, h.weights("star", 1), 0.0, "f32", 2)
+    h.st.stencil_set_blocking(plan, 2)
+    base = dict(x=1 << 40, k=2 << 40, out=3 << 40, ws=4 << 40, steps=24, stream=CALLER)
+    out = []
+    for change in ({}, {}, {"x": 5 << 40}, {}, {"out": 6 << 40}, {"ws": 7 << 40}, {"steps": 26}, {"stream": CALLER + 1}, {},
+                   {"k": 8 << 40}, {}, {"steps": 16}, {"steps": 24}):
+        base.update(change)
+        a = [base["x"]] + ([base["k"]] if heat else []) + [base["out"], base["steps"], base["ws"], 64 * 64 * 4, base["stream"]]
+        rc = (h.lib.stencil_run_varcoef if heat else h.lib.stencil_run)(plan, *a)
+        log = h.log()
+        live = len(made(log, "exec")) - len(made(log, "exec-"))
+        out.append([rc, len(made(log, "captured")), len(made(log, "replay")), live])
+    h.st.stencil_destroy(plan)
+    return {"calls": out, "end": len(made(h.log(), "exec-"))}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -319,6 +338,18 @@ def test_batch_tuner_of_narrow_grids(stub):
     assert wide["engine"] == 1 and wide["marched"]
     assert narrow["engine"] == 0 and not narrow["marched"] and narrow["depth"] in (1, 2, 3, 4, 6, 8, 12, 16)
     assert narrow["runs"] < wide["runs"]
+
+
+@pytest.mark.parametrize("kind", ["const", "varcoef"])
+def test_graph_is_made_again_for_whatever_changes(stub, kind):
+    """Runs of more than eight passes replay one graph per (input, diffusivity, output, workspace, steps, stream)."""
+    res = ask(stub, "graph", kind=kind)
+    k = int(kind == "varcoef")  # a constant plan has no diffusivity to change
+    # 16 steps are eight passes, enqueued directly; 24 after them find the graph as it was, but for their steps
+    assert [c[0] for c in res["calls"]] == [0] * 13
+    assert [c[1] for c in res["calls"]] == [1, 0, 1, 0, 1, 1, 1, 1, 0, k, 0, 0, 1]
+    assert [c[2] for c in res["calls"]] == [1] * 11 + [0, 1]
+    assert sum(c[3] for c in res["calls"]) == 1 == res["end"]  # one graph at a time
 
 
 if __name__ == "__main__":
