@@ -604,6 +604,8 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
             plan->tb = tb;
             plan->tile_x = tx;
             plan->tile_y = ty;
+            // (nor is a pass whose tile another replaces a candidate of its own: the other's is)
+            if (var == VARIANT_TILED && !step && tile_replaced(plan, tb)) continue;
             size_t need = 0;
             stencil_workspace_bytes(plan, sample_steps, &need);
             if (need > ws_bytes) continue;

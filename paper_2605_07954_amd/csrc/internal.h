@@ -114,6 +114,9 @@ int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa
 // last level)^2 and of x^2: 2 doubles for each of sums_tiles() tiles (0: no such pass for this plan).
 int launch_sums(const st_plan* p, const void* src, void* dst, int levels, double* sums, int64_t* tiles, hipStream_t s);
 int64_t sums_tiles(const st_plan* p, int levels);
+// Whether a pass of this depth runs on another register tile than the plan's (block::pick).
+bool tile_replaced(const st_plan* p, int levels);
+constexpr double VARCOEF_OPS = 9.0;  // operations of a cell and level of the variable-coefficient step
 // Cells a pass of `levels` levels on register tiles computes, margins included.
 double block_work(const st_plan* p, int levels);
 int launch_naive(const st_plan* p, const void* src, void* dst, const float* kappa, hipStream_t s);

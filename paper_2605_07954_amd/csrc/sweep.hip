@@ -363,15 +363,23 @@ BlockFn block_lookup(int storage, int shape, int r, int def) {
     return nullptr;
 }
 
-// The register tiles of a pass.
-block::Cover plan_cover(const st_plan* p, int levels) {
+// Operations of a cell and level.
+double cell_ops(const st_plan* p) {
     const int k = 2 * p->radius + 1;
-    return block::pick(tile_index(p->tile_x, p->tile_y), p->shape == SHAPE_BOX ? k * k + 1 : 2 * k, p->radius, levels, p->rows, p->cols);
+    return p->kind == KIND_VARCOEF ? VARCOEF_OPS : p->shape == SHAPE_BOX ? k * k + 1 : 2 * k;
+}
+
+// The register tiles of a pass.  One that sums keeps to the plan's tile as far as that goes: with the cells
+// before the last level in registers too the tallest tile, which others pick, spills (star r = 1 at 2048^2, 20
+// steps a check as 16 + 4 levels on 256 x 32 tiles 56 us, as 10 + 10 on picked ones 60).
+block::Cover plan_cover(const st_plan* p, int levels, bool sums) {
+    if (sums) return block::cover(tile_index(p->tile_x, p->tile_y), p->radius, levels, p->rows, p->cols);
+    return block::pick(tile_index(p->tile_x, p->tile_y), cell_ops(p), p->radius, levels, p->rows, p->cols);
 }
 
 // A pass on register tiles; with `sums` its last level's sums per tile (sweep_block_sums), `tiles` of them.
 int launch_block(const st_plan* p, const void* src, void* dst, int levels, double* sums, int64_t* tiles, hipStream_t s) {
-    const block::Cover c = plan_cover(p, levels);
+    const block::Cover c = plan_cover(p, levels, sums);
     if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
     if (c.tiles >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
     const block::Def& d = block::kDefs[c.def];
@@ -502,6 +510,12 @@ int supported_tiles(int* xy, int cap) {
         xy[2 * i + 1] = kTiles[i].ty;
     }
     return kNumTiles;
+}
+
+bool tile_replaced(const st_plan* p, int levels) {
+    const int def = tile_index(p->tile_x, p->tile_y);
+    return block::cover(def, p->radius, levels, p->rows, p->cols).def == def &&
+           block::pick(def, cell_ops(p), p->radius, levels, p->rows, p->cols).def != def;
 }
 
 int max_tb(const st_plan* p, int tx, int ty) {
@@ -650,12 +664,12 @@ int launch_pass(const st_plan* p, const void* src, void* dst, const float* kappa
 
 int64_t sums_tiles(const st_plan* p, int levels) {
     if (p->kind != KIND_CONST || p->bc != ST_BC_CONST) return 0;
-    const block::Cover c = plan_cover(p, levels);
+    const block::Cover c = plan_cover(p, levels, true);
     return c.def < 0 || c.tiles >= int64_t(1) << 31 ? 0 : c.tiles;
 }
 
 double block_work(const st_plan* p, int levels) {
-    const block::Cover c = plan_cover(p, levels);
+    const block::Cover c = plan_cover(p, levels, true);
     if (c.def < 0) return HUGE_VAL;
     const block::Def& d = block::kDefs[c.def];
     return double(c.tiles) * (64 * d.v * d.rw * d.nw) * levels;

@@ -221,7 +221,7 @@ size_t varcoef_lds_bytes(int tb, int tx, int ty) { return vlds_bytes(tb, tx, ty)
 
 // A pass of `levels` levels on register tiles over `fields` fields (or windows) of rows x cols cells.
 static int launch_vc_block(int tile, VArgs a, hipStream_t s) {
-    const block::Cover c = block::pick(tile, 9, 1, a.tb, a.rows, a.cols);
+    const block::Cover c = block::pick(tile, VARCOEF_OPS, 1, a.tb, a.rows, a.cols);
     if (c.def < 0) return fail(ST_EUNSUPPORTED, "temporal block too deep for the tile");
     if (c.tiles * a.fields >= int64_t(1) << 31) return fail(ST_EUNSUPPORTED, "too many tiles for one launch");
     const block::Def& d = block::kDefs[c.def];

@@ -163,6 +163,15 @@ def case_graph(h, kind):
     return {"calls": out, "end": len(made(h.log(), "exec-"))}
 
 
+def case_tuner(h, rows, cols, steps):
+    """The register-tile kernels that the tuner of a star of r = 1 times, and the tile and depth it keeps."""
+    plan = h.st.stencil_plan(rows, cols, 1, h.weights("star", 1), 0.0, "f32", 0)
+    tb, tx, ty = (ctypes.c_int() for _ in range(3))
+    need = h.st.stencil_workspace_bytes(plan, 2) + (64 << 20)
+    rc = h.lib.stencil_autotune(plan, 1 << 40, 2 << 40, 3 << 40, need, steps, *map(ctypes.byref, (tb, tx, ty)), CALLER)
+    return {"rc": rc, "launches": made(h.log(), "launch"), "kept": [tb.value, tx.value, ty.value]}
+
+
 CASES = {k[5:]: f for k, f in list(globals().items()) if k.startswith("case_")}
 
 
@@ -350,6 +359,15 @@ def test_graph_is_made_again_for_whatever_changes(stub, kind):
     assert [c[1] for c in res["calls"]] == [1, 0, 1, 0, 1, 1, 1, 1, 0, k, 0, 0, 1]
     assert [c[2] for c in res["calls"]] == [1] * 11 + [0, 1]
     assert sum(c[3] for c in res["calls"]) == 1 == res["end"]  # one graph at a time
+
+
+def test_tuner_times_a_replaced_tile_once(stub):
+    """48 steps of 2048^2 at 16 levels: three passes each on the tallest tile, for the tiles that cannot hold the
+    depth at all; the ones it replaces are not timed again under their own name."""
+    res = ask(stub, "tuner", rows=2048, cols=2048, steps=48)
+    assert res["rc"] == 0
+    tall = [c for c in res["launches"] if c[1] == "sweep_block<0,1,0,2,8,16>" and int(c[2]) == 22 * 22]
+    assert len(tall) == 2 * 3 * 3  # two tiles, three runs of three passes
 
 
 if __name__ == "__main__":
