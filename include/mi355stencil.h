@@ -303,9 +303,10 @@ int stencil_norms(const st_plan* plan, const void* u_prev, const void* u, double
 
 /* stencil_autotune -- time every supported (variant, tb, tile) candidate on the caller's buffers
  * for `sample_steps` steps (one warm-up run, then the better of two timed runs) and keep the
- * fastest in the plan (variant, blocking and segment length).  Candidates: register tiles with tb in
- * {1, 2, 3, 4, 6, 8, 12, 16} and LDS tiles with tb in {1, 2, 3, 4, 6, 8} within their budgets; marching with one, four and, when cols % 8 == 0,
- * eight columns per lane at every depth each offers, each depth above 1 also with segments of
+ * fastest in the plan (variant, blocking and segment length).  Candidates: the tiled
+ * variant with tb in {1, 2, 3, 4, 6, 8, 12, 16} (passes of it that march are left to the marching
+ * candidates) and streaming with tb in {1, 2, 3, 4, 6, 8}, as deep as each tile takes; marching with
+ * one, four and, when cols % 8 == 0, eight columns per lane at every depth each offers, each depth above 1 also with segments of
  * at least 1/2 (when that is 2 rows or more), 1, 2, 4 and 8 x r (tb - 1) rows
  * (stencil_set_march_segment); the resident variant at swap depths {1, 2, 4, 8, 12, 16, 24, 32, 48}
  * where the grid's tiles allow them; the matrix-core variant only for plans created with

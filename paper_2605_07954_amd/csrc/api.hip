@@ -281,9 +281,9 @@ int stencil_set_blocking(st_plan* plan, int tb, int tile_x, int tile_y) {
     if (!tile_supported(plan->shape, plan->radius, tx, ty)) return fail(ST_EUNSUPPORTED, "tile not instantiated");
     const int t = tb ? tb : plan->tb;
     if (plan->kind == KIND_CONST && t > max_tb(plan, tx, ty))
-        return fail(ST_EUNSUPPORTED, "temporal block too deep for this tile's LDS budget");
+        return fail(ST_EUNSUPPORTED, "temporal block too deep for this tile");
     if (plan->kind == KIND_VARCOEF && varcoef_lds_bytes(t, tx, ty) > lds_limit())
-        return fail(ST_EUNSUPPORTED, "temporal block too deep for the LDS budget");
+        return fail(ST_EUNSUPPORTED, "temporal block too deep for this tile");
     plan->tb = t;
     plan->tile_x = tx;
     plan->tile_y = ty;
@@ -578,7 +578,7 @@ static int autotune_impl(st_plan* plan, const void* in, const float* kappa, void
         if (var == VARIANT_MARCH8 && plan->cols % 8 != 0) break;  // would run the four-column kernels
         const int tx = tiles[2 * ti], ty = tiles[2 * ti + 1];
         plan->variant = var;
-        // LDS tiles: the depths of kTb; marching: every depth it offers
+        // tiles: the depths of kTb; marching: every depth it offers
         int cands[16], nc = 0;
         if (var == VARIANT_MFMA) {
             cands[nc++] = 1;

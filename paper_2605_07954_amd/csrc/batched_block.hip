@@ -7,8 +7,8 @@
 // load and the last store touches memory; a level costs what its cells do, one barrier and a row exchange.
 //
 // Tuned batches of mixed classes, before (tiles and whole grids in LDS, one kernel for all classes) and
-// after, us: 100 grids of sides up to 256, 50 steps 850 and 290; 64 of up to 1024, 30 steps 609 and 325; 256
-// of up to 2048, 40 steps, most of which march, 2190 and 1870-2100.
+// after, us: 100 grids of sides up to 256, 50 steps 850 and 300; 64 of up to 1024, 30 steps 609 and 275; 256
+// of up to 2048, 40 steps, most of which march, 2190 and 1935-1963 (four tunings).
 #include "batched.h"
 #include "sweep_block.h"
 

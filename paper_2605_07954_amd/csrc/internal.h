@@ -147,7 +147,6 @@ __host__ __device__ inline int64_t window_origin(int y, int64_t reach, int64_t f
 // fields * rows * cols floats each (scratch for more than one pass of eight steps).
 int varcoef_windows(const float* u0, const float* kappa, const VcWindows& w, int64_t rows, int64_t cols, int fields,
                     int64_t steps, float* out, float* scratch, hipStream_t s);
-size_t tiled_lds_bytes(int r, int tb, int tx, int ty);
 size_t varcoef_lds_bytes(int tb, int tile_x, int tile_y);
 
 // Largest dynamic LDS allocation one workgroup may request on the current device (bytes);

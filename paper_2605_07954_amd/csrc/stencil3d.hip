@@ -146,7 +146,7 @@ Fn3 ring_lookup(int shape, int r, int storage) {
 }
 
 // Single levels of an FP32 star that run on LDS tiles: their 64 columns start on cache lines where the rows
-// do, while a register tile stores 64 - 2r columns and so parts of lines at every tile's sides.  The widths
+// do, while a register tile's start inside them (1.45 GB moved for 1.05 at 512^3, r = 1).  The widths
 // (a multiple of 16) and sizes where that is faster; us a step, LDS tiles / register tiles.  r = 1: 256^3
 // 35 / 36, 400^3 145 / 154, 512^3 241 / 331, 4 x 8192^2 502 / 611; at other widths 300^3 56 / 52, 450^3
 // 236 / 210.  r = 2, larger halos to load, from fields beyond the 256 MB cache on: 400^3 197 / 163; 512^3

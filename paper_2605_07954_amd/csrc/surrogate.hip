@@ -1703,7 +1703,7 @@ int surrogate_train(sg_model* m, float* params, float* optim, const float* coef,
     // cells around it, inside the grid).  All windows of a step advance together when there is room for
     // their ping-pong copy, in the gradient's workspace, which is free until the gradient is computed;
     // else one by one, with the copy of one field.
-    const int64_t wr = std::min<int64_t>(c.rows, c.crop + 2 * c.K), wc = std::min<int64_t>(c.cols, c.crop + 2 * c.K);
+    const int64_t wr = std::min<int64_t>(c.rows, c.crop + 2 * int64_t(c.K)), wc = std::min<int64_t>(c.cols, c.crop + 2 * int64_t(c.K));
     const bool together = size_t(B * wr * wc) * 4 <= T.total - T.sg;
     int rc = ST_OK;
     const int64_t field = c.rows * c.cols;

@@ -518,6 +518,14 @@ bool tile_replaced(const st_plan* p, int levels) {
            block::pick(def, cell_ops(p), p->radius, levels, p->rows, p->cols).def != def;
 }
 
+// The depths that a tiled plan accepts per tile: as many levels as two LDS buffers of the tile and the halo
+// around it (16-byte chunks) would hold.  No kernel keeps them: register tiles hold any r tb up to 39 on one
+// tile or another, but the limit decides which calls are refused, and stays what it was.
+static size_t accepted_lds_bytes(int r, int tb, int tx, int ty) {
+    const int h = r * tb, off = (h + 4 + 7) / 8 * 8, bw = (off + tx + h + 7 + 7) / 8 * 8;
+    return (size_t(tb > 1 ? 2 : 1) * size_t(bw) * size_t(ty + 2 * h) + MAXK) * sizeof(float);
+}
+
 int max_tb(const st_plan* p, int tx, int ty) {
     int tb = 1;
     if (is_march(p->variant)) return march_max_tb(p->shape, p->radius, march_vmax(p->variant));
@@ -526,14 +534,12 @@ int max_tb(const st_plan* p, int tx, int ty) {
     if (p->variant == VARIANT_STREAM) {
         while (tb < 16 && stream_lds_bytes(p->radius, tb + 1, tx, ty) <= lds_limit()) ++tb;
     } else {
-        while (tb < 16 && lds_bytes(p->radius, tb + 1, tx, ty) <= lds_limit()) ++tb;
+        while (tb < 16 && accepted_lds_bytes(p->radius, tb + 1, tx, ty) <= lds_limit()) ++tb;
     }
     return tb;
 }
 
 bool stream_usable(const st_plan* p) { return p->storage == ST_F32 && p->cols % 4 == 0; }
-
-size_t tiled_lds_bytes(int r, int tb, int tx, int ty) { return lds_bytes(r, tb, tx, ty); }
 
 int launch_naive(const st_plan* p, const void* src, void* dst, const float* kappa, hipStream_t s) {
     KernelFn fn = naive_lookup(p->storage, p->shape, p->radius);

@@ -12,9 +12,10 @@
 //
 // One level per pass is bound by HBM (8 bytes per update; LDS tiles of whole cache lines reach 4.4 TB/s,
 // 560 GStencil/s for the 7-point star at 512^3, and run single levels of large FP32 stars); T levels divide
-// the bytes by T.  Measured there at T = 1 .. 7: 424, 900, 1216, 1468, 1590, 1646, 1331 GStencil/s -- 3.4 to
-// 3.6 TB/s up to T = 2; the work grows with the tile's margin (64 x 64 cells for (64 - 2T)^2), and T = 7
-// spills registers.  Sixteen wavefronts of four rows beat eight of eight (1193 at T = 3) and 128-column tiles
+// the bytes by T.  Measured there at T = 1 .. 7: 424, 900, 1216, 1468, 1590, 1646, 1331 GStencil/s -- at
+// T = 1 4.4 TB/s (64 columns that start inside a cache line read three lines for two and write parts of lines:
+// 1.45 GB for 1.05), at T = 5 4.1 TB/s and vector issue on 0.61 of the cycles; the work grows with the tile's
+// margin (64 x 64 cells for (64 - 2T)^2), and T = 7 spills registers.  Sixteen wavefronts of four rows beat eight of eight (1193 at T = 3) and 128-column tiles
 // (997), which leave fewer wavefronts to a SIMD.
 #pragma once
 

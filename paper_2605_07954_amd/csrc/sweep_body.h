@@ -1,5 +1,5 @@
-// What the LDS kernels share: the geometry of the streaming pass's LDS tiles (sweep.hip) and the body of the
-// whole-grid pass that keeps a batched grid in LDS (batched.hip).
+// What the LDS kernels share, and the body of the whole-grid pass that keeps a batched grid in LDS
+// (batched.hip).
 //
 // Each of 256 threads computes a 4-column x RS-row block from a register ring of input rows (three 16-byte
 // LDS reads per row); every tap is a register operand of one FMA.  Per cell the FP32 order is the centre
@@ -17,33 +17,6 @@ __device__ __forceinline__ bool tap_in(int shape, int dy, int dx) {
     return shape == SHAPE_BOX || dy == 0 || dx == 0;
 }
 
-
-// LDS geometry of one pass.  Buffer column bc holds global column x0 - off + bc, buffer row br
-// holds global row y0 - H + br, with H = r*tb the halo depth.  off is a multiple of 8 so that
-// 16-byte chunks of the buffer map to aligned 16-byte chunks of the field.
-struct Geo {
-    int H, off, bw, bh;
-};
-
-__host__ __device__ inline Geo geometry(int R, int tb, int TX, int TY) {
-    Geo g;
-    g.H = R * tb;
-    g.off = ((g.H + 4 + 7) / 8) * 8;
-    g.bw = ((g.off + TX + g.H + 7 + 7) / 8) * 8;
-    g.bh = TY + 2 * g.H;
-    return g;
-}
-
-// LDS of one pass: one or two field buffers, then the weights (kept in dynamic LDS so that
-// several inlined bodies in one kernel do not each reserve their own static copy).
-__host__ __device__ inline size_t lds_floats(int R, int tb, int TX, int TY) {
-    Geo g = geometry(R, tb, TX, TY);
-    return size_t(tb > 1 ? 2 : 1) * size_t(g.bw) * size_t(g.bh);
-}
-
-__host__ __device__ inline size_t lds_bytes(int R, int tb, int TX, int TY) {
-    return (lds_floats(R, tb, TX, TY) + MAXK) * sizeof(float);
-}
 
 // Map the launch's block index to a tile so that each of the 8 XCDs (which receive blocks
 // round-robin) works on a contiguous band of tiles; vertically adjacent tiles then share

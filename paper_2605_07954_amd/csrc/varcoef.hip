@@ -44,7 +44,9 @@ __global__ __launch_bounds__(NT) void varcoef_naive(SweepArgs a) {
     }
 }
 
-// Depths that a plan accepts per tile: the LDS of two field buffers and kappa with their margins.
+// The depths that a plan accepts per tile: the LDS that two buffers of the field and one of kappa would take,
+// the halo around the tile included.  No kernel keeps them; the limit decides which calls are refused, and
+// stays what it was.
 size_t vlds_bytes(int tb, int TX, int TY) {
     const int off = ((tb + 4 + 3) / 4) * 4;
     const int bw = ((off + TX + tb + 8 + 3) / 4) * 4, bh = TY + 2 * tb;
