@@ -324,7 +324,7 @@ def extra_star9_profile(torch, lib, stream, variant: int = 2, tb: int = 6, stora
 
 
 def extra_batched(torch, lib, stream) -> dict:
-    """256 grids, one hipGraph launch of the batched kernels vs per-grid launches (each grid autotuned)."""
+    """256 grids in one call of the batched kernels vs per-grid launches (each grid autotuned)."""
     probs = wl.batch_problems()
     ins = [torch.from_numpy(q.u0).to("cuda") for q in probs]
     outs = [torch.empty_like(i) for i in ins]

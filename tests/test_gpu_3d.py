@@ -51,7 +51,7 @@ def run3(g, lib, u, W, b, steps, storage="f32", flags=0, noalloc=False):
             ws = torch.empty_like(x)
             lib.stencil_run(plan, x, out, steps, ws)
             if flags:
-                lib.stencil_run(plan, x, out, steps, ws)  # a replay of the captured graph
+                lib.stencil_run(plan, x, out, steps, ws)  # again (few passes are enqueued directly)
         torch.cuda.synchronize()
         return g.to_host(out)
     finally:

@@ -1,5 +1,5 @@
-"""GPU parity of the batched persistent kernel: every grid of a mixed batch equals the FP32-canonical
-oracle bit for bit (and the per-grid launch path), with and without the captured hipGraph."""
+"""GPU parity of the batched kernels: every grid of a mixed batch equals the FP32-canonical oracle bit
+for bit (and the per-grid launch path), on the caller's stream and on the batch's own branch streams."""
 import os
 import sys
 
@@ -48,7 +48,7 @@ def _run_batch(g, problems, flags, tbs=None, tiles=None, reps=2):
                 lib.stencil_run_batched(batch, ins, outs, ws)
                 torch.cuda.synchronize()
                 results.append([g.to_host(o) for o in outs])
-                _ = (ins[0] * 3).sum().item()  # eager work between replays
+                _ = (ins[0] * 3).sum().item()  # eager work between runs
             return results
         finally:
             lib.stencil_batch_destroy(batch)
@@ -116,7 +116,7 @@ def test_batched_config_sample(g):
 
 def test_batched_autotune_bitwise(g):
     """The batch autotuner changes only the depth of each class's passes: results stay bitwise equal
-    to the oracle, before and after tuning, with and without the graph."""
+    to the oracle, before and after tuning, on branch streams."""
     import torch
     import paper_2605_07954_amd as lib
     problems = _mixed(20, 11)
@@ -128,7 +128,7 @@ def test_batched_autotune_bitwise(g):
             ins = [g.to_dev(p.u0) for p in problems]
             outs = [torch.empty_like(x) for x in ins]
             ws = torch.empty(lib.stencil_batch_workspace_bytes(batch), dtype=torch.uint8, device=g.DEV)
-            lib.stencil_run_batched(batch, ins, outs, ws)  # builds the graph with the plans' depths
+            lib.stencil_run_batched(batch, ins, outs, ws)  # with the plans' depths
             caps = lib.stencil_batch_autotune(batch, ins, outs, ws)
             say("chosen caps", caps)
             assert caps and all(e in ("tiles", "march") and 1 <= d <= 16 for (e, d) in caps.values())
@@ -148,10 +148,10 @@ def test_batched_autotune_bitwise(g):
 
 @pytest.mark.parametrize("graph", [0, 2])
 def test_batched_engines_every_class_bitwise(g, graph):
-    """Every stencil class on LDS tiles and on the marching engine (four columns per lane: vector
-    accesses for widths divisible by 4, element accesses otherwise) at every
+    """Every stencil class on register tiles and on the marching engine (four columns per lane, vector
+    accesses at every width; grids narrower than a band stay on tiles) at every
     depth, with a shallower last pass (step counts not divisible by the depth): bitwise equal to the
-    FP32-canonical oracle, directly and through the graph."""
+    FP32-canonical oracle, on the caller's stream and on branch streams."""
     import torch
     import paper_2605_07954_amd as lib
     rng = np.random.default_rng(21)

@@ -84,7 +84,7 @@ def test_register_tiles_varcoef_bitwise(g, tile, tb):
 
 def test_tiled_plan_of_a_large_grid(g):
     """A grid large enough that the tiled variant's passes run on the marching kernels, whole passes and a
-    shallower last one: the same bits as the register tiles give on its top rows' light cone."""
+    shallower last one: the whole field equals the oracle's."""
     import torch
     import paper_2605_07954_amd as lib
     rows, cols, r, tb, steps = 2899, 2903, 1, 6, 8

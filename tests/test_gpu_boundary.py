@@ -84,7 +84,7 @@ def test_boundary_march_bitwise(g, bc, case):
                     np.testing.assert_array_equal(g.to_host(out), ref, err_msg=f"{bc} variant {variant} tb {tb} seg 5")
             finally:
                 lib.stencil_destroy(plan)
-    # a buffer off a 16-byte boundary takes element accesses
+    # a buffer off a 16-byte boundary
     plan = lib.stencil_plan(rows, cols, r, W, 0.0, "f32", lib.ST_FLAG_GRAPH)
     try:
         lib.stencil_set_boundary(plan, kind, fd)
@@ -92,7 +92,7 @@ def test_boundary_march_bitwise(g, bc, case):
         xb[1:].copy_(x.reshape(-1))
         ob = torch.full_like(xb, float("nan"))
         ws = torch.empty_like(xb)
-        for _ in range(2):  # graph capture, then a replay
+        for _ in range(2):  # (up to eight passes are enqueued directly)
             lib.stencil_run(plan, xb[1:], ob[1:], steps, ws)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(g.to_host(ob[1:]).reshape(rows, cols), ref, err_msg=f"{bc} unaligned, graph")

@@ -206,7 +206,7 @@ def test_bitwise_across_blocking_and_graph(g):
             np.testing.assert_array_equal(got, base)
             checked += 1
     assert checked >= 12
-    # graph replays (with eager work between them) equal the direct run, every time
+    # graph-flagged runs (with eager work between them) equal the direct run, every time
     plan = lib.stencil_plan(rows, cols, 3, W, 0.0, "f32", lib.ST_FLAG_GRAPH)
     try:
         x = g.to_dev(u0)
@@ -371,7 +371,7 @@ def test_varcoef_tiles_and_autotune(g):
         lib.stencil_run_varcoef(plan, x, k, out, steps, ws)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(g.to_host(out), ref32)
-        # same buffers, another diffusivity field: the cached graph must not replay the old one
+        # same buffers, another diffusivity field: nothing of the old one may be kept
         _, kap2 = wl.varcoef_problem(rows, cols, seed=6)
         ref2 = oracle.varcoef_f32(u0, kap2, b, steps)
         k2 = g.to_dev(kap2)
