@@ -66,6 +66,33 @@ int march_max_tb(int shape, int radius, int vmax) {
 
 bool march_usable(const st_plan* p) { return p->kind == KIND_CONST && p->radius <= 4; }
 
+// Passes at widths that are no multiple of four where four elements per lane are faster than one vector all the
+// same: at such widths the vector form can need a band more, and its rows start on no vector boundary, so that
+// what its single access saves depends on what else the kernel does.  Measured at 2000 x 2003, 3000 x 3002 and 4099 x 5003 (one pass, us, vector / elements):
+//   boxes of r = 4, two levels: periodic BF16 328 / 206, 709 / 445, 1057 / 645, FP32 384 / 307, 825 / 615, 1284 /
+//   925 (at 700 x 257 123 / 127); framed FP32 375 / 314, 803 / 620, 1116 / 884 (framed BF16: no difference);
+//   stars of r = 1 (halo value 0; 0.5), four levels: FP32 43 / 38, 62 / 55, 106 / 100; 44 / 38, 65 / 55, 110 / 100
+//   (at 1000 x 701 19 / 24), F16 38 / 36, 51 / 48, 76 / 72; 40 / 35, 56 / 47, 72 / 70, BF16 34 / 36, 46 / 46, 74 /
+//   69; 36 / 35, 50 / 45, 73 / 67; five, F16: 40 / 47, 60 / 62, 95 / 87; 45 / 47, 67 / 61, 93 / 85 (BF16 54 / 59
+//   and FP32 56 / 64 at 3000 x 3002); six, FP32: 45 / 56, 66 / 62, 106 / 105; 48 / 55, 72 / 63, 110 / 104, BF16 43 /
+//   53, 62 / 62, 92 / 92; 49 / 53, 71 / 61, 97 / 90;
+//   boxes of r = 1, six levels: FP32 65 / 65, 94 / 88, 147 / 144; 72 / 65, 93 / 88, 147 / 141, BF16 64 / 67, 95 /
+//   90, 153 / 146; 73 / 67, 95 / 90, 153 / 146 (at 1000 x 701 34 / 42; 39 / 41);
+//   stars of r = 4, three levels, BF16: 71 / 83, 93 / 109, 176 / 155.
+static bool element_accesses(const st_plan* p, int levels) {
+    if (p->cols % 4 == 0) return false;
+    const bool f32 = p->storage == ST_F32;
+    const int64_t cells = p->rows * p->cols;
+    if (p->bc != ST_BC_CONST)
+        return p->shape == SHAPE_BOX && p->radius == 4 && levels == 2 && (p->bc == ST_BC_PERIODIC || f32);
+    if (p->radius == 1 && p->shape == SHAPE_BOX) return levels == 6 && cells >= 2500000;
+    if (p->radius == 1) {
+        if (levels == 4) return cells >= (f32 ? 2500000 : 6000000);
+        return (levels == 6 || (levels == 5 && p->storage == ST_F16)) && cells >= 6000000;
+    }
+    return p->radius == 4 && levels == 3 && !f32 && cells >= 15000000;
+}
+
 int launch_march(const st_plan* p, const void* src, void* dst, int levels, int vmax, hipStream_t s) {
     // Four columns per lane with one vector access per lane and row, at any width and alignment, when no
     // lane's vector straddles the grid's side (march_layout.h; 4099 x 5003, halo 1.5, us a pass with four
@@ -77,7 +104,7 @@ int launch_march(const st_plan* p, const void* src, void* dst, int levels, int v
     const bool xbc = p->bc != ST_BC_CONST;
     if (xbc && vmax == 8) vmax = 4;
     const bool aligned = (reinterpret_cast<uintptr_t>(src) % 16) == 0 && (reinterpret_cast<uintptr_t>(dst) % 16) == 0;
-    const int mode = vmax == 1 ? 1 : vmax == 8 && aligned && p->cols % 8 == 0 ? 8 : march::whole_lanes(p->cols, 4) ? 4 : 0;
+    const int mode = vmax == 1 ? 1 : vmax == 8 && aligned && p->cols % 8 == 0 ? 8 : march::whole_lanes(p->cols, 4) && !element_accesses(p, levels) ? 4 : 0;
     const int V = mode == 8 ? 8 : mode == 1 ? 1 : 4;
     MarchFn fn = march_lookup(p->storage, mode, p->shape, p->radius, levels, xbc, p->bc == ST_BC_PERIODIC);
     if (!fn) return fail(ST_EUNSUPPORTED, "no row-marching kernel for this shape/radius/depth");

@@ -112,6 +112,19 @@ def case_run(h, rows, cols, shape, r, steps, storage="f32", tb=0, tile=(0, 0), s
     return {"rc": rc, "launches": made(h.log(), "launch")}
 
 
+def case_march(h, rows, cols, shape, r, storage, tb, bc):
+    """The kernel of one pass of the marching variant."""
+    plan = h.st.stencil_plan(rows, cols, r, h.weights(shape, r), 0.0, storage, 0)
+    h.st.stencil_set_blocking(plan, 1)
+    h.st.stencil_set_variant(plan, h.st.ST_VARIANT_MARCH)
+    if bc != "const":
+        frame = ctypes.c_void_p(4 << 40) if bc == "frame" else None
+        assert h.lib.stencil_set_boundary(plan, {"periodic": h.st.ST_BC_PERIODIC, "frame": h.st.ST_BC_FRAME}[bc], frame) == 0
+    h.st.stencil_set_blocking(plan, tb)
+    rc = h.lib.stencil_run(plan, 1 << 40, 2 << 40, tb, 3 << 40, h.st.stencil_workspace_bytes(plan, tb), CALLER)
+    return {"rc": rc, "kernels": [c[1] for c in made(h.log(), "launch") if "march" in c[1]]}
+
+
 def case_varcoef(h, rows, cols, steps, tb, tile):
     plan = h.st.stencil_plan_varcoef(rows, cols, 0.0, 0)
     h.st.stencil_set_blocking(plan, tb, *tile)
@@ -320,6 +333,21 @@ def test_marching_of_narrow_grids(stub, rows, cols, shape, r, kernel):
     """Bands that a narrow grid would leave empty are not taken, however many rows it has."""
     res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=12)
     assert res["rc"] == 0 and all(c[1].startswith(kernel) for c in res["launches"])
+
+
+@pytest.mark.parametrize("rows,cols,shape,r,storage,tb,bc,elements", [
+    (1000, 701, "box", 4, "bf16", 2, "periodic", True), (1000, 701, "box", 4, "f32", 2, "frame", True),
+    (1000, 701, "box", 4, "bf16", 2, "frame", False), (1000, 701, "box", 4, "f32", 1, "periodic", False),
+    (1000, 704, "box", 4, "f32", 2, "periodic", False), (2000, 2003, "star", 1, "f32", 4, "const", True),
+    (1000, 701, "star", 1, "f32", 4, "const", False), (2000, 2003, "star", 1, "bf16", 4, "const", False),
+    (2000, 2003, "box", 1, "f16", 6, "const", True), (2000, 2003, "star", 1, "f32", 6, "const", False),
+    (3000, 3002, "star", 1, "bf16", 6, "const", True), (3000, 3002, "star", 1, "f16", 5, "const", True),
+    (4099, 5003, "star", 4, "f16", 3, "const", True), (4099, 5003, "star", 4, "f32", 3, "const", False)])
+def test_marching_with_element_accesses(stub, rows, cols, shape, r, storage, tb, bc, elements):
+    res = ask(stub, "march", rows=rows, cols=cols, shape=shape, r=r, storage=storage, tb=tb, bc=bc)
+    assert res["rc"] == 0 and len(res["kernels"]) == 1
+    args = res["kernels"][0].split("<")[1].split(">")[0].split(",")
+    assert args[2] == "4" and (args[5] == "false") == elements, res["kernels"]
 
 
 @pytest.mark.parametrize("case,kw,blocks", [

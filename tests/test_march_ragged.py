@@ -76,3 +76,38 @@ def test_ragged_march_bitwise(g, cols, shape, r, tb, storage, bc):
         ref = (oracle.stencil_bc_f32(u0, W, bc, steps, frame) if storage == "f32"
                else oracle.stencil_bc_lowp(host, W, bc, steps, storage))
     np.testing.assert_array_equal(got, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,cols,shape,r,tb,storage,bc", [
+    (37, 485, "box", 4, 2, "f32", "periodic"), (37, 515, "box", 4, 2, "bf16", "periodic"), (37, 751, "box", 4, 2, "f32", "frame"),
+    (5000, 501, "star", 1, 4, "f32", "const"), (12000, 501, "star", 1, 6, "f16", "const"),
+    (8003, 751, "box", 1, 6, "f32", "const"), (30001, 501, "star", 4, 3, "bf16", "const")])
+def test_ragged_march_with_element_accesses(g, rows, cols, shape, r, tb, storage, bc):
+    """Zero tolerance: both sides run the same FP32 operations in the same order."""
+    import paper_2605_07954_amd as lib
+    W = wl.random_footprint_weights(np.random.default_rng(r), shape, r)
+    rng = np.random.default_rng(cols)
+    u0 = rng.random((rows, cols), dtype=np.float32)
+    host = u0 if storage == "f32" else oracle.to_bits(u0, storage)
+    frame = rng.random(oracle.frame_elems(rows, cols, r), dtype=np.float32) if bc == "frame" else None
+    x = g.to_dev(host)
+    out, ws = x.clone(), x.clone()
+    fdev = g.to_dev(frame) if frame is not None else None
+    plan = lib.stencil_plan(rows, cols, r, W, 0.0, storage, 0)
+    try:
+        lib.stencil_set_blocking(plan, 1, 0, 0)
+        lib.stencil_set_variant(plan, lib.ST_VARIANT_MARCH)
+        if bc != "const":
+            lib.stencil_set_boundary(plan, {"periodic": lib.ST_BC_PERIODIC, "frame": lib.ST_BC_FRAME}[bc], fdev)
+        lib.stencil_set_blocking(plan, tb, 0, 0)
+        lib.stencil_run(plan, x, out, tb + 1, ws)
+        got = g.to_host(out)
+    finally:
+        lib.stencil_destroy(plan)
+    if bc == "const":
+        ref = (oracle.stencil_f32(u0, W, 0.0, tb + 1) if storage == "f32" else oracle.stencil_lowp(host, W, 0.0, tb + 1, storage))
+    else:
+        ref = (oracle.stencil_bc_f32(u0, W, bc, tb + 1, frame) if storage == "f32"
+               else oracle.stencil_bc_lowp(host, W, bc, tb + 1, storage))
+    np.testing.assert_array_equal(got, ref)
