@@ -210,10 +210,13 @@ inline Cover cover(int def, int r, int levels, int64_t rows, int64_t cols) {
 
 // The tile that a plan's pass runs on: the plan's own (`def`), unless its margins would leave less than
 // two fifths of its cells and another is estimated to take less than 0.85 of its time: the instructions that
-// a compute unit issues per level (`ops` a cell, a few per row, and the exchange) for its share of the 256.
+// a compute unit issues per level (`ops` a cell, a few per row, and the exchange) for the most tiles that one of
+// the 256 gets, each after the first at 0.7 of it (their waits overlap).  The constants are fitted to 4 passes of
+// every tile at 12 grids up to 2000^2, six footprints, 3 to 16 levels: of 1024 choices 495 are more than 3 % faster
+// than the own tile, and 4 slower (the most 5 %).
 // Three passes at 2000^2, us, own tile / picked: star r = 4, 64 x 64, 6 levels (6 % kept) 592 / 157 (LDS tiles,
 // whose halo lies around the tile, took 295); box r = 2, 64 x 64, 12 levels 1429 / 351; star r = 4, 128 x 64, 4
-// levels (38 %) 94 / 88.  From two fifths up the own tile was never slower than LDS tiles.  Small grids are
+// levels (38 %) 95 / 89.  From two fifths up the own tile was never slower than LDS tiles.  Small grids are
 // often best on small tiles all the same: star r = 1 at 512^2, 64 x 64, 16 levels (25 %) 8.0 us a pass, on the
 // next tile 9.7.
 inline Cover pick(int def, double ops, int r, int levels, int64_t rows, int64_t cols) {
@@ -225,8 +228,8 @@ inline Cover pick(int def, double ops, int r, int levels, int64_t rows, int64_t 
     }
     auto time = [&](const Cover& c) {
         const Def& d = kDefs[c.def];
-        const double share = c.tiles <= 256 ? 1.0 : double(c.tiles) / 256 + 0.3;  // (a last round is partly hidden)
-        return share * d.nw * (d.rw * d.v * ops + 6.0 * d.rw + 40.0);
+        const double share = 0.3 + 0.7 * double((c.tiles + 255) / 256);  // (tiles on one compute unit overlap)
+        return share * d.nw * (d.rw * d.v * ops + 4.0 * d.rw + 15.0);
     };
     Cover best = own;
     if (own.def < 0) return own;

@@ -297,6 +297,16 @@ def test_tiles_that_margins_use_up(stub, rows, shape, r, tb, tile, kernel):
     assert {c[1] for c in res["launches"]} == {f"sweep_block<0,{r},{int(shape == 'box')},{kernel}>"}
 
 
+@pytest.mark.parametrize("rows,cols,shape,r,tb,tile,kernel", [
+    (1040, 432, "star", 1, 16, (64, 64), "1,8,8"), (1500, 900, "star", 3, 3, (256, 32), "4,4,8"),
+    (2000, 2000, "box", 1, 12, (64, 64), "2,8,8")])
+def test_tiles_by_the_most_one_unit_gets(stub, rows, cols, shape, r, tb, tile, kernel):
+    """Tiles whose margins are wide are weighed by how many of them the busiest compute unit takes."""
+    res = ask(stub, "run", rows=rows, cols=cols, shape=shape, r=r, steps=3 * tb, tb=tb, tile=tile)
+    assert res["rc"] == 0
+    assert {c[1] for c in res["launches"]} == {f"sweep_block<0,{r},{int(shape == 'box')},{kernel}>"}
+
+
 @pytest.mark.parametrize("rows,cols,shape,r,storage,kw,kernel", [
     (1024, 1024, "star", 1, "f32", {}, "sweep_step"), (8192, 8192, "star", 1, "f32", {}, "sweep_step"),
     (2000, 3000, "star", 4, "bf16", {}, "sweep_step"), (4096, 4096, "box", 4, "bf16", {}, "sweep_step"),
