@@ -32,7 +32,7 @@ def lib():
     global _lib
     if _lib is None:
         if not os.path.exists(_LIBPATH):
-            # compile the checker where it is used (gcc only; nothing of the GPU library is involved)
+            # compile the oracle where it is used (gcc only; nothing of the GPU library is involved)
             from . import build as _build
             _build.build()
         L = ctypes.CDLL(_LIBPATH)

@@ -1,6 +1,6 @@
 """Compile the CPU oracle (plain C + OpenMP) into ``oracle/liboracle.so``.
 
-Test infrastructure only: building the checker is not using it.  The flags
+Test infrastructure only: building the oracle is not using it.  The flags
 keep the arithmetic IEEE-exact (no fast-math, no contraction of a*b+c into an
 FMA except where the source calls fmaf explicitly).
 """
